@@ -15,8 +15,20 @@
 //   2. relax d in the model's own space (RM: raw, HM/PR: Hermite, RR: recursive Hermite
 //      (eq. RRformulas_D2Q9), CHM/CM/K: central (Hermite) moments obtained by the binomial shift
 //      by -u of d, whose inverse is eq. CHM2HM_Q9)
-//   3. A* = A^eq + d*  ->  raw moments (eq. HM2RM_Q9)  ->  populations (eq. Q9postCollVDF_RM)
+//   3. back to populations (eq. HM2RM_Q9, eq. Q9postCollVDF_RM).  Every map is linear and the density
+//      and momentum do not change, so only the *changes* D_pq = d*_pq - d_pq are carried back and
+//      added to the stored values: h* = h + P(D).
 //
+// The arithmetic is what bounds the fused kernels (vector-ALU issue in FP32 and FP16, see
+// lbm_step3.hpp), so it is written for few operations:
+//   - the equilibrium differences are chained through the momentum of the deviations,
+//       rho a^2 - rho_s A^2     = jx a + rho_s A (a - A),       jx = rho a - rho_s A,
+//       rho a^2 b - rho_s A^2 B = E20 b + rho_s A^2 (b - B),    rho a^2 b^2 - ... = E21 b + rho_s A^2 B (b - B)
+//     (two operations each; every factor stays a deviation, so nothing of order one cancels), and the
+//     constants rho_s A, rho_s A^2, ... come precomputed in Ref;
+//   - P(D) needs neither the equilibrium nor the conserved moments;
+//   - the central shifts are chained through the third order: t22 = d22 - uy (d21 + t21) - ux (d12 + t12);
+//   - BGK, RM and CM relax the raw fourth moment X = d22 + cs^2 (d20 + d02), which is also what P takes.
 // Relaxation vector (omega_nu, omega_b, omega_21, omega_12, omega_22): deviatoric and trace
 // parts of the second-order block, then the two third-order and the fourth-order moment.
 // The paper's (omega_nu, omega_3, omega_4) is omega_b = omega_nu, omega_21 = omega_12 = omega_3,
@@ -53,9 +65,11 @@ __host__ __device__ constexpr double rest_weight(int i) {
 }
 
 // Relaxation coefficients in the form used by the kernels: (1 - omega) factors, with the
-// second-order diagonal pair written as d20* = cpp d20 + cpm d02, d02* = cpm d20 + cpp d02.
+// second-order diagonal pair written as d20* = cpp d20 + cpm d02, d02* = cpm d20 + cpp d02, and the
+// factors k = c - 1 of the changes d* - d.
 template <typename R> struct Coef {
     R cpp, cpm, c11, c21, c12, c22, om;  // om = omega_nu (BGK)
+    R kpp, k11, k21, k12, k22;
 };
 
 template <typename R>
@@ -70,19 +84,55 @@ __host__ __device__ inline Coef<R> make_coef(const double w[5]) {
     c.c12 = R(1.0 - w[3]);
     c.c22 = R(1.0 - w[4]);
     c.om = R(w[0]);
+    c.kpp = R(-0.5 * (w[0] + w[1]));
+    c.k11 = R(-w[0]);
+    c.k21 = R(-w[2]);
+    c.k12 = R(-w[3]);
+    c.k22 = R(-w[4]);
     return c;
 }
 
-// Reference state of the stored deviations (density rho_s, velocity U).
+// Reference state of the stored deviations (density rho_s, velocity U = (A, B)) and the products of
+// it that the collision uses: jx = rho_s A, jy = rho_s B, a20 = rho_s A^2, a02 = rho_s B^2,
+// a21 = rho_s A^2 B.
 template <typename R> struct Ref {
     R rho, ux, uy;
+    R jx, jy, a20, a02, a21;
 };
+
+template <typename R>
+__host__ __device__ inline Ref<R> make_ref(double rho, double ux, double uy) {
+    return Ref<R>{R(rho), R(ux), R(uy), R(rho * ux), R(rho * uy), R(rho * ux * ux), R(rho * uy * uy), R(rho * ux * ux * uy)};
+}
+
+// Sums and differences of the stored populations that the density, the momentum and the raw
+// moments share: s13 = h1 + h3, s24 = h2 + h4, d13 = h1 - h3, d24 = h2 - h4 and the moments of the
+// diagonal populations m22, m11, m21 (less h2 - h4's share of jy), m12.
+template <typename R> struct Sums {
+    R s13, s24, d13, d24, m22, m11, m21, m12;
+};
+
+template <typename R>
+__host__ __device__ __forceinline__ Sums<R> sums_of(const R (&h)[9]) {
+    const R a = h[5] + h[7], b = h[6] + h[8], p = h[5] - h[7], q = h[8] - h[6];
+    Sums<R> s;
+    s.s13 = h[1] + h[3];
+    s.s24 = h[2] + h[4];
+    s.d13 = h[1] - h[3];
+    s.d24 = h[2] - h[4];
+    s.m22 = a + b;
+    s.m11 = a - b;
+    s.m12 = p + q;
+    s.m21 = p - q;
+    return s;
+}
 
 // Conserved quantities of a cell: drho = rho - rho_s, (jx, jy) = rho u - rho_s U (the momentum
 // of the stored deviations), u and du = u - U.
 template <typename R> struct Macro {
     R drho, rho, jx, jy, ux, uy, dux, duy;
     R inv_rho;  // 1 / rho
+    Sums<R> s;  // sums of the populations (macro_of; not set by macro_of_fields)
 };
 
 // Hermite equilibrium moments of order N (A^eq_pq = rho ux^p uy^q, zero above order N), as
@@ -187,7 +237,27 @@ __device__ __forceinline__ Neq<R> hermite_neq(const R (&h)[9], const Macro<R>& m
     return d;
 }
 
-// Collide one cell in place.  N is the equilibrium order (2, 3 or 4; CM, CHM and K use 4).
+// h += scale * P(D): the populations of the moment changes (D20, D02, D11, D21, D12) and of the raw
+// fourth-moment change M22, density and momentum unchanged (eq. HM2RM_Q9, eq. Q9postCollVDF_RM); the
+// pairs of opposite populations share their sums and differences.
+template <typename R>
+__device__ __forceinline__ void add_change(R (&h)[9], R scale, R D20, R D02, R D11, R D21, R D12, R M22) {
+    const R s1 = R(0.5) * scale, s5 = R(0.25) * scale;
+    const R u = D20 - M22, p = D02 - M22;
+    const R A = M22 + D11, B = M22 - D11, C = D12 + D21, D = D12 - D21;
+    h[0] = fmadd(scale, M22 - (D20 + D02), h[0]);
+    h[1] = fmadd(s1, u - D12, h[1]);
+    h[3] = fmadd(s1, u + D12, h[3]);
+    h[2] = fmadd(s1, p - D21, h[2]);
+    h[4] = fmadd(s1, p + D21, h[4]);
+    h[5] = fmadd(s5, A + C, h[5]);
+    h[6] = fmadd(s5, B - D, h[6]);
+    h[7] = fmadd(s5, A - C, h[7]);
+    h[8] = fmadd(s5, B + D, h[8]);
+}
+
+// Collide one cell in place.  N is the equilibrium order (2, 3 or 4; CM, CHM and K use 4).  In FP64
+// the populations are stored unshifted (the reference is zero) and its terms are left out.
 template <int MODEL, typename R>
 __device__ __forceinline__ void collide(R (&h)[9], const Macro<R>& m, const Ref<R>& ref,
                                         const Coef<R>& c, int N) {
@@ -195,65 +265,92 @@ __device__ __forceinline__ void collide(R (&h)[9], const Macro<R>& m, const Ref<
     if constexpr (MODEL == kStreamOnly) {
         return;
     } else {
-        const Eq<R> e = hermite_eq(m, ref, N);
+        constexpr bool kShifted = sizeof(R) == 4;
+        constexpr bool kCentral = MODEL == kCM || MODEL == kCHM || MODEL == kK;
+        constexpr bool kRawX = MODEL == kBGK || MODEL == kRM || MODEL == kCM;  // relaxes X (see the top)
+        const R ux = m.ux, uy = m.uy;
+        // equilibrium differences and non-equilibrium moments
+        R e20 = m.jx * ux, e02 = m.jy * uy;
+        R d11 = fmadd(-m.jx, uy, m.s.m11);
+        if constexpr (kShifted) {
+            e20 = fmadd(ref.jx, m.dux, e20);
+            e02 = fmadd(ref.jy, m.duy, e02);
+            d11 = fmadd(-ref.jx, m.duy, d11);
+        }
+        const R a20 = fmadd(-L::cs2, m.drho, m.s.s13 + m.s.m22);
+        const R a02 = fmadd(-L::cs2, m.drho, m.s.s24 + m.s.m22);
+        const R d20 = a20 - e20, d02 = a02 - e02;
+        R d21 = fmadd(-L::cs2, m.jy, m.s.m21);
+        R d12 = fmadd(-L::cs2, m.jx, m.s.m12);
+        // d22 = A22 - E22, or X = d22 + cs^2 (d20 + d02) = m22 - cs^4 drho - cs^2 (E20 + E02) - E22
+        R d22 = fmadd(-L::cs2, kRawX ? e20 + e02 : a20 + a02, fmadd(-L::cs4, m.drho, m.s.m22));
+        if (kCentral || N >= 3) {
+            R e21 = e20 * uy;
+            d12 = fmadd(-e02, ux, d12);
+            if constexpr (kShifted) {
+                e21 = fmadd(ref.a20, m.duy, e21);
+                d12 = fmadd(-ref.a02, m.dux, d12);
+            }
+            d21 = d21 - e21;
+            if (kCentral || N >= 4) {
+                d22 = fmadd(-e21, uy, d22);
+                if constexpr (kShifted) d22 = fmadd(-ref.a21, m.duy, d22);
+            }
+        }
         if constexpr (MODEL == kBGK) {
-            R heq[9];
-            hermite_to_pop(m, e.e20, e.e02, e.e11, e.e21, e.e12, e.e22, heq);
-#pragma unroll
-            for (int i = 0; i < 9; ++i) h[i] = h[i] - c.om * (h[i] - heq[i]);
+            add_change(h, -c.om, d20, d02, d11, d21, d12, d22);
         } else {
-            const Neq<R> d = hermite_neq(h, m, e);
             // second-order block, common to every moment space
-            const R n20 = c.cpp * d.d20 + c.cpm * d.d02;
-            const R n02 = c.cpm * d.d20 + c.cpp * d.d02;
-            const R n11 = c.c11 * d.d11;
-            R n21, n12, n22;
-            if constexpr (MODEL == kHM || MODEL == kPR) {
-                if constexpr (MODEL == kPR) {
-                    n21 = R(0); n12 = R(0); n22 = R(0);
-                } else {
-                    n21 = c.c21 * d.d21;
-                    n12 = c.c12 * d.d12;
-                    n22 = c.c22 * d.d22;
-                }
+            const R D20 = fmadd(c.kpp, d20, c.cpm * d02);
+            const R D02 = fmadd(c.kpp, d02, c.cpm * d20);
+            const R D11 = c.k11 * d11;
+            R D21, D12, M22;
+            if constexpr (MODEL == kHM) {
+                D21 = c.k21 * d21;
+                D12 = c.k12 * d12;
+                M22 = fmadd(c.k22, d22, L::cs2 * (D20 + D02));
+            } else if constexpr (MODEL == kPR) {
+                D21 = -d21;
+                D12 = -d12;
+                M22 = fmadd(L::cs2, D20 + D02, -d22);
             } else if constexpr (MODEL == kRM) {
-                // raw fourth-order moment: M22 - M22^eq = d22 + cs2 (d20 + d02)
-                n21 = c.c21 * d.d21;
-                n12 = c.c12 * d.d12;
-                n22 = c.c22 * (d.d22 + L::cs2 * (d.d20 + d.d02)) - L::cs2 * (n20 + n02);
+                D21 = c.k21 * d21;
+                D12 = c.k12 * d12;
+                M22 = c.k22 * d22;
             } else if constexpr (MODEL == kRR) {
                 // recursive non-equilibrium Hermite moments (eq. RRformulas_D2Q9)
-                n21 = c.c21 * (m.uy * d.d20 + R(2) * m.ux * d.d11);
-                n12 = c.c12 * (m.ux * d.d02 + R(2) * m.uy * d.d11);
-                n22 = c.c22 * (m.uy * m.uy * d.d20 + m.ux * m.ux * d.d02 + R(4) * m.ux * m.uy * d.d11);
-            } else {  // kCM, kCHM, kK: central Hermite moments t = shift(-u) of d
-                const R ux = m.ux, uy = m.uy;
-                const R t21 = d.d21 - uy * d.d20 - R(2) * ux * d.d11;
-                const R t12 = d.d12 - ux * d.d02 - R(2) * uy * d.d11;
-                const R t22 = d.d22 - R(2) * (uy * d.d21 + ux * d.d12) + uy * uy * d.d20 +
-                              ux * ux * d.d02 + R(4) * ux * uy * d.d11;
-                const R s21 = c.c21 * t21;
-                const R s12 = c.c12 * t12;
+                const R f11 = d11 + d11;
+                const R r21 = fmadd(ux, f11, uy * d20);
+                const R r12 = fmadd(uy, f11, ux * d02);
+                const R r22 = fmadd(ux, r12, uy * r21);
+                D21 = fmadd(c.c21, r21, -d21);
+                D12 = fmadd(c.c12, r12, -d12);
+                M22 = fmadd(c.c22, r22, fmadd(L::cs2, D20 + D02, -d22));
+            } else {  // kCM, kCHM, kK: central (Hermite) moments t = shift(-u) of d, s = t* - t
+                const R vx = ux + ux, vy = uy + uy;
+                const R t21 = fmadd(-vx, d11, fmadd(-uy, d20, d21));
+                const R t12 = fmadd(-vy, d11, fmadd(-ux, d02, d12));
+                const R t22 = fmadd(-ux, d12 + t12, fmadd(-uy, d21 + t21, d22));
+                const R s21 = c.k21 * t21;
+                const R s12 = c.k12 * t12;
                 R s22;
-                if constexpr (MODEL == kCHM) {
-                    s22 = c.c22 * t22;
-                } else if constexpr (MODEL == kCM) {
-                    // central fourth-order moment: k22 - k22^eq = t22 + cs2 (t20 + t02)
-                    s22 = c.c22 * (t22 + L::cs2 * (d.d20 + d.d02)) - L::cs2 * (n20 + n02);
+                if constexpr (MODEL == kCM) {
+                    s22 = c.k22 * t22;  // raw central fourth moment (t22 holds t22 + cs^2 (t20 + t02))
+                } else if constexpr (MODEL == kCHM) {
+                    s22 = fmadd(c.k22, t22, L::cs2 * (D20 + D02));
                 } else {
                     // fourth-order cumulant times rho: t22 - (t20 t02 + 2 t11^2) / rho
-                    const R inv = m.inv_rho;
-                    s22 = c.c22 * (t22 - (d.d20 * d.d02 + R(2) * d.d11 * d.d11) * inv) +
-                          (n20 * n02 + R(2) * n11 * n11) * inv;
+                    const R n20 = d20 + D20, n02 = d02 + D02, n11 = d11 + D11;
+                    const R p = fmadd(d11 + d11, d11, d20 * d02);
+                    const R q = fmadd(n11 + n11, n11, n20 * n02);
+                    s22 = fmadd(fmadd(-c.c22, p, q), m.inv_rho, fmadd(c.k22, t22, L::cs2 * (D20 + D02)));
                 }
                 // back to Hermite moments (eq. CHM2HM_Q9, equilibrium parts cancel)
-                n21 = s21 + uy * n20 + R(2) * ux * n11;
-                n12 = s12 + ux * n02 + R(2) * uy * n11;
-                n22 = s22 + R(2) * (uy * s21 + ux * s12) + uy * uy * n20 + ux * ux * n02 +
-                      R(4) * ux * uy * n11;
+                D21 = fmadd(vx, D11, fmadd(uy, D20, s21));
+                D12 = fmadd(vy, D11, fmadd(ux, D02, s12));
+                M22 = fmadd(ux, s12 + D12, fmadd(uy, s21 + D21, s22));
             }
-            hermite_to_pop(m, e.e20 + n20, e.e02 + n02, e.e11 + n11, e.e21 + n21, e.e12 + n12,
-                           e.e22 + n22, h);
+            add_change(h, R(1), D20, D02, D11, D21, D12, M22);
         }
     }
 }

@@ -190,37 +190,49 @@ __device__ __forceinline__ void prestream_store(S* __restrict__ dst, const Geom&
 template <typename S, typename R>
 __device__ __forceinline__ Macro<R> macro_of(const R (&h)[9], const Ref<R>& ref, double& rho_d) {
     Macro<R> m;
-    if constexpr (std::is_same<R, double>::value || std::is_same<S, _Float16>::value) {
-        m.drho = ((h[0] + (h[1] + h[3])) + (h[2] + h[4])) + ((h[5] + h[7]) + (h[6] + h[8]));
-        m.rho = ref.rho + m.drho;
+    m.s = sums_of(h);
+    m.jx = m.s.d13 + m.s.m12;
+    m.jy = m.s.d24 + m.s.m21;
+    if constexpr (std::is_same<R, double>::value) {
+        // unshifted storage: the reference is zero.  1 / rho by two Newton steps on the hardware
+        // reciprocal: each is one fused correction, so the result is within an ulp (and all but a few
+        // quotients correctly rounded) in five instructions against the eleven of a division
+        m.drho = (h[0] + m.s.s13) + (m.s.s24 + m.s.m22);
+        m.rho = m.drho;
         rho_d = m.rho;
+        R y = __builtin_amdgcn_rcp(m.rho);
+        y = fma(fma(-m.rho, y, 1.0), y, y);
+        m.inv_rho = fma(fma(-m.rho, y, 1.0), y, y);
+        m.ux = m.dux = m.jx * m.inv_rho;
+        m.uy = m.duy = m.jy * m.inv_rho;
     } else {
-        const double d = (((double)h[0] + ((double)h[1] + (double)h[3])) + ((double)h[2] + (double)h[4])) +
-                         (((double)h[5] + (double)h[7]) + ((double)h[6] + (double)h[8]));
-        rho_d = (double)ref.rho + d;
-        m.drho = (R)d;
-        m.rho = (R)rho_d;
-    }
-    m.jx = ((h[1] + h[5]) + h[8]) - ((h[3] + h[6]) + h[7]);
-    m.jy = ((h[2] + h[5]) + h[6]) - ((h[4] + h[7]) + h[8]);
-    // FP32 arithmetic takes the hardware reciprocal (1 ulp; the correctly rounded quotient costs
-    // nine more instructions per node): it scales O(u) quantities only, and every kernel that
-    // collides (plain, batched, adjoint) shares this function, so they stay bit-identical
-    if constexpr (std::is_same<R, float>::value)
+        if constexpr (std::is_same<S, _Float16>::value) {
+            m.drho = (h[0] + m.s.s13) + (m.s.s24 + m.s.m22);
+            m.rho = ref.rho + m.drho;
+            rho_d = m.rho;
+        } else {
+            const double d = (((double)h[0] + ((double)h[1] + (double)h[3])) + ((double)h[2] + (double)h[4])) +
+                             (((double)h[5] + (double)h[7]) + ((double)h[6] + (double)h[8]));
+            rho_d = (double)ref.rho + d;
+            m.drho = (R)d;
+            m.rho = (R)rho_d;
+        }
+        // FP32 arithmetic takes the hardware reciprocal (1 ulp; the correctly rounded quotient costs
+        // nine more instructions per node): it scales O(u) quantities only, and every kernel that
+        // collides (plain, batched, adjoint) shares this function, so they stay bit-identical
         m.inv_rho = __builtin_amdgcn_rcpf(m.rho);
-    else
-        m.inv_rho = R(1) / m.rho;
-    m.dux = (m.jx - m.drho * ref.ux) * m.inv_rho;
-    m.duy = (m.jy - m.drho * ref.uy) * m.inv_rho;
-    m.ux = ref.ux + m.dux;
-    m.uy = ref.uy + m.duy;
+        m.dux = fmadd(-m.drho, ref.ux, m.jx) * m.inv_rho;
+        m.duy = fmadd(-m.drho, ref.uy, m.jy) * m.inv_rho;
+        m.ux = ref.ux + m.dux;
+        m.uy = ref.uy + m.duy;
+    }
     return m;
 }
 
 // Conserved quantities of a node given by its macroscopic fields (FP64, initialisation).
 __host__ __device__ inline Macro<double> macro_of_fields(double rho, double ux, double uy,
                                                          const Ref<double>& r) {
-    Macro<double> m;
+    Macro<double> m{};
     m.rho = rho;
     m.ux = ux;
     m.uy = uy;
@@ -247,7 +259,7 @@ struct Pop9 {
 };
 
 inline Pop9 reference_populations(const Ref<double>& r, int N) {
-    const Ref<double> zero{0.0, 0.0, 0.0};
+    const Ref<double> zero = make_ref<double>(0.0, 0.0, 0.0);
     double h[9];
     eq_deviation(r.rho, r.ux, r.uy, zero, N, h);
     Pop9 p;
@@ -258,13 +270,13 @@ inline Pop9 reference_populations(const Ref<double>& r, int N) {
 // Reference of a precision: none for FP64; for shifted storage the values are rounded to FP32
 // once so that the FP32 kernels and the FP64 set-up use exactly the same reference.
 inline Ref<double> storage_reference(int prec, double rho0, double ux0, double uy0) {
-    if (prec == LBM_F64) return Ref<double>{0.0, 0.0, 0.0};
-    return Ref<double>{(double)(float)rho0, (double)(float)ux0, (double)(float)uy0};
+    if (prec == LBM_F64) return make_ref<double>(0.0, 0.0, 0.0);
+    return make_ref<double>((double)(float)rho0, (double)(float)ux0, (double)(float)uy0);
 }
 
 template <typename R>
 inline Ref<R> ref_as(const Ref<double>& r) {
-    return Ref<R>{(R)r.rho, (R)r.ux, (R)r.uy};
+    return make_ref<R>(r.rho, r.ux, r.uy);
 }
 
 // Record `step` in *flag (atomic min) if any lane of the wave saw a bad node.
@@ -318,7 +330,7 @@ int reduce_partials(lbm_ctx* ctx);  // d_tot[0..4] := sum over blocks of d_part 
 
 struct lbm_ctx {
     int nx = 0, ny = 0, prec = 0, eq_order = 4;
-    lbm::Ref<double> ref{0.0, 0.0, 0.0};  // storage reference: h_i = f_i - f^eq_N(rho_s, U)_i
+    lbm::Ref<double> ref{};                // storage reference: h_i = f_i - f^eq_N(rho_s, U)_i
     lbm::Pop9 fref{};                      // the reference populations
     char* buf = nullptr;          // caller-owned population buffer (two copies)
     size_t bytes = 0;

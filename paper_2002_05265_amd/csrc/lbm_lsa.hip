@@ -64,7 +64,7 @@ __global__ void k_lsa_jacobian(const lbm_lsa_point* __restrict__ pts, double* __
     const int p = blockIdx.x, i = threadIdx.x;
     if (i >= kQ) return;
     const lbm_lsa_point& q = pts[p];
-    const Ref<double> ref{0.0, 0.0, 0.0};  // FP64: populations stored unshifted
+    const Ref<double> ref = make_ref<double>(0.0, 0.0, 0.0);  // FP64: populations stored unshifted
     double h[9];
     eq_deviation(1.0, q.ux, q.uy, ref, q.eq_order, h);
     double rho_d;
