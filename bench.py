@@ -25,7 +25,8 @@ PROFILE_DIR = os.path.join(ROOT, "profiles")
 # while these are unchanged since the counters were taken
 STEP_SOURCES = ("paper_2002_05265_amd/csrc/lbm_core.hip", "paper_2002_05265_amd/csrc/lbm_cell.hpp",
                 "paper_2002_05265_amd/csrc/lbm_internal.hpp", "paper_2002_05265_amd/csrc/lbm_step2.hpp",
-                "paper_2002_05265_amd/csrc/lbm_step3.hpp", "paper_2002_05265_amd/build.py")
+                "paper_2002_05265_amd/csrc/lbm_step3.hpp", "paper_2002_05265_amd/csrc/lbm_walk.hpp",
+                "paper_2002_05265_amd/csrc/lbm_walk_kernel.hpp", "paper_2002_05265_amd/build.py")
 MODEL_ORDER = ("BGK", "RM", "HM", "CM", "CHM", "K", "PR", "RR")
 PREC_CODE = {"f64": 0, "f32": 1, "f16": 2}
 
@@ -50,6 +51,15 @@ def step_kernel_keys(model: str, prec: str):
     args = f"{MODEL_ORDER.index(model)}, {PREC_CODE[prec]}, "
     return [("k_step3", f"k_step3<{args}"), ("k_step3n", f"k_step3n<{args}"), ("k_step2", f"k_step2<{args}"),
             ("k_step", f"k_step<{args}")]
+
+
+def launch_kernel_keys(model: str, prec: str):
+    """(label, name prefix, steps per launch) of every kernel that advances the model, the one with the
+    most steps per launch first: the walking kernel (k_walk and its steps), then step_kernel_keys."""
+    args = f"{MODEL_ORDER.index(model)}, {PREC_CODE[prec]}, "
+    walk = [(f"k_walk{d}", f"k_walk<{args}{d}>", d) for d in ((6, 5, 4) if prec == "f16" else (8, 6, 4))]
+    steps = {"k_step3": 3, "k_step3n": 3, "k_step2": 2, "k_step": 1}
+    return walk + [(label, key, steps[label]) for label, key in step_kernel_keys(model, prec)]
 
 
 def repeated_windows(sims, models, omega, steps: int, k: int = 5):
@@ -106,7 +116,9 @@ def launch_us_from(ev):
 
 
 def launch_steps(sim, model: str) -> int:
-    """Steps one launch of `model` advances on `sim`: 3, 2 or 1."""
+    """Steps one launch of `model` advances on `sim`: those of its walking launches, else 3, 2 or 1."""
+    if hasattr(sim, "walk") and sim.walk(model)[0]:
+        return sim.walk(model)[0]
     ring = sim.fusion(model)[0]
     if not ring:
         return 1
@@ -728,8 +740,8 @@ def profile_summary(out_root: str, prec: str, n: int, commands: dict):
              "Command (from the repository root, with `cd /tmp && export TMPDIR=/tmp` semantics for",
              "the profiler's scratch files):", "", "```", commands["trace"], "```", "",
              f"Algorithmic bytes per launch: {n}*{n} nodes * 18 * {bytes_per_cell(prec) // 18} B = {alg} B "
-             "(every population read and written once; k_step3 and k_step3n advance three steps per "
-             "launch, k_step2 two, k_step one).",
+             "(every population read and written once; k_walk<d> advances d steps per launch, k_step3 and "
+             "k_step3n three, k_step2 two, k_step one).",
              "", "| kernel | calls | average us | min us | max us | GB/s at algorithmic bytes |",
              "|---|---|---|---|---|---|"]
     for r in stats:
@@ -738,7 +750,7 @@ def profile_summary(out_root: str, prec: str, n: int, commands: dict):
         avg = float(r["AverageNs"]) * 1e-3
         gbs = ""
         for m in MODEL_ORDER:
-            for label, key in step_kernel_keys(m, prec):
+            for label, key, _ in launch_kernel_keys(m, prec):
                 if key in name:
                     gbs = f"{alg / (avg * 1e-6) / 1e9:.1f}"
                     short = f"{label}<{m}, {prec}>"
@@ -764,13 +776,12 @@ def profile_summary(out_root: str, prec: str, n: int, commands: dict):
     rows = ["| kernel | dispatches | FETCH_SIZE KiB | WRITE_SIZE KiB | HBM bytes (scaled) | / algorithmic | VALUBusy % "
             "| flops per node and step |",
             "|---|---|---|---|---|---|---|---|"]
-    steps_of = {"k_step3": 3, "k_step3n": 3, "k_step2": 2, "k_step": 1}
     for m in MODEL_ORDER:
-        # the first kernel of the model found (three-step, then two-step, then single-step) is the
+        # the first kernel of the model found (most steps per launch first) is the
         # one reported; the single-step kernel (no halo recomputation) gives the algorithmic flops
         # per node update
         single = _flops_per_dispatch(flops, step_kernel_keys(m, prec)[-1][1], prec)
-        for label, key in step_kernel_keys(m, prec):
+        for label, key, steps in launch_kernel_keys(m, prec):
             f_kib, nf = _per_dispatch(fetch, key)
             w_kib, _ = _per_dispatch(write, key)
             if f_kib is None or w_kib is None:
@@ -779,7 +790,7 @@ def profile_summary(out_root: str, prec: str, n: int, commands: dict):
             vb, _ = _per_dispatch(valu, key)
             vtxt = "" if vb is None else f"{vb:.1f}"
             fl = _flops_per_dispatch(flops, key, prec)
-            executed = None if fl is None else fl / (cells * steps_of[label])
+            executed = None if fl is None else fl / (cells * steps)
             ftxt = "" if executed is None else f"{executed:.1f}"
             rows.append(f"| {label}<{m}, {prec}> | {nf} | {f_kib:.1f} | {w_kib:.1f} | {hbm:.4g} | {hbm / alg:.4f} | "
                         f"{vtxt} | {ftxt} |")
@@ -1081,7 +1092,7 @@ def main():
     dominant = max(models, key=lambda m: per_model[m]["launch_us"])  # the slowest kernel
     spl = per_model[dominant]["steps_per_launch"]
     dom_launch_us = per_model[dominant]["launch_us"]
-    kname = {3: "k_step3n" if args.prec == "f64" else "k_step3", 2: "k_step2", 1: "k_step"}[spl]
+    kname = {3: "k_step3n" if args.prec == "f64" else "k_step3", 2: "k_step2", 1: "k_step"}.get(spl, f"k_walk{spl}")
     for m in models:
         rec = counter_record(m, args.prec) if n == 4096 else None
         lu = per_model[m]["launch_us"]

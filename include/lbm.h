@@ -203,16 +203,28 @@ int lbm_set_fusion_depth(lbm_ctx* ctx, int model, int steps);
 /* Steps per fused launch of `model` (host pointer, may be NULL). */
 int lbm_get_fusion_depth(lbm_ctx* ctx, int model, int* steps);
 
+/* Walking launches of `model`: 4 to 8 steps per launch (4 to 6 in FP16), one wave walking down each
+ * strip of 112 columns and *rows rows with the steps kept in registers, so that each population is
+ * read and written once per launch.  A new context takes them for every model where the grid has
+ * enough strips to fill the device (from about 576 x 576 in FP64, 896 x 896 in FP16 and 1280 x 1280 in
+ * FP32); lbm_step then splits its steps into such launches of at most *steps steps and, for what they
+ * do not fill, the launches that lbm_get_fusion and lbm_get_fusion_depth describe.
+ * lbm_set_fusion and lbm_set_fusion_depth turn them off for the model, lbm_autotune keeps them where
+ * they are the fastest.  Bit-identical to single steps.  *steps = *rows = 0 when off; host pointers,
+ * each may be NULL. */
+int lbm_get_walk(lbm_ctx* ctx, int model, int* steps, int* rows);
+
 /* Autotune the launches of `model` on this context's grid: every single-step shape
  * (rows in {1, 2, 4} x xcd in {0, 1}), the two-step shapes (ring_rows, strip_rows) in
  * {(8, 8), (8, 16), (8, 40), (8, 64), (16, 16), (4, 16), (4, 20), (4, 64)} and, except for FP16,
  * the three-step shapes {(4, 8), (4, 16), (4, 32), (4, 64), (8, 8), (8, 16), (8, 24), (8, 32),
- * (8, 64), (8, 80), (8, 96), (8, 128)} are timed with HIP
+ * (8, 64), (8, 80), (8, 96), (8, 128)} and, where a new context may take them, the walking launches
+ * (lbm_get_walk) are timed with HIP
  * events over `trials` (>= 1) launches that recompute from the same input copy, so the state, the
  * step counter and the blow-up record are unchanged.  The fastest single-step shape is kept (it
  * also takes the last steps that do not fill a fused launch) and returned through rows_out /
  * xcd_out; the fastest fused shape per step is kept (lbm_get_fusion, lbm_get_fusion_depth) when it
- * beats it, and fusion is switched off otherwise.  us_per_step is the best time per step.  Host
+ * beats it, and fusion is switched off otherwise; walking launches are kept when they beat both.  us_per_step is the best time per step.  Host
  * pointers, each may be NULL.  Synchronises. */
 int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* rows_out,
                  int* xcd_out, double* us_per_step);

@@ -26,6 +26,7 @@
 #include "lbm_internal.hpp"
 #include "lbm_step2.hpp"
 #include "lbm_step3.hpp"
+#include "lbm_walk.hpp"
 
 using namespace lbm;
 
@@ -251,6 +252,57 @@ FusionPick deep_pick(int model, int nx, int ny, int prec, int cus) {
 // Widest strip for a model and precision; the launch uses it only while it still gives at least
 // kWideMinStrips strips (otherwise 64 columns keep enough workgroups in flight on small grids).
 constexpr long long kWideMinStrips = 1024;
+
+// Walking launches (lbm_walk.hpp) of a new context: the segment height that gives at most one wave per
+// slot of the device (two waves per SIMD in FP32 and FP16, one in FP64, where a wave takes more than half
+// of the SIMD's registers), so that all of them walk at once, and the most steps per launch that pays
+// for it; rows = 0 where the strip launches stay faster.  Measured on MI355X (us per step, walking
+// against the strip launches, BGK / K):
+// - FP64: 512^2 4.2 / 4.9 against 4.6 / 4.6, 576^2 4.5 / 5.1 against 5.2 / 5.5, 1024^2 8.1 / 10.2
+//   against 13.5 / 14.0, 2048^2 23.2 / 27.5 against 46.9 / 48.3, 4096^2 81 / 100 against 163 / 169;
+// - FP32: 1152^2 9.3 / 11.1 against 9.8 / 10.3, 1280^2 9.5 / 11.3 against 11.4 / 12.1, 2048^2 18.4 / 23.5
+//   against 26.2 / 27.6, 4096^2 55 / 73 against 88 / 86, 3001 x 2047 23.7 / 30.8 against 45.8 / 46.1;
+// - FP16: 768^2 5.8 / 7.4 against 6.2 / 6.3, 896^2 5.9 / 7.6 against 8.2 / 8.5, 2048^2 17.8 / 23.2 against
+//   27.0 / 28.8, 4096^2 50 / 68 against 77 / 80.
+// The line is drawn at the rows of a strip per slot (512^2 in FP64: 2.5, 576^2: 3.4; FP32 1152^2: 6.2,
+// 1280^2: 7.5; FP16 768^2: 2.6, 896^2: 3.5) and where at most a quarter of the strips' columns lie outside
+// the grid.  A segment's first 2 (D - 1) iterations fill up the D steps, so low segments take fewer: FP64
+// 768^2 (6 rows) 5.7 / 7.0 with six steps, 6.0 / 6.7 with four; 1152^2 (14 rows) 9.7 / 11.7 with six, 11.8
+// / 12.5 with four; 2048^2 (40 rows) 23.2 / 27.5 with six, 22.2 / 28.9 with eight; 4096^2 (152 rows) 89
+// / 103 with six; FP32 1408^2 (10 rows) 11.1 / 13.8 with six, 11.7 / 13.1 with four; 2600^2 (32 rows)
+// 28.2 / 33.6 with six, 26.5 / 34.0 with eight.
+struct WalkPick {
+    int rows, depth;
+};
+
+WalkPick walk_pick(int nx, int ny, int prec, int cus) {
+    static_assert(walk_cols<kF64>() == 2 && walk_cols<kF32>() == 2 && walk_cols<kF16>() == 2, "one strip width");
+    constexpr int V = walk_cols<kF32>(), W = walk_width<kF32>();
+    if (cus <= 0 || nx < 64 * V || ny < 2 * kWalkHalo) return {0, 0};
+    const long long sx = walk_strips(nx, W, V), slots = 4LL * cus * (prec == LBM_F64 ? 1 : 2);
+    const double per_slot = (double)sx * ny / (double)slots;
+    if (per_slot < (prec == LBM_F32_SHIFTED ? 7.2 : 3.2) || 3 * sx * W > 4LL * nx) return {0, 0};
+    const long long segments = std::max(1LL, slots / sx);
+    const int hs = (int)((ny + segments - 1) / segments + 1) / 2 * 2;
+    switch (prec) {
+        case LBM_F64: return {hs, hs < 8 ? 4 : (hs < 48 ? 6 : 8)};
+        case LBM_F32_SHIFTED: return {hs, hs < 14 ? 4 : (hs < 28 ? 6 : 8)};
+        default: return {hs, hs < 10 ? 4 : 6};
+    }
+}
+
+// Steps of the next launch of a run with `left` steps to go on walking launches of at most `depth`
+// steps: a split into the depths that exist (4, 6 and 8; 4, 5 and 6 in FP16) and, for what they do not
+// fill, the strip launches of at most 3 (2 in FP16) steps.
+int next_walk(int prec, int depth, int left) {
+    static constexpr signed char kNext8[16] = {0, 1, 2, 3, 4, 3, 6, 4, 8, 6, 6, 8, 6, 6, 8, 8};
+    static constexpr signed char kNext6[12] = {0, 1, 2, 3, 4, 3, 6, 4, 4, 6, 6, 4};
+    static constexpr signed char kNext4[8] = {0, 1, 2, 3, 4, 3, 3, 4};
+    static constexpr signed char kNextHalf[12] = {0, 1, 2, 2, 4, 5, 6, 5, 4, 5, 5, 6};
+    if (prec == LBM_F16_SHIFTED) return left >= 12 ? depth : kNextHalf[left];
+    if (left >= 2 * depth) return depth;
+    return depth == 8 ? kNext8[left] : (depth == 6 ? kNext6[left] : kNext4[left]);
+}
 
 template <int MODEL, int PREC>
 constexpr int strip_width() {
@@ -718,6 +770,46 @@ void launch_init_p(lbm_ctx* ctx, const double* rho, const double* ux, const doub
         }                                                     \
     } while (0)
 
+// `depth` steps of the whole grid in one walking launch src -> dst.
+void launch_walk(lbm_ctx* ctx, int model, const double* w, int depth, const void* src, void* dst) {
+    switch (ctx->prec) {
+        case LBM_F64: launch_walk_f64(ctx, model, w, depth, ctx->walk_rows, src, dst, (int)ctx->step); break;
+        case LBM_F32_SHIFTED: launch_walk_f32(ctx, model, w, depth, ctx->walk_rows, src, dst, (int)ctx->step); break;
+        default: launch_walk_f16(ctx, model, w, depth, ctx->walk_rows, src, dst, (int)ctx->step); break;
+    }
+}
+
+// nsteps steps on strip launches (three and two steps per launch where the model's setting has them)
+// and single steps.
+void step_strips(lbm_ctx* ctx, int model, const double* omega, int nsteps) {
+    const StepShape sh = ctx->shape_of(model);
+    const int ring = ctx->fuse_ring[lbm_ctx::slot(model)], hs = ctx->fuse_strip[lbm_ctx::slot(model)];
+    int s = 0;
+    if ((ring == 4 || ring == 8) && ctx->fuse_depth[lbm_ctx::slot(model)] == 3)
+        for (; s + 3 <= nsteps; s += 3) {
+            LBM_DISPATCH_PREC(ctx->prec, launch_step3_p, ctx, model, omega, ring, hs, ctx->copy(ctx->cur),
+                              ctx->copy(ctx->cur ^ 1), (int)ctx->step);
+            ctx->cur ^= 1;
+            ctx->step += 3;
+        }
+    if (ring > 0) {
+        // two steps left over by three-step launches (or asked for alone): the tail shape, if any
+        const bool tail = ctx->fuse_depth[lbm_ctx::slot(model)] == 3 && ctx->tail_ring[lbm_ctx::slot(model)] > 0;
+        const int ring2 = tail ? ctx->tail_ring[lbm_ctx::slot(model)] : ring;
+        const int hs2 = tail ? ctx->tail_strip[lbm_ctx::slot(model)] : hs;
+        for (; s + 2 <= nsteps; s += 2) {
+            LBM_DISPATCH_PREC(ctx->prec, launch_step2_p, ctx, model, omega, ring2, hs2, ctx->cur);
+            ctx->cur ^= 1;
+            ctx->step += 2;
+        }
+    }
+    for (; s < nsteps; ++s) {
+        LBM_DISPATCH_PREC(ctx->prec, launch_step_p, ctx, model, omega, sh, ctx->cur);
+        ctx->cur ^= 1;
+        ctx->step += 1;
+    }
+}
+
 __global__ void k_fill_int(int* __restrict__ p, int n, int v) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -838,6 +930,9 @@ int lbm_init_shifted(lbm_ctx** out, int nx, int ny, int prec, int eq_order, doub
             ctx->fuse_ring[k] = t.ring;
             ctx->fuse_strip[k] = t.strip;
         }
+    const WalkPick walk = walk_pick(nx, ny, prec, cus);
+    ctx->walk_rows = walk.rows;
+    for (int k = 0; k < 9; ++k) ctx->walk_depth[k] = walk.depth;
     int rc = check_hip(hipGetDevice(&ctx->device), "hipGetDevice");
     if (rc == LBM_OK) rc = scratch_address(ctx->device, &ctx->d_static);
     if (rc == LBM_OK) rc = check_hip(hipMalloc(&ctx->d_flag, sizeof(int)), "hipMalloc(flag)");
@@ -865,31 +960,17 @@ int lbm_step(lbm_ctx* ctx, int model, const double* omega, int nsteps) {
     rc = validate_omega(omega);
     if (rc != LBM_OK) return rc;
     if (ctx->step + nsteps >= INT_MAX) return set_error(LBM_EINVAL, "step counter would overflow");
-    const StepShape sh = ctx->shape_of(model);
-    const int ring = ctx->fuse_ring[lbm_ctx::slot(model)], hs = ctx->fuse_strip[lbm_ctx::slot(model)];
-    int s = 0;
-    if ((ring == 4 || ring == 8) && ctx->fuse_depth[lbm_ctx::slot(model)] == 3)
-        for (; s + 3 <= nsteps; s += 3) {
-            LBM_DISPATCH_PREC(ctx->prec, launch_step3_p, ctx, model, omega, ring, hs, ctx->copy(ctx->cur),
-                              ctx->copy(ctx->cur ^ 1), (int)ctx->step);
+    const int depth = ctx->walk_depth[lbm_ctx::slot(model)];
+    for (int left = nsteps; left > 0;) {
+        const int d = depth ? next_walk(ctx->prec, depth, left) : left;
+        if (depth && d >= 4) {
+            launch_walk(ctx, model, omega, d, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1));
             ctx->cur ^= 1;
-            ctx->step += 3;
+            ctx->step += d;
+        } else {
+            step_strips(ctx, model, omega, d);
         }
-    if (ring > 0) {
-        // two steps left over by three-step launches (or asked for alone): the tail shape, if any
-        const bool tail = ctx->fuse_depth[lbm_ctx::slot(model)] == 3 && ctx->tail_ring[lbm_ctx::slot(model)] > 0;
-        const int ring2 = tail ? ctx->tail_ring[lbm_ctx::slot(model)] : ring;
-        const int hs2 = tail ? ctx->tail_strip[lbm_ctx::slot(model)] : hs;
-        for (; s + 2 <= nsteps; s += 2) {
-            LBM_DISPATCH_PREC(ctx->prec, launch_step2_p, ctx, model, omega, ring2, hs2, ctx->cur);
-            ctx->cur ^= 1;
-            ctx->step += 2;
-        }
-    }
-    for (; s < nsteps; ++s) {
-        LBM_DISPATCH_PREC(ctx->prec, launch_step_p, ctx, model, omega, sh, ctx->cur);
-        ctx->cur ^= 1;
-        ctx->step += 1;
+        left -= d;
     }
     return check_hip(hipGetLastError(), "step kernel launch");
 }
@@ -1068,6 +1149,7 @@ int lbm_set_fusion(lbm_ctx* ctx, int model, int ring_rows, int strip_rows) {
     ctx->fuse_strip[lbm_ctx::slot(model)] = ring_rows ? strip_rows : 0;
     ctx->tail_ring[lbm_ctx::slot(model)] = 0;  // an explicit shape also takes the leftover steps
     ctx->tail_strip[lbm_ctx::slot(model)] = 0;
+    ctx->walk_depth[lbm_ctx::slot(model)] = 0;  // and all others
     return LBM_OK;
 }
 
@@ -1080,6 +1162,17 @@ int lbm_set_fusion_depth(lbm_ctx* ctx, int model, int steps) {
         return set_error(LBM_EUNSUPPORTED, "three steps per launch need an FP32 or FP64 context");
     if (steps == 3 && (ctx->nx < 2 || ctx->ny < 2)) return set_error(LBM_EUNSUPPORTED, "grid below 2 x 2");
     ctx->fuse_depth[lbm_ctx::slot(model)] = steps;
+    ctx->walk_depth[lbm_ctx::slot(model)] = 0;
+    return LBM_OK;
+}
+
+int lbm_get_walk(lbm_ctx* ctx, int model, int* steps, int* rows) {
+    if (!ctx) return set_error(LBM_ESTATE, "context is NULL");
+    const int rc = validate_model(model, 4);
+    if (rc != LBM_OK) return rc;
+    const int depth = ctx->walk_depth[lbm_ctx::slot(model)];
+    if (steps) *steps = depth;
+    if (rows) *rows = depth ? ctx->walk_rows : 0;
     return LBM_OK;
 }
 
@@ -1179,6 +1272,16 @@ int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* 
             best_depth = 3;
         }
     }
+    // walking launches, per step, on the grids where a new context may take them
+    int best_walk = 0;
+    for (int depth = 4; depth <= 8 && rc == LBM_OK && ctx->walk_rows > 0; depth += 2) {
+        if (depth == 8 && ctx->prec == LBM_F16_SHIFTED) continue;
+        const float ms = timed([&] { launch_walk(ctx, model, omega, depth, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1)); }) / (float)depth;
+        if (rc == LBM_OK && ms < best) {
+            best = ms;
+            best_walk = depth;
+        }
+    }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     if (rc == LBM_OK)
@@ -1191,6 +1294,7 @@ int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* 
     ctx->fuse_ring[lbm_ctx::slot(model)] = best_ring;
     ctx->fuse_strip[lbm_ctx::slot(model)] = best_strip;
     ctx->fuse_depth[lbm_ctx::slot(model)] = best_depth;
+    ctx->walk_depth[lbm_ctx::slot(model)] = best_walk;
     // the fastest two-step shape takes the two steps left after three-step launches, if it beats
     // one step per launch
     const bool tail = best_depth == 3 && best_ring > 0 && tail_ring > 0 && best2 < best1;

@@ -326,6 +326,11 @@ struct lbm_ctx;
 namespace lbm {
 int reset_blowup(lbm_ctx* ctx);     // blow-up record := none (kernel on the context's stream)
 int reduce_partials(lbm_ctx* ctx);  // d_tot[0..4] := sum over blocks of d_part (fixed order)
+// One launch of the walking kernel: `depth` steps src -> dst of the whole grid on segments of hs rows
+// (lbm_walk.hpp; depth 4, 6 or, in FP64 and FP32, 8 and, in FP16, 5).
+void launch_walk_f64(lbm_ctx* ctx, int model, const double* w, int depth, int hs, const void* src, void* dst, int step);
+void launch_walk_f32(lbm_ctx* ctx, int model, const double* w, int depth, int hs, const void* src, void* dst, int step);
+void launch_walk_f16(lbm_ctx* ctx, int model, const double* w, int depth, int hs, const void* src, void* dst, int step);
 }  // namespace lbm
 
 struct lbm_ctx {
@@ -363,6 +368,9 @@ struct lbm_ctx {
     // and strip height (0: those of fuse_ring / fuse_strip)
     int tail_ring[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     int tail_strip[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    // walking launches (lbm_walk.hpp): most steps per launch, per model (0 = off), and rows per segment
+    int walk_depth[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    int walk_rows = 0;
 
     static int slot(int model) { return (model >= 0 && model < 8) ? model : 8; }
     lbm::StepShape shape_of(int model) const {

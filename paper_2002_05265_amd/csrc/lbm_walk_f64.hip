@@ -1,0 +1,7 @@
+#include "lbm_walk_kernel.hpp"
+
+namespace lbm {
+void launch_walk_f64(lbm_ctx* ctx, int model, const double* w, int depth, int hs, const void* src, void* dst, int step) {
+    launch_walk_p<kF64>(ctx, model, w, depth, hs, src, dst, step);
+}
+}  // namespace lbm

@@ -68,6 +68,10 @@ class Sim:
         the steps per launch)."""
         return B.lbm_get_fusion(self.ctx, _model_code(model))
 
+    def walk(self, model):
+        """(steps per launch, rows per segment) of `model`'s walking launches, (0, 0) when off."""
+        return B.lbm_get_walk(self.ctx, _model_code(model))
+
     def autotune(self, model, omega, trials: int = 10):
         """Pick the fastest launches for `model` (state unchanged); returns the single-step shape
         (rows, xcd) and the best microseconds per step; fusion() and fusion_depth() give the fused

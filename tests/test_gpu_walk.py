@@ -1,0 +1,108 @@
+"""Walking launches (several steps in registers, lbm_get_walk) against single steps: the same arithmetic
+per node on values of the stored type, so states, step counters and blow-up steps are bit-identical.
+Grids at every depth of every precision whose sides are multiples of neither the strip width (112
+columns, the last strip down to two), a lane's two columns, nor the segment height; step counts that
+take every depth and every leftover; blow-ups in each step of a launch, on strip and segment edges."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2002_05265_amd import inputs
+from paper_2002_05265_amd.sim import Sim
+
+pytestmark = pytest.mark.gpu
+
+MODELS = list(inputs.MODEL_NAMES) + ["STREAM_ONLY"]
+# (precision, nx, ny, most steps per launch, steps): the steps split into 8 8 6 4 3; 6 6 6 4 4 3;
+# 4 4 3 2; in FP16 6 6 5 2 and 4 5 4
+CASES = [("f64", 671, 590, 4, 13), ("f64", 1009, 997, 6, 29), ("f64", 2465, 2410, 8, 29),
+         ("f32", 1345, 1290, 4, 13), ("f32", 1905, 1801, 6, 29), ("f32", 2689, 2300, 8, 29),
+         ("f16", 897, 905, 4, 13), ("f16", 1457, 1403, 6, 19)]
+
+
+def rough(nx, ny, seed, device):
+    """A vortex on a mean flow with 1% noise on every node."""
+    rho, ux, uy = (torch.from_numpy(a).to(device) for a in inputs.vortex_fields(nx, ny, 0.2))
+    g = torch.Generator(device=device).manual_seed(seed)
+    return [a + 0.01 * torch.randn(a.shape, generator=g, device=device, dtype=torch.float64)
+            for a in (rho, ux, uy)]
+
+
+def pair(gpu, prec, model, nx, ny, omega, steps, order=4):
+    fields = rough(nx, ny, nx + ny, gpu)
+    ref = (0.2 * inputs.CS, 0.01)
+    a = Sim(*fields, prec=prec, eq_order=order, device=gpu, ref_velocity=ref)
+    b = Sim(*fields, prec=prec, eq_order=order, device=gpu, ref_velocity=ref)
+    a.set_fusion(model, 0)
+    assert a.walk(model) == (0, 0)
+    walk = b.walk(model)
+    a.step(model, omega, steps)
+    b.step(model, omega, steps)
+    same = torch.equal(a.state(), b.state())
+    st = (a.status(), b.status())
+    a.close()
+    b.close()
+    return walk, same, st
+
+
+@pytest.mark.parametrize("prec,nx,ny,depth,steps", CASES)
+def test_walk_bit_identical(gpu, prec, nx, ny, depth, steps):
+    rng = np.random.default_rng(nx)
+    # every model at the depths that one precision tests on small grids, four on the others
+    models = MODELS if nx * ny < 2_000_000 else [MODELS[(nx + 2 * k) % 9] for k in range(4)]
+    for k, model in enumerate(models):
+        omega = inputs.rates(1e-2, "REG") if k % 2 else np.array([1.8, *rng.uniform(0.6, 1.8, 4)])
+        order = 2 + k % 3 if model in ("BGK", "RM", "HM", "PR", "RR") else 4
+        print(f"walk {prec} {model} {nx}x{ny} order {order} steps {steps}", flush=True)
+        walk, same, (ta, tb) = pair(gpu, prec, model, nx, ny, omega, steps, order)
+        assert walk[0] == depth
+        assert same and ta == tb == (steps, -1)
+
+
+@pytest.mark.parametrize("prec,depth", [("f64", 4), ("f32", 4), ("f16", 4), ("f64", 6)])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12])
+def test_walk_step_counts(gpu, prec, depth, n):
+    nx, ny = {"f64": (640, 620) if depth == 4 else (960, 900), "f32": (1344, 1290), "f16": (896, 900)}[prec]
+    print(f"walk {prec} {nx}x{ny} steps {n}", flush=True)
+    walk, same, (ta, tb) = pair(gpu, prec, "RR", nx, ny, inputs.rates(1e-2, "SRT"), n)
+    assert walk[0] == depth
+    assert same and ta == tb == (n, -1)
+
+
+@pytest.mark.parametrize("prec,nx,ny", [("f64", 673, 600), ("f64", 1000, 1000), ("f32", 1343, 1300), ("f16", 897, 905)])
+def test_walk_blowup_step(gpu, prec, nx, ny):
+    # zero rates: populations only stream.  f_3 = f_1 = -0.6 planted d nodes right and left of a node
+    # meet there d steps later and make its density negative; nowhere before
+    one, zero = np.ones((ny, nx)), np.zeros((ny, nx))
+    f = torch.from_numpy(oracle.init_eq(4, one, zero, zero)).to(gpu)
+    rows = Sim(one, zero, zero, prec=prec, device=gpu).walk("BGK")[1]
+    for ax, ay in ((111, rows), (112, rows - 1), (0, 0), (nx - 1, ny - 1), (113, 3 * rows + 1)):
+        for d in range(1, 7):
+            g = f.clone()
+            g[3, ay, (ax + d) % nx] = g[1, ay, (ax - d) % nx] = -0.6
+            s = Sim(one, zero, zero, prec=prec, device=gpu)
+            assert s.walk("BGK")[0] in (4, 6)
+            s.set_state(g, 10)
+            s.step("BGK", [0.0] * 5, 12)
+            assert s.status() == (22, 10 + d), (ax, ay, d)
+            s.close()
+
+
+def test_walk_settings(gpu):
+    one, zero = np.ones((700, 700)), np.zeros((700, 700))
+    s = Sim(one, zero, zero, prec="f64", device=gpu)
+    depth, rows = s.walk("K")
+    assert depth == 4 and rows % 2 == 0
+    s.set_fusion("K", 8, 16)
+    s.set_fusion_depth("RR", 3)
+    assert s.walk("K") == s.walk("RR") == (0, 0) and s.walk("CM") == (depth, rows)
+    s.autotune("K", inputs.rates(1e-2), 2)
+    assert s.walk("K")[0] in (0, 4, 6, 8)
+    s.close()
+    # too few strips, too narrow, too low
+    for prec, nx, ny in (("f64", 512, 512), ("f32", 1024, 1024), ("f16", 768, 768), ("f64", 120, 40000),
+                         ("f64", 130, 40000), ("f64", 40000, 15)):
+        t = Sim(np.ones((ny, nx)), np.zeros((ny, nx)), np.zeros((ny, nx)), prec=prec, device=gpu)
+        assert t.walk("BGK") == (0, 0), (prec, nx, ny)
+        t.close()
