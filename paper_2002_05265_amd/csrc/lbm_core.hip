@@ -395,17 +395,23 @@ __global__ __launch_bounds__(64 * step3_waves<RING>()) void k_step3n(const typen
 }
 
 // Macroscopic fields of the state f(., n) (pulled from the post-collision copy) and per-block
-// partial sums of {rho, rho ux, rho uy, rho |u|^2 / 2, |u|^2} in FP64.
+// partial sums of {rho, rho ux, rho uy, rho |u|^2 / 2, |u|^2} in FP64.  A thread takes `rows` nodes of
+// its column (moment_rows): the block's sum costs thirty cross-lane exchanges per thread and a row of
+// partials, which with one node per thread bounded the FP16 kernel (213 us at 4096^2, where its bytes
+// take 135) and left k_finalize 65536 rows to add in one block (124 us).
 template <int PREC>
 __global__ __launch_bounds__(256) void k_moments(const typename Store<PREC>::S* __restrict__ src,
                                                  Geom g, Ref<double> ref, double* __restrict__ rho,
                                                  double* __restrict__ ux, double* __restrict__ uy,
                                                  double* __restrict__ partials, int step,
-                                                 int* __restrict__ blowup) {
+                                                 int* __restrict__ blowup, int rows) {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
+    const int y0 = blockIdx.y * blockDim.y * rows + threadIdx.y;
     double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (x < g.nx && y < g.ny) {
+    bool bad = false;
+    for (int k = 0; k < rows; ++k) {
+        const int y = y0 + k * (int)blockDim.y;
+        if (x >= g.nx || y >= g.ny) break;
         const Nbr nb = neighbours(x, y, g.nx, g.ny);
         double h[9];
         pull_load(src, g.plane, nb, h);
@@ -418,15 +424,24 @@ __global__ __launch_bounds__(256) void k_moments(const typename Store<PREC>::S* 
         if (ux) ux[c] = u;
         if (uy) uy[c] = w;
         const double u2 = u * u + w * w;
-        v[0] = r; v[1] = r * u; v[2] = r * w; v[3] = 0.5 * r * u2; v[4] = u2;
-        flag_bad(!(r > 0.0), blowup, step);
+        v[0] += r; v[1] += r * u; v[2] += r * w; v[3] += 0.5 * r * u2; v[4] += u2;
+        bad = bad || !(r > 0.0);
     }
+    flag_bad(bad, blowup, step);
     block_sum<5>(v, partials + 5 * (size_t)(blockIdx.y * gridDim.x + blockIdx.x));
 }
 
-// Sum nblocks rows of 5 partials in a fixed order (one block of 256 threads).
-__global__ __launch_bounds__(256) void k_finalize(const double* __restrict__ partials, int nblocks,
-                                                  double* __restrict__ out) {
+// Nodes per thread of k_moments: a power of two up to 16 that leaves about eight blocks per CU.
+int moment_rows(int nblocks) {
+    int rows = 1;
+    while (rows < 16 && nblocks / (2 * rows) >= 2048) rows *= 2;
+    return rows;
+}
+
+// Sum nblocks rows of 5 partials in a fixed order (one block).
+constexpr int kFinalizeThreads = 1024;
+__global__ __launch_bounds__(kFinalizeThreads) void k_finalize(const double* __restrict__ partials, int nblocks,
+                                                               double* __restrict__ out) {
     double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     for (int b = threadIdx.x; b < nblocks; b += blockDim.x)
         for (int k = 0; k < 5; ++k) v[k] += partials[5 * (size_t)b + k];
@@ -727,13 +742,25 @@ void launch_step_p(lbm_ctx* ctx, int model, const double* w, const StepShape& sh
     }
 }
 
+// Launches k_moments; returns the number of its blocks (rows of partial sums).
 template <int PREC>
-void launch_moments_p(lbm_ctx* ctx, double* rho, double* ux, double* uy, double* partials) {
+int launch_moments_p(lbm_ctx* ctx, double* rho, double* ux, double* uy, double* partials) {
     using S = typename Store<PREC>::S;
-    const Launch l = launch_for(ctx->nx, ctx->ny);
+    Launch l = launch_for(ctx->nx, ctx->ny);
+    const int rows = moment_rows(ctx->nblocks);
+    l.grid.y = (l.grid.y + rows - 1) / rows;
     hipLaunchKernelGGL((k_moments<PREC>), l.grid, l.block, 0, ctx->stream,
                        reinterpret_cast<const S*>(ctx->copy(ctx->cur)), ctx->geom(), ctx->ref, rho,
-                       ux, uy, partials, (int)ctx->step, ctx->d_flag);
+                       ux, uy, partials, (int)ctx->step, ctx->d_flag, rows);
+    return (int)(l.grid.x * l.grid.y);
+}
+
+int launch_moments(lbm_ctx* ctx, double* rho, double* ux, double* uy, double* partials) {
+    switch (ctx->prec) {
+        case LBM_F64: return launch_moments_p<kF64>(ctx, rho, ux, uy, partials);
+        case LBM_F32_SHIFTED: return launch_moments_p<kF32>(ctx, rho, ux, uy, partials);
+        default: return launch_moments_p<kF16>(ctx, rho, ux, uy, partials);
+    }
 }
 
 template <int PREC>
@@ -827,7 +854,8 @@ namespace lbm {
 int reset_blowup(lbm_ctx* ctx) { return reset_flag(ctx); }
 
 int reduce_partials(lbm_ctx* ctx) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, ctx->stream, ctx->d_part, ctx->nblocks, ctx->d_tot);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kFinalizeThreads), 0, ctx->stream, ctx->d_part, ctx->nblocks,
+                       ctx->d_tot);
     return check_hip(hipGetLastError(), "finalize kernel launch");
 }
 
@@ -1058,11 +1086,10 @@ int lbm_step3_raw_many(lbm_ctx* ctx, int model, const double* omega, const void*
 
 int lbm_moments(lbm_ctx* ctx, double* rho, double* ux, double* uy, double* totals) {
     if (!ctx) return set_error(LBM_ESTATE, "context is NULL");
-    LBM_DISPATCH_PREC(ctx->prec, launch_moments_p, ctx, rho, ux, uy, ctx->d_part);
+    const int nb = launch_moments(ctx, rho, ux, uy, ctx->d_part);
     int rc = check_hip(hipGetLastError(), "moments kernel launch");
     if (rc != LBM_OK || !totals) return rc;
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, ctx->stream, ctx->d_part, ctx->nblocks,
-                       ctx->d_tot);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kFinalizeThreads), 0, ctx->stream, ctx->d_part, nb, ctx->d_tot);
     rc = check_hip(hipGetLastError(), "finalize kernel launch");
     double t[5];
     if (rc == LBM_OK)
@@ -1084,10 +1111,10 @@ int lbm_moments_noalloc(lbm_ctx* ctx, double* rho, double* ux, double* uy, doubl
                          ctx->nx, ctx->ny, ctx->nblocks, kNoAllocMaxBlocks);
     double* part = ctx->d_static;
     double* tot = ctx->d_static + 5 * (size_t)kNoAllocMaxBlocks;
-    LBM_DISPATCH_PREC(ctx->prec, launch_moments_p, ctx, rho, ux, uy, part);
+    const int nb = launch_moments(ctx, rho, ux, uy, part);
     int rc = check_hip(hipGetLastError(), "moments kernel launch");
     if (rc != LBM_OK || !totals) return rc;
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, ctx->stream, part, ctx->nblocks, tot);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kFinalizeThreads), 0, ctx->stream, part, nb, tot);
     rc = check_hip(hipGetLastError(), "finalize kernel launch");
     if (rc != LBM_OK) return rc;
     hipLaunchKernelGGL(k_totals_out, dim3(1), dim3(64), 0, ctx->stream, tot,
