@@ -291,17 +291,36 @@ WalkPick walk_pick(int nx, int ny, int prec, int cus) {
     }
 }
 
-// Steps of the next launch of a run with `left` steps to go on walking launches of at most `depth`
-// steps: a split into the depths that exist (4, 6 and 8; 4, 5 and 6 in FP16) and, for what they do not
-// fill, the strip launches of at most 3 (2 in FP16) steps.
-int next_walk(int prec, int depth, int left) {
-    static constexpr signed char kNext8[16] = {0, 1, 2, 3, 4, 3, 6, 4, 8, 6, 6, 8, 6, 6, 8, 8};
-    static constexpr signed char kNext6[12] = {0, 1, 2, 3, 4, 3, 6, 4, 4, 6, 6, 4};
-    static constexpr signed char kNext4[8] = {0, 1, 2, 3, 4, 3, 3, 4};
-    static constexpr signed char kNextHalf[12] = {0, 1, 2, 2, 4, 5, 6, 5, 4, 5, 5, 6};
-    if (prec == LBM_F16_SHIFTED) return left >= 12 ? depth : kNextHalf[left];
-    if (left >= 2 * depth) return depth;
-    return depth == 8 ? kNext8[left] : (depth == 6 ? kNext6[left] : kNext4[left]);
+// The launches of a run of n <= kPlanMax steps: plan[i] steps in launch i, their number returned.  Walking
+// launches of the depths that exist (4, 6 and 8; 4, 5 and 6 in FP16) up to `depth` (5 in FP16 also for 4), and strip launches of
+// one step and of those of 2 and 3 that `pieces` (bit d: d steps) has, at the least total of kCost, the time of a
+// launch of d steps at 4096^2 (in 50 us in FP64, in 10 us in FP16; FP32 lies between FP64 and FP16); with
+// parity 0 or 1 among the splits into an even or odd number of launches only.
+constexpr int kPlanMax = 20;
+
+int plan_walk(int prec, int depth, int n, unsigned pieces, int parity, signed char (&plan)[kPlanMax]) {
+    static constexpr signed char kCost[9] = {0, 9, 9, 10, 10, 0, 12, 0, 15};
+    static constexpr signed char kCostHalf[9] = {0, 11, 15, 0, 22, 26, 30, 0, 0};
+    const signed char* cost = prec == LBM_F16_SHIFTED ? kCostHalf : kCost;
+    const int most = prec == LBM_F16_SHIFTED ? std::max(depth, 5) : depth;
+    int best[kPlanMax + 1][2], last[kPlanMax + 1][2];
+    for (int m = 0; m <= n; ++m)
+        for (int o = 0; o < 2; ++o) {
+            best[m][o] = m == 0 && o == 0 ? 0 : INT_MAX;
+            last[m][o] = 0;
+            for (int d = 1; d <= 8 && d <= m; ++d) {
+                if (!cost[d] || (d < 4 ? !(pieces >> d & 1) : d > most) || best[m - d][o ^ 1] == INT_MAX) continue;
+                const int c = best[m - d][o ^ 1] + cost[d];
+                if (c < best[m][o]) {
+                    best[m][o] = c;
+                    last[m][o] = d;
+                }
+            }
+        }
+    int o = parity >= 0 ? parity : best[n][1] < best[n][0], k = 0;
+    for (int m = n; m > 0; m -= last[m][o], o ^= 1) plan[k++] = (signed char)last[m][o];
+    std::sort(plan, plan + k, [](signed char x, signed char y) { return x > y; });
+    return k;
 }
 
 template <int MODEL, int PREC>
@@ -806,6 +825,18 @@ void launch_walk(lbm_ctx* ctx, int model, const double* w, int depth, const void
     }
 }
 
+// Strip launches of `model`: bit d set where one launch advances d steps, and the launches of n steps.
+unsigned strip_pieces(const lbm_ctx* ctx, int model) {
+    const int k = lbm_ctx::slot(model), ring = ctx->fuse_ring[k];
+    return 2u | (ring > 0 ? 4u : 0u) | ((ring == 4 || ring == 8) && ctx->fuse_depth[k] == 3 ? 8u : 0u);
+}
+
+int strip_launches(const lbm_ctx* ctx, int model, int n) {
+    const unsigned pieces = strip_pieces(ctx, model);
+    const int most = pieces & 8 ? 3 : (pieces & 4 ? 2 : 1);
+    return (n + most - 1) / most;
+}
+
 // nsteps steps on strip launches (three and two steps per launch where the model's setting has them)
 // and single steps.
 void step_strips(lbm_ctx* ctx, int model, const double* omega, int nsteps) {
@@ -989,17 +1020,32 @@ int lbm_step(lbm_ctx* ctx, int model, const double* omega, int nsteps) {
     if (rc != LBM_OK) return rc;
     if (ctx->step + nsteps >= INT_MAX) return set_error(LBM_EINVAL, "step counter would overflow");
     const int depth = ctx->walk_depth[lbm_ctx::slot(model)];
-    for (int left = nsteps; left > 0;) {
-        const int d = depth ? next_walk(ctx->prec, depth, left) : left;
-        if (depth && d >= 4) {
-            launch_walk(ctx, model, omega, d, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1));
-            ctx->cur ^= 1;
-            ctx->step += d;
-        } else {
-            step_strips(ctx, model, omega, d);
-        }
-        left -= d;
+    if (!depth) {
+        step_strips(ctx, model, omega, nsteps);
+        return check_hip(hipGetLastError(), "step kernel launch");
     }
+    // A captured run leaves the state in the copy that the strip launches would leave it in: one with an
+    // even number of them can be replayed to go on from its own result
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (ctx->stream) {
+        rc = check_hip(hipStreamIsCapturing(ctx->stream, &cap), "hipStreamIsCapturing");
+        if (rc != LBM_OK) return rc;
+    }
+    int parity = cap == hipStreamCaptureStatusNone ? -1 : strip_launches(ctx, model, nsteps) & 1;
+    auto launch = [&](int d) {
+        if (d < 4) return step_strips(ctx, model, omega, d);
+        launch_walk(ctx, model, omega, d, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1));
+        ctx->cur ^= 1;
+        ctx->step += d;
+    };
+    int left = nsteps;
+    for (; left > kPlanMax; left -= depth) {
+        launch(depth);
+        if (parity >= 0) parity ^= 1;
+    }
+    signed char plan[kPlanMax];
+    const int k = plan_walk(ctx->prec, depth, left, strip_pieces(ctx, model), parity, plan);
+    for (int i = 0; i < k; ++i) launch(plan[i]);
     return check_hip(hipGetLastError(), "step kernel launch");
 }
 

@@ -106,3 +106,30 @@ def test_walk_settings(gpu):
         t = Sim(np.ones((ny, nx)), np.zeros((ny, nx)), np.zeros((ny, nx)), prec=prec, device=gpu)
         assert t.walk("BGK") == (0, 0), (prec, nx, ny)
         t.close()
+
+
+@pytest.mark.parametrize("prec,nx,ny,n", [("f64", 700, 640, 12), ("f64", 1009, 997, 4), ("f32", 1408, 1400, 6),
+                                          ("f32", 1408, 1400, 40), ("f16", 1000, 1003, 8), ("f16", 1000, 1003, 14)])
+def test_walk_captured_run(gpu, prec, nx, ny, n):
+    # an even number of strip launches: the captured run ends in the copy it starts from and can be
+    # replayed to go on, with eager work between the replays
+    omega = inputs.rates(1e-2, "REG")
+    stream = torch.cuda.Stream(gpu)
+    with torch.cuda.stream(stream):
+        fields = rough(nx, ny, 5, gpu)
+        a, b = (Sim(*fields, prec=prec, device=gpu) for _ in range(2))
+        print(f"walk {prec} {nx}x{ny} captured run of {n}", flush=True)
+        b.step("K", omega, n)
+        start = b.state()
+        b.set_state(a.state(), 0)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            b.step("K", omega, n)
+        for r in range(4):
+            a.step("K", omega, n)
+            g.replay()
+            assert torch.equal(a.state(), b.state()), r
+            assert r or torch.equal(start, b.state())
+    a.close()
+    b.close()
+
