@@ -26,7 +26,8 @@ PROFILE_DIR = os.path.join(ROOT, "profiles")
 STEP_SOURCES = ("paper_2002_05265_amd/csrc/lbm_core.hip", "paper_2002_05265_amd/csrc/lbm_cell.hpp",
                 "paper_2002_05265_amd/csrc/lbm_internal.hpp", "paper_2002_05265_amd/csrc/lbm_step2.hpp",
                 "paper_2002_05265_amd/csrc/lbm_step3.hpp", "paper_2002_05265_amd/csrc/lbm_walk.hpp",
-                "paper_2002_05265_amd/csrc/lbm_walk_kernel.hpp", "paper_2002_05265_amd/build.py")
+                "paper_2002_05265_amd/csrc/lbm_walk_kernel.hpp", "paper_2002_05265_amd/csrc/lbm_tile_kernel.hpp",
+                "paper_2002_05265_amd/build.py")
 MODEL_ORDER = ("BGK", "RM", "HM", "CM", "CHM", "K", "PR", "RR")
 PREC_CODE = {"f64": 0, "f32": 1, "f16": 2}
 
@@ -116,9 +117,11 @@ def launch_us_from(ev):
 
 
 def launch_steps(sim, model: str) -> int:
-    """Steps one launch of `model` advances on `sim`: those of its walking launches, else 3, 2 or 1."""
-    if hasattr(sim, "walk") and sim.walk(model)[0]:
-        return sim.walk(model)[0]
+    """Steps one launch of `model` advances on `sim`: those of its walking or tile launches, else 3, 2
+    or 1."""
+    for kind in ("walk", "tile"):
+        if hasattr(sim, kind) and getattr(sim, kind)(model)[0]:
+            return getattr(sim, kind)(model)[0]
     ring = sim.fusion(model)[0]
     if not ring:
         return 1

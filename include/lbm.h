@@ -206,26 +206,35 @@ int lbm_get_fusion_depth(lbm_ctx* ctx, int model, int* steps);
 /* Walking launches of `model`: 4 to 8 steps per launch (4 to 6 in FP16), one wave walking down each
  * strip of 112 columns and *rows rows with the steps kept in registers, so that each population is
  * read and written once per launch.  A new context takes them for every model where the grid has
- * enough strips to fill the device (from about 576 x 576 in FP64, 896 x 896 in FP16 and 1280 x 1280 in
- * FP32); lbm_step then splits its steps into such launches of at most *steps steps and, for what they
+ * enough strips to fill the device (from about 1024 x 1024 in FP64 and 1700 x 1700 in FP32 and FP16);
+ * lbm_step then splits its steps into such launches of at most *steps steps and, for what they
  * do not fill, the launches that lbm_get_fusion and lbm_get_fusion_depth describe.
  * lbm_set_fusion and lbm_set_fusion_depth turn them off for the model, lbm_autotune keeps them where
  * they are the fastest.  Bit-identical to single steps.  *steps = *rows = 0 when off; host pointers,
  * each may be NULL. */
 int lbm_get_walk(lbm_ctx* ctx, int model, int* steps, int* rows);
 
+/* Tile launches of `model`: a workgroup pulls a patch of *patch x *patch nodes (22, 32 or 44), advances it
+ * by up to *steps steps in LDS, the valid part shrinking by one node on each side per step, and stores the
+ * rest, *patch - 2 (*steps - 1) nodes a side.  A new context takes them for every model on grids of at most
+ * 3 * 2^20 nodes that the walking launches do not take (on grids lower or narrower than 16 nodes while one
+ * patch per CU is enough); lbm_step then splits two steps and more into as few launches as there can be, of
+ * nearly equal numbers of steps.  lbm_set_fusion and lbm_set_fusion_depth turn them off for the model,
+ * lbm_autotune keeps them where they are the fastest.  Bit-identical to single steps.  *steps = *patch = 0
+ * when off; host pointers, each may be NULL. */
+int lbm_get_tile(lbm_ctx* ctx, int model, int* steps, int* patch);
+
 /* Autotune the launches of `model` on this context's grid: every single-step shape
  * (rows in {1, 2, 4} x xcd in {0, 1}), the two-step shapes (ring_rows, strip_rows) in
  * {(8, 8), (8, 16), (8, 40), (8, 64), (16, 16), (4, 16), (4, 20), (4, 64)} and, except for FP16,
  * the three-step shapes {(4, 8), (4, 16), (4, 32), (4, 64), (8, 8), (8, 16), (8, 24), (8, 32),
- * (8, 64), (8, 80), (8, 96), (8, 128)} and, where a new context may take them, the walking launches
- * (lbm_get_walk) are timed with HIP
- * events over `trials` (>= 1) launches that recompute from the same input copy, so the state, the
+ * (8, 64), (8, 80), (8, 96), (8, 128)} and, where a new context may take them, the walking and tile
+ * launches (lbm_get_walk, lbm_get_tile) are timed with HIP events over `trials` (>= 1) launches that recompute from the same input copy, so the state, the
  * step counter and the blow-up record are unchanged.  The fastest single-step shape is kept (it
  * also takes the last steps that do not fill a fused launch) and returned through rows_out /
  * xcd_out; the fastest fused shape per step is kept (lbm_get_fusion, lbm_get_fusion_depth) when it
- * beats it, and fusion is switched off otherwise; walking launches are kept when they beat both.  us_per_step is the best time per step.  Host
- * pointers, each may be NULL.  Synchronises. */
+ * beats it, and fusion is switched off otherwise; walking or tile launches are
+ * kept when they beat both.  us_per_step is the best time per step.  Host pointers, each may be NULL.  Synchronises. */
 int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* rows_out,
                  int* xcd_out, double* us_per_step);
 

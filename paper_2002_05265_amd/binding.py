@@ -25,7 +25,7 @@ EXPORTS = (
     "lbm_population_bytes", "lbm_init", "lbm_init_shifted", "lbm_step", "lbm_moments", "lbm_moments_noalloc",
     "lbm_status",
     "lbm_get_state", "lbm_set_state", "lbm_set_launch", "lbm_set_fusion", "lbm_get_fusion",
-    "lbm_set_fusion_depth", "lbm_get_fusion_depth", "lbm_get_walk", "lbm_autotune", "lbm_destroy", "lbm_last_error",
+    "lbm_set_fusion_depth", "lbm_get_fusion_depth", "lbm_get_walk", "lbm_get_tile", "lbm_autotune", "lbm_destroy", "lbm_last_error",
     "lbm_batch_population_bytes", "lbm_batch_create", "lbm_batch_run", "lbm_batch_status",
     "lbm_batch_get_state", "lbm_batch_mean_u2", "lbm_batch_set_active", "lbm_batch_rebalance",
     "lbm_batch_set_launch", "lbm_batch_set_fusion", "lbm_batch_get_fusion",
@@ -81,6 +81,7 @@ def _declare(L: ctypes.CDLL):
         "lbm_set_fusion_depth": (_i, [_vp, _i, _i]),
         "lbm_get_fusion_depth": (_i, [_vp, _i, ctypes.POINTER(_i)]),
         "lbm_get_walk": (_i, [_vp, _i, ctypes.POINTER(_i), ctypes.POINTER(_i)]),
+        "lbm_get_tile": (_i, [_vp, _i, ctypes.POINTER(_i), ctypes.POINTER(_i)]),
         "lbm_autotune": (_i, [_vp, _i, _dp, _i, ctypes.POINTER(_i), ctypes.POINTER(_i), _dp]),
         "lbm_destroy": (None, [_vp]),
         "lbm_last_error": (ctypes.c_char_p, []),
@@ -232,6 +233,12 @@ def lbm_get_walk(ctx: int, model: int):
     steps, rows = _i(0), _i(0)
     _check(lib().lbm_get_walk(ctx, model, ctypes.byref(steps), ctypes.byref(rows)), "lbm_get_walk")
     return steps.value, rows.value
+
+
+def lbm_get_tile(ctx: int, model: int):
+    steps, patch = _i(0), _i(0)
+    _check(lib().lbm_get_tile(ctx, model, ctypes.byref(steps), ctypes.byref(patch)), "lbm_get_tile")
+    return steps.value, patch.value
 
 
 def lbm_get_fusion(ctx: int, model: int):

@@ -256,21 +256,18 @@ constexpr long long kWideMinStrips = 1024;
 // Walking launches (lbm_walk.hpp) of a new context: the segment height that gives at most one wave per
 // slot of the device (two waves per SIMD in FP32 and FP16, one in FP64, where a wave takes more than half
 // of the SIMD's registers), so that all of them walk at once, and the most steps per launch that pays
-// for it; rows = 0 where the strip launches stay faster.  Measured on MI355X (us per step, walking
-// against the strip launches, BGK / K):
-// - FP64: 512^2 4.2 / 4.9 against 4.6 / 4.6, 576^2 4.5 / 5.1 against 5.2 / 5.5, 1024^2 8.1 / 10.2
-//   against 13.5 / 14.0, 2048^2 23.2 / 27.5 against 46.9 / 48.3, 4096^2 81 / 100 against 163 / 169;
-// - FP32: 1152^2 9.3 / 11.1 against 9.8 / 10.3, 1280^2 9.5 / 11.3 against 11.4 / 12.1, 2048^2 18.4 / 23.5
-//   against 26.2 / 27.6, 4096^2 55 / 73 against 88 / 86, 3001 x 2047 23.7 / 30.8 against 45.8 / 46.1;
-// - FP16: 768^2 5.8 / 7.4 against 6.2 / 6.3, 896^2 5.9 / 7.6 against 8.2 / 8.5, 2048^2 17.8 / 23.2 against
-//   27.0 / 28.8, 4096^2 50 / 68 against 77 / 80.
-// The line is drawn at the rows of a strip per slot (512^2 in FP64: 2.5, 576^2: 3.4; FP32 1152^2: 6.2,
-// 1280^2: 7.5; FP16 768^2: 2.6, 896^2: 3.5) and where at most a quarter of the strips' columns lie outside
-// the grid.  A segment's first 2 (D - 1) iterations fill up the D steps, so low segments take fewer: FP64
-// 768^2 (6 rows) 5.7 / 7.0 with six steps, 6.0 / 6.7 with four; 1152^2 (14 rows) 9.7 / 11.7 with six, 11.8
-// / 12.5 with four; 2048^2 (40 rows) 23.2 / 27.5 with six, 22.2 / 28.9 with eight; 4096^2 (152 rows) 89
-// / 103 with six; FP32 1408^2 (10 rows) 11.1 / 13.8 with six, 11.7 / 13.1 with four; 2600^2 (32 rows)
-// 28.2 / 33.6 with six, 26.5 / 34.0 with eight.
+// for it; rows = 0 where the tile or strip launches stay faster.  Measured on MI355X (us per step, walking
+// against strip launches and, in brackets, tile launches, BGK / K):
+// - FP64: 768^2 5.7 / 7.0 against 6.3 / 7.0 (4.9 / 5.4), 1024^2 8.1 / 10.2 against 13.5 / 14.0 (8.4 / 9.9),
+//   2048^2 23.2 / 27.5 against 46.9 / 48.3, 4096^2 81 / 100 against 163 / 169;
+// - FP32: 1024^2 7.7 / 8.2 (5.4 / 6.4), 1470^2 12.8 / 16.5 (1450^2: 11.1 / 12.6), 2048^2 18.4 / 23.5 against
+//   26.2 / 27.6, 4096^2 55 / 73 against 88 / 86, 3001 x 2047 23.7 / 30.8 against 45.8 / 46.1;
+// - FP16: 1024^2 7.2 / 9.3 (5.0 / 5.9), 1470^2 12.2 / 16.1 (1450^2: 9.8 / 11.6), 2048^2 17.8 / 23.2 against 27.0 / 28.8, 4096^2 50 / 68 against 77 / 80.
+// The line is drawn at the rows of a strip per slot (1024^2: 10 in FP64, 5 in FP32 and FP16; 1470^2: 10.0,
+// 2048^2: 19) and where at most a quarter of the strips' columns lie outside the grid.  A segment's first
+// 2 (D - 1) iterations fill up the D steps, so lower segments take fewer: FP64 1152^2 (14 rows) 9.7 / 11.7
+// with six, 11.8 / 12.5 with four; 2048^2 (40 rows) 23.2 / 27.5 with six, 22.2 / 28.9 with eight; 4096^2
+// (152 rows) 89 / 103 with six; FP32 2600^2 (32 rows) 28.2 / 33.6 with six, 26.5 / 34.0 with eight.
 struct WalkPick {
     int rows, depth;
 };
@@ -281,14 +278,47 @@ WalkPick walk_pick(int nx, int ny, int prec, int cus) {
     if (cus <= 0 || nx < 64 * V || ny < 2 * kWalkHalo) return {0, 0};
     const long long sx = walk_strips(nx, W, V), slots = 4LL * cus * (prec == LBM_F64 ? 1 : 2);
     const double per_slot = (double)sx * ny / (double)slots;
-    if (per_slot < (prec == LBM_F32_SHIFTED ? 7.2 : 3.2) || 3 * sx * W > 4LL * nx) return {0, 0};
+    if (per_slot < (prec == LBM_F64 ? 9.5 : 13.0) || 3 * sx * W > 4LL * nx) return {0, 0};
     const long long segments = std::max(1LL, slots / sx);
     const int hs = (int)((ny + segments - 1) / segments + 1) / 2 * 2;
     switch (prec) {
-        case LBM_F64: return {hs, hs < 8 ? 4 : (hs < 48 ? 6 : 8)};
-        case LBM_F32_SHIFTED: return {hs, hs < 14 ? 4 : (hs < 28 ? 6 : 8)};
-        default: return {hs, hs < 10 ? 4 : 6};
+        case LBM_F64: return {hs, hs < 48 ? 6 : 8};
+        case LBM_F32_SHIFTED: return {hs, hs < 28 ? 6 : 8};
+        default: return {hs, 6};
     }
+}
+
+// Tile launches (lbm_tile_kernel.hpp) of a new context: the patch and the steps per launch with the least
+// time per step of a model fitted to sweeps of both from 64^2 to 1024^2 (within 10% of the best pair
+// measured at each size): 3.6 us per launch, and per step the larger of 0.55 us, the latency of a patch's
+// step, and its work, by the nodes of the rows that are still valid, times the patches per CU.  A patch of
+// 44 in FP64 fills a CU's LDS, and one patch at a time hides no latency (768^2: 6.0 us per step, 32: 4.9).
+// patch = 0 where strips stay: grids of more than 3 2^20 nodes (FP32 4096^2: strips 5.5 us per million nodes,
+// tiles 5.3 / 6.0 at 1450^2) and grids of fewer than 16 nodes a side that need more than one patch per CU.
+struct TilePick {
+    int patch, steps;
+};
+
+TilePick tile_pick(int nx, int ny, int prec, int cus) {
+    if (cus <= 0 || (long long)nx * ny > 3LL << 20) return {0, 0};
+    const double work = prec == LBM_F64 ? 0.30 : (prec == LBM_F32_SHIFTED ? 0.20 : 0.19);
+    TilePick pick{0, 0};
+    double best = 0.0;
+    for (int pw : {22, 32, 44})
+        for (int t = 3; pw - 2 * (t - 1) >= 4; ++t) {
+            const int tw = pw - 2 * (t - 1);
+            const long long tiles = (long long)((nx + tw - 1) / tw) * ((ny + tw - 1) / tw);
+            const long long each = (tiles + cus - 1) / cus;
+            if (each > 1 && ((pw == 44 && prec == LBM_F64) || std::min(nx, ny) < 16)) continue;
+            double us = 3.6;
+            for (int s = 0; s < t; ++s)
+                us += std::max(0.55, (double)each * (work * (pw - 2 * s) * pw / 256.0 + 0.1));
+            if (best == 0.0 || us < best * t) {
+                best = us / t;
+                pick = {pw, t};
+            }
+        }
+    return pick;
 }
 
 // The launches of a run of n <= kPlanMax steps: plan[i] steps in launch i, their number returned.  Walking
@@ -837,6 +867,15 @@ int strip_launches(const lbm_ctx* ctx, int model, int n) {
     return (n + most - 1) / most;
 }
 
+// `nsteps` steps of the whole grid in one tile launch src -> dst.
+void launch_tile(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst) {
+    switch (ctx->prec) {
+        case LBM_F64: launch_tile_f64(ctx, model, w, nsteps, src, dst, (int)ctx->step); break;
+        case LBM_F32_SHIFTED: launch_tile_f32(ctx, model, w, nsteps, src, dst, (int)ctx->step); break;
+        default: launch_tile_f16(ctx, model, w, nsteps, src, dst, (int)ctx->step); break;
+    }
+}
+
 // nsteps steps on strip launches (three and two steps per launch where the model's setting has them)
 // and single steps.
 void step_strips(lbm_ctx* ctx, int model, const double* omega, int nsteps) {
@@ -991,7 +1030,13 @@ int lbm_init_shifted(lbm_ctx** out, int nx, int ny, int prec, int eq_order, doub
         }
     const WalkPick walk = walk_pick(nx, ny, prec, cus);
     ctx->walk_rows = walk.rows;
-    for (int k = 0; k < 9; ++k) ctx->walk_depth[k] = walk.depth;
+    const TilePick tile = tile_pick(nx, ny, prec, cus);
+    ctx->tile_patch = tile.patch;
+    ctx->tile_most = tile.steps;
+    for (int k = 0; k < 9; ++k) {
+        ctx->walk_depth[k] = walk.depth;
+        ctx->tile_steps[k] = walk.depth ? 0 : tile.steps;
+    }
     int rc = check_hip(hipGetDevice(&ctx->device), "hipGetDevice");
     if (rc == LBM_OK) rc = scratch_address(ctx->device, &ctx->d_static);
     if (rc == LBM_OK) rc = check_hip(hipMalloc(&ctx->d_flag, sizeof(int)), "hipMalloc(flag)");
@@ -1019,8 +1064,8 @@ int lbm_step(lbm_ctx* ctx, int model, const double* omega, int nsteps) {
     rc = validate_omega(omega);
     if (rc != LBM_OK) return rc;
     if (ctx->step + nsteps >= INT_MAX) return set_error(LBM_EINVAL, "step counter would overflow");
-    const int depth = ctx->walk_depth[lbm_ctx::slot(model)];
-    if (!depth) {
+    const int depth = ctx->walk_depth[lbm_ctx::slot(model)], tile = ctx->tile_steps[lbm_ctx::slot(model)];
+    if ((!depth && !tile) || nsteps < 2) {
         step_strips(ctx, model, omega, nsteps);
         return check_hip(hipGetLastError(), "step kernel launch");
     }
@@ -1033,19 +1078,33 @@ int lbm_step(lbm_ctx* ctx, int model, const double* omega, int nsteps) {
     }
     int parity = cap == hipStreamCaptureStatusNone ? -1 : strip_launches(ctx, model, nsteps) & 1;
     auto launch = [&](int d) {
-        if (d < 4) return step_strips(ctx, model, omega, d);
-        launch_walk(ctx, model, omega, d, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1));
+        if (d < (depth ? 4 : 2)) return step_strips(ctx, model, omega, d);
+        if (depth)
+            launch_walk(ctx, model, omega, d, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1));
+        else
+            launch_tile(ctx, model, omega, d, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1));
         ctx->cur ^= 1;
         ctx->step += d;
     };
-    int left = nsteps;
-    for (; left > kPlanMax; left -= depth) {
-        launch(depth);
-        if (parity >= 0) parity ^= 1;
+    if (depth) {
+        int left = nsteps;
+        for (; left > kPlanMax; left -= depth) {
+            launch(depth);
+            if (parity >= 0) parity ^= 1;
+        }
+        signed char plan[kPlanMax];
+        const int k = plan_walk(ctx->prec, depth, left, strip_pieces(ctx, model), parity, plan);
+        for (int i = 0; i < k; ++i) launch(plan[i]);
+    } else {
+        // as few launches as there can be, their steps differing by at most one
+        int k = (nsteps + tile - 1) / tile;
+        if (parity >= 0 && (k & 1) != parity) ++k;  // still at most nsteps: tile is at least 3
+        for (int i = 0, done = 0; i < k; ++i) {
+            const int next = (int)((long long)nsteps * (i + 1) / k);
+            launch(next - done);
+            done = next;
+        }
     }
-    signed char plan[kPlanMax];
-    const int k = plan_walk(ctx->prec, depth, left, strip_pieces(ctx, model), parity, plan);
-    for (int i = 0; i < k; ++i) launch(plan[i]);
     return check_hip(hipGetLastError(), "step kernel launch");
 }
 
@@ -1223,6 +1282,7 @@ int lbm_set_fusion(lbm_ctx* ctx, int model, int ring_rows, int strip_rows) {
     ctx->tail_ring[lbm_ctx::slot(model)] = 0;  // an explicit shape also takes the leftover steps
     ctx->tail_strip[lbm_ctx::slot(model)] = 0;
     ctx->walk_depth[lbm_ctx::slot(model)] = 0;  // and all others
+    ctx->tile_steps[lbm_ctx::slot(model)] = 0;
     return LBM_OK;
 }
 
@@ -1236,6 +1296,17 @@ int lbm_set_fusion_depth(lbm_ctx* ctx, int model, int steps) {
     if (steps == 3 && (ctx->nx < 2 || ctx->ny < 2)) return set_error(LBM_EUNSUPPORTED, "grid below 2 x 2");
     ctx->fuse_depth[lbm_ctx::slot(model)] = steps;
     ctx->walk_depth[lbm_ctx::slot(model)] = 0;
+    ctx->tile_steps[lbm_ctx::slot(model)] = 0;
+    return LBM_OK;
+}
+
+int lbm_get_tile(lbm_ctx* ctx, int model, int* steps, int* patch) {
+    if (!ctx) return set_error(LBM_ESTATE, "context is NULL");
+    const int rc = validate_model(model, 4);
+    if (rc != LBM_OK) return rc;
+    const int most = ctx->tile_steps[lbm_ctx::slot(model)];
+    if (steps) *steps = most;
+    if (patch) *patch = most ? ctx->tile_patch : 0;
     return LBM_OK;
 }
 
@@ -1355,6 +1426,17 @@ int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* 
             best_walk = depth;
         }
     }
+    // and tile launches
+    int best_tile = 0;
+    if (rc == LBM_OK && ctx->tile_patch > 0) {
+        const int most = ctx->tile_most;
+        const float ms = timed([&] { launch_tile(ctx, model, omega, most, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1)); }) / (float)most;
+        if (rc == LBM_OK && ms < best) {
+            best = ms;
+            best_tile = most;
+            best_walk = 0;
+        }
+    }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     if (rc == LBM_OK)
@@ -1368,6 +1450,7 @@ int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* 
     ctx->fuse_strip[lbm_ctx::slot(model)] = best_strip;
     ctx->fuse_depth[lbm_ctx::slot(model)] = best_depth;
     ctx->walk_depth[lbm_ctx::slot(model)] = best_walk;
+    ctx->tile_steps[lbm_ctx::slot(model)] = best_tile;
     // the fastest two-step shape takes the two steps left after three-step launches, if it beats
     // one step per launch
     const bool tail = best_depth == 3 && best_ring > 0 && tail_ring > 0 && best2 < best1;

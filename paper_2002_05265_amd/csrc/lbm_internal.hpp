@@ -331,6 +331,11 @@ int reduce_partials(lbm_ctx* ctx);  // d_tot[0..4] := sum over blocks of d_part 
 void launch_walk_f64(lbm_ctx* ctx, int model, const double* w, int depth, int hs, const void* src, void* dst, int step);
 void launch_walk_f32(lbm_ctx* ctx, int model, const double* w, int depth, int hs, const void* src, void* dst, int step);
 void launch_walk_f16(lbm_ctx* ctx, int model, const double* w, int depth, int hs, const void* src, void* dst, int step);
+// One launch of the tile kernel: nsteps steps src -> dst of the whole grid on patches of ctx->tile_patch
+// nodes a side (lbm_tile_kernel.hpp; 1 <= nsteps <= tile_patch / 2).
+void launch_tile_f64(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst, int step);
+void launch_tile_f32(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst, int step);
+void launch_tile_f16(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst, int step);
 }  // namespace lbm
 
 struct lbm_ctx {
@@ -371,6 +376,10 @@ struct lbm_ctx {
     // walking launches (lbm_walk.hpp): most steps per launch, per model (0 = off), and rows per segment
     int walk_depth[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     int walk_rows = 0;
+    // tile launches (lbm_tile_kernel.hpp): most steps per launch, per model (0 = off); the patch's side and its
+    // steps on this grid (0 = never)
+    int tile_steps[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    int tile_patch = 0, tile_most = 0;
 
     static int slot(int model) { return (model >= 0 && model < 8) ? model : 8; }
     lbm::StepShape shape_of(int model) const {

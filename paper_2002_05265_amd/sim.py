@@ -72,6 +72,10 @@ class Sim:
         """(steps per launch, rows per segment) of `model`'s walking launches, (0, 0) when off."""
         return B.lbm_get_walk(self.ctx, _model_code(model))
 
+    def tile(self, model):
+        """(steps per launch, patch side) of `model`'s tile launches, (0, 0) when off."""
+        return B.lbm_get_tile(self.ctx, _model_code(model))
+
     def autotune(self, model, omega, trials: int = 10):
         """Pick the fastest launches for `model` (state unchanged); returns the single-step shape
         (rows, xcd) and the best microseconds per step; fusion() and fusion_depth() give the fused
