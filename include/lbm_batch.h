@@ -140,6 +140,25 @@ int lbm_batch_set_fusion_depth(lbm_batch* b, int steps);
 /* Steps per fused pass (host pointer, may be NULL). */
 int lbm_batch_get_fusion_depth(lbm_batch* b, int* steps);
 
+/* Passes by ordinary launches in place of the persistent ones (which are the default):
+ *   kind 0  persistent launches, as lbm_batch_set_launch, _set_fusion and _set_fusion_depth say (each of
+ *           these returns to them);
+ *   kind 1  walking passes: 7, 5 and 3 steps per pass (5 and 3 in FP16), one wave walking down each strip of
+ *           112 columns with the steps kept in registers (as lbm_get_walk for a single grid); one or two
+ *           steps that are left over are taken one per pass.  For batches whose instances all have at least
+ *           8 rows and an even number of columns or at least 128;
+ *   kind 2  resident passes: one workgroup keeps an instance in LDS for all the steps of a run.  For batches
+ *           whose instances have at most 2496 nodes (FP64) or 4096 (FP32, FP16).
+ * LBM_EUNSUPPORTED for other batches.  lbm_batch_autotune picks between them.  Bit-identical to single steps,
+ * blow-up steps included; a blown-up instance stops at the end of the walking pass containing its step, and
+ * one step after it in resident passes.  Neither kind needs a probe before a stream capture, but the single
+ * steps after walking passes do. */
+int lbm_batch_set_pass(lbm_batch* b, int kind);
+
+/* The kind of pass and, for walking passes, the most steps of one (0 for the others); host pointers, each
+ * may be NULL. */
+int lbm_batch_get_pass(lbm_batch* b, int* kind, int* steps);
+
 /* Residency of launch shape `shape` (0, 1, 2: one step per pass with 1, 2, 4 nodes per thread;
  * 3: two steps per pass; 4: three steps per pass): the workgroups per CU that the persistent
  * kernel's resources allow, the runtime's occupancy figure, the figure confirmed by the first run
@@ -155,7 +174,9 @@ int lbm_batch_residency(lbm_batch* b, int shape, int* from_resources, int* occup
  * counters are unchanged, and the blow-up records are restored afterwards.  Keeps the fastest per
  * step: it sets nodes per thread, groups per CU and whether two or three steps per pass are used
  * (lbm_batch_get_fusion, lbm_batch_get_fusion_depth), and returns the first two and the time per
- * step.  Synchronises. */
+ * step.  Walking passes of 5 and (FP64, FP32) 7 steps and resident passes (timed over 16 * trials steps) are
+ * candidates where the batch allows them and are set when they beat all of these (lbm_batch_get_pass).
+ * Synchronises. */
 int lbm_batch_autotune(lbm_batch* b, int trials, int* nodes_per_thread, int* groups_per_cu,
                        double* us_per_step);
 

@@ -97,9 +97,18 @@ class Batch:
     def fusion_depth(self) -> int:
         return B.lbm_batch_get_fusion_depth(self.handle)
 
+    def set_pass(self, kind: int):
+        """0 persistent launches, 1 walking passes, 2 resident passes (lbm_batch_set_pass)."""
+        B.lbm_batch_set_pass(self.handle, kind)
+
+    def passes(self):
+        """(kind of pass, most steps of a walking pass)"""
+        return B.lbm_batch_get_pass(self.handle)
+
     def autotune(self, trials: int = 5):
         """Fastest launch shape (nodes per thread, groups per CU, us per step); also decides
-        whether two or three steps per pass are used (see fusion(), fusion_depth())."""
+        whether two or three steps per pass are used (see fusion(), fusion_depth()) and the kind of
+        pass (see passes())."""
         return B.lbm_batch_autotune(self.handle, trials)
 
     def residency(self, shape: int):

@@ -30,6 +30,7 @@ EXPORTS = (
     "lbm_batch_get_state", "lbm_batch_mean_u2", "lbm_batch_set_active", "lbm_batch_rebalance",
     "lbm_batch_set_launch", "lbm_batch_set_fusion", "lbm_batch_get_fusion",
     "lbm_batch_set_fusion_depth", "lbm_batch_get_fusion_depth",
+    "lbm_batch_set_pass", "lbm_batch_get_pass",
     "lbm_batch_autotune", "lbm_batch_residency", "lbm_batch_destroy",
     "lbm_state_bytes", "lbm_adjoint_bytes", "lbm_save_state", "lbm_load_state", "lbm_step_raw",
     "lbm_step_raw_many", "lbm_step2_raw_many", "lbm_step3_raw_many", "lbm_adjoint_many", "lbm_adjoint_flush",
@@ -103,6 +104,8 @@ def _declare(L: ctypes.CDLL):
         "lbm_batch_get_fusion": (_i, [_vp, ctypes.POINTER(_i)]),
         "lbm_batch_set_fusion_depth": (_i, [_vp, _i]),
         "lbm_batch_get_fusion_depth": (_i, [_vp, ctypes.POINTER(_i)]),
+        "lbm_batch_set_pass": (_i, [_vp, _i]),
+        "lbm_batch_get_pass": (_i, [_vp, ctypes.POINTER(_i), ctypes.POINTER(_i)]),
         "lbm_batch_autotune": (_i, [_vp, _i, ctypes.POINTER(_i), ctypes.POINTER(_i), _dp]),
         "lbm_batch_destroy": (None, [_vp]),
         "lbm_batch_residency": (_i, [_vp, _i, ctypes.POINTER(_i), ctypes.POINTER(_i), ctypes.POINTER(_i), ctypes.POINTER(_i)]),
@@ -326,6 +329,16 @@ def lbm_batch_get_fusion_depth(b: int) -> int:
     v = _i(0)
     _check(lib().lbm_batch_get_fusion_depth(b, ctypes.byref(v)), "lbm_batch_get_fusion_depth")
     return v.value
+
+
+def lbm_batch_set_pass(b: int, kind: int):
+    _check(lib().lbm_batch_set_pass(b, kind), "lbm_batch_set_pass")
+
+
+def lbm_batch_get_pass(b: int):
+    kind, steps = _i(0), _i(0)
+    _check(lib().lbm_batch_get_pass(b, ctypes.byref(kind), ctypes.byref(steps)), "lbm_batch_get_pass")
+    return kind.value, steps.value
 
 
 def lbm_batch_get_fusion(b: int) -> int:

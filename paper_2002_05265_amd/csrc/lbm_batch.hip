@@ -19,36 +19,18 @@
 
 #include "lbm.h"
 #include "lbm_batch.h"
+#include "lbm_batch_desc.hpp"
 #include "lbm_cell.hpp"
 #include "lbm_internal.hpp"
 #include "lbm_step2.hpp"
 #include "lbm_step3.hpp"
+#include "lbm_walk.hpp"
 
 using namespace lbm;
 
 namespace {
 
 constexpr int kTileThreads = 256;
-
-template <typename R>
-struct BDesc {
-    int nx, ny, model, N;
-    int cells, tile0;       // node count, first tile of this instance (for the current NPT)
-    long long off;          // element offset of the instance inside each copy
-    long long plane;        // elements per population plane of the instance
-    long long foff;         // offset of the instance's initial fields
-    float inv_nx;
-    Ref<R> ref;             // storage reference (rho_s, U) in the arithmetic type
-    Ref<double> ref_d;      // the same values in FP64 (initialisation)
-    Coef<R> c;
-};
-
-__device__ __forceinline__ int row_of(int c, int nx, float inv_nx) {
-    int y = (int)((float)c * inv_nx);
-    if (y * nx > c) --y;
-    else if ((y + 1) * nx <= c) ++y;
-    return y;
-}
 
 template <typename R>
 __device__ __forceinline__ void collide_model(int model, R (&h)[9], const Macro<R>& m,
@@ -475,6 +457,11 @@ __global__ void k_batch_reset(unsigned* __restrict__ bar) {
     for (int i = threadIdx.x; i < kBarrierWords; i += blockDim.x) bar[i] = 0u;
 }
 
+// The step counter after passes that do not advance it themselves.
+__global__ void k_step_add(long long* __restrict__ step_ctr, int n) {
+    if (threadIdx.x == 0) *step_ctr += n;
+}
+
 __global__ void k_clear_i32(int* __restrict__ p) {
     if (threadIdx.x == 0) *p = 0;
 }
@@ -515,6 +502,12 @@ struct lbm_batch {
     int* d_xtab[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};  // per XCC id: first run entry, entry count
     long long run_cap[5] = {0, 0, 0, 0, 0};                          // entries d_run[k] can hold
     std::vector<int> xccs;                          // XCC ids the device dispatches to
+    // passes by ordinary launches, in place of the persistent ones: 1 walking (lbm_batch_walk.hpp) of at
+    // most walk_depth steps, 2 resident (lbm_batch_resident.hpp)
+    int pass = 0, walk_depth = 0;
+    int most_cells = 0;                // nodes of the largest instance
+    WalkTask* d_tasks = nullptr;       // tasks of the live instances (nullptr: no walking passes), j < 0 past them
+    int ntasks = 0;                    // entries of d_tasks
     int* d_blowup = nullptr;
     int* d_active = nullptr;           // per instance: nonzero = advanced by lbm_batch_run
     int* d_retired = nullptr;          // per instance: step at which it was retired (INT_MAX)
@@ -659,6 +652,79 @@ hipError_t launch_batch_p(lbm_batch* b, hipStream_t s, int G, int nsteps, int ad
     }
 }
 
+// Walking passes take instances of which no lane's two columns straddle the periodic edge, halo included (an
+// even width, or a first strip whose halo ends before the edge) and of more rows than a pass has steps.
+bool walk_takes(const lbm_instance_desc& d) {
+    return d.ny >= kWalkHalo && (d.nx % 2 == 0 || d.nx >= 64 * walk_cols<kF64>());
+}
+
+// The tasks of the live instances, in order of the model, cut at about hs rows (an even number, spread
+// evenly over the segments); with `out` null only counted.  `rows` receives the rows of all of them with the
+// 2 (D - 1) that fill up a task's steps, `longest` the most of one.
+long long walk_tasks(const lbm_batch* b, const std::vector<char>& live, int hs, int depth, std::vector<WalkTask>* out,
+                     long long& rows, int& longest) {
+    long long count = 0;
+    rows = 0;
+    longest = 0;
+    for (int model = 0; model < 8; ++model)
+        for (int j = 0; j < b->n; ++j) {
+            const lbm_instance_desc& d = b->hdesc[j];
+            if (!live[j] || d.model != model) continue;
+            const int sx = walk_strips(d.nx, walk_width<kF64>(), walk_cols<kF64>());
+            const int pieces = (d.ny + hs - 1) / hs, h = ((d.ny + pieces - 1) / pieces + 1) / 2 * 2;
+            const int segments = (d.ny + h - 1) / h;
+            count += (long long)sx * segments;
+            rows += (long long)sx * (d.ny + 2LL * (depth - 1) * segments);
+            longest = std::max(longest, std::min(h, d.ny) + 2 * (depth - 1));
+            if (out)
+                for (int y = 0; y < segments; ++y)
+                    for (int x = 0; x < sx; ++x) out->push_back({j, x, y * h, std::min((y + 1) * h, d.ny)});
+        }
+    return count;
+}
+
+// Cut the live instances into tasks for the device's wave slots (one per SIMD in FP64, two in FP32 and FP16):
+// the height with the shortest pass, which lasts as long as its longest task, and where there are more
+// tasks than slots up to as long as all of them over the slots on top.  The table keeps its size (d_tasks null: it is allocated for these tasks), so that a captured pass
+// stays valid when the instances are dealt anew.  Synchronous.
+int deal_tasks(lbm_batch* b, const std::vector<char>& live) {
+    for (const lbm_instance_desc& d : b->hdesc)
+        if (!walk_takes(d)) return LBM_OK;
+    const long long slots = 4LL * b->cus * (b->prec == LBM_F64 ? 1 : 2);
+    const int depth = b->prec == LBM_F16_SHIFTED ? 5 : 7;
+    int best = 0, tallest = 0;
+    double time = 0.0;
+    for (const lbm_instance_desc& d : b->hdesc) tallest = std::max(tallest, d.ny);
+    for (int hs = 8;; hs += std::max(2, hs / 16 * 2)) {
+        long long rows;
+        int longest;
+        const long long count = walk_tasks(b, live, hs, depth, nullptr, rows, longest);
+        const double t = (double)longest + (count > slots ? (double)rows / (double)slots : 0.0);
+        if ((!b->d_tasks || count <= b->ntasks) && (best == 0 || t < time)) {
+            best = hs;
+            time = t;
+        }
+        if (hs >= tallest) break;
+    }
+    if (best == 0) return set_error(LBM_EHIP, "walking tasks overflow");
+    std::vector<WalkTask> tasks;
+    long long rows;
+    int longest;
+    walk_tasks(b, live, best, depth, &tasks, rows, longest);
+    int rc = LBM_OK;
+    if (!b->d_tasks) {
+        const long long entries = std::max(slots, (long long)tasks.size());
+        if (entries >= INT_MAX) return LBM_OK;
+        rc = check_hip(hipMalloc(&b->d_tasks, sizeof(WalkTask) * (size_t)entries), "hipMalloc(tasks)");
+        if (rc == LBM_OK) b->ntasks = (int)entries;
+    }
+    tasks.resize((size_t)b->ntasks, WalkTask{-1, 0, 0, 0});
+    if (rc == LBM_OK)
+        rc = check_hip(hipMemcpy(b->d_tasks, tasks.data(), sizeof(WalkTask) * tasks.size(), hipMemcpyHostToDevice),
+                       "copy tasks");
+    return rc;
+}
+
 // Deal the live instances to the XCDs, largest first, each to the XCD with the fewest nodes so
 // far, and write each launch shape's run table (one contiguous list of (instance, tile) per XCD,
 // instances in index order within it) and XCD table.  Synchronous.
@@ -704,7 +770,7 @@ int deal_tables(lbm_batch* b, const std::vector<char>& live) {
                            "copy xtab");
         if (rc != LBM_OK) return rc;
     }
-    return LBM_OK;
+    return deal_tasks(b, live);
 }
 
 int shape_of(const lbm_batch* b, bool fused) { return fused ? (b->depth == 3 ? 4 : 3) : npt_index(b->npt); }
@@ -842,6 +908,62 @@ int run_units(lbm_batch* b, int k, int units) {
     return LBM_OK;
 }
 
+bool resident_takes(const lbm_batch* b) {
+    return b->most_cells <= (b->prec == LBM_F64 ? kResidentNodes64 : kResidentNodes32);
+}
+
+BatchPass pass_of(const lbm_batch* b, int first, int advance) {
+    return BatchPass{b->stream, b->buf, b->copy_elems, b->d_desc[0], b->n, b->d_blowup, b->d_active, b->d_lastcopy,
+                     b->d_step, first, advance};
+}
+
+void walk_pass(const lbm_batch* b, int depth, int first, int advance) {
+    const BatchPass p = pass_of(b, first, advance);
+    switch (b->prec) {
+        case LBM_F64: launch_batch_walk_f64(p, depth, b->d_tasks, b->ntasks); break;
+        case LBM_F32_SHIFTED: launch_batch_walk_f32(p, depth, b->d_tasks, b->ntasks); break;
+        default: launch_batch_walk_f16(p, depth, b->d_tasks, b->ntasks); break;
+    }
+}
+
+void resident_pass(const lbm_batch* b, int nsteps, int advance) {
+    const BatchPass p = pass_of(b, 0, advance);
+    switch (b->prec) {
+        case LBM_F64: launch_batch_resident_f64(p, nsteps, b->most_cells); break;
+        case LBM_F32_SHIFTED: launch_batch_resident_f32(p, nsteps, b->most_cells); break;
+        default: launch_batch_resident_f16(p, nsteps, b->most_cells); break;
+    }
+}
+
+// Steps of the next walking pass of a run with `left` steps to go, 0 where single steps are left: a split into
+// 7, 5 and 3 (at most `depth`) in as few passes as there can be, the odd one or two steps out of 1, 2 and 4.
+int next_walk(int depth, int left) {
+    static constexpr signed char kNext[21] = {0, 0, 0, 3, 3, 5, 3, 7, 5, 3, 7, 5, 7, 7, 7, 5, 7, 7, 7, 7, 7};
+    static constexpr signed char kNext5[16] = {0, 0, 0, 3, 3, 5, 3, 3, 5, 3, 5, 5, 3, 5, 3, 5};
+    if (depth == 7) return left > 20 ? 7 : kNext[left];
+    return left > 15 ? 5 : kNext5[left];
+}
+
+// Advance every live instance by nsteps steps by ordinary launches.  The kernels take the step from the
+// device counter, which a launch of its own advances at the end, so that a captured run can be replayed.
+int run_passes(lbm_batch* b, int nsteps) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    int rc = check_hip(hipStreamIsCapturing(b->stream, &cap), "hipStreamIsCapturing");
+    if (rc != LBM_OK) return rc;
+    int done = 0;
+    if (b->pass == 2) {
+        resident_pass(b, nsteps, 1);
+        done = nsteps;
+    } else {
+        for (int d; (d = next_walk(b->walk_depth, nsteps - done)) > 0; done += d) walk_pass(b, d, done, 1);
+    }
+    if (done > 0) hipLaunchKernelGGL(k_step_add, dim3(1), dim3(64), 0, b->stream, b->d_step, done);
+    rc = check_hip(hipGetLastError(), "batch pass launch");
+    if (rc != LBM_OK) return rc;
+    if (cap == hipStreamCaptureStatusNone) b->step += done;
+    return run_units(b, npt_index(b->npt), nsteps - done);
+}
+
 // Live instances: neither blown up nor retired.  Synchronous.
 int live_set(lbm_batch* b, std::vector<char>& live) {
     std::vector<int> blow((size_t)b->n), ret((size_t)b->n);
@@ -944,6 +1066,8 @@ int lbm_batch_create(lbm_batch** out, const lbm_instance_desc* desc, int n, int 
         fo += (long long)desc[j].nx * desc[j].ny;
     }
     b->copy_elems = o;
+    for (int j = 0; j < n; ++j) b->most_cells = std::max(b->most_cells, desc[j].nx * desc[j].ny);
+    b->walk_depth = prec == LBM_F16_SHIFTED ? 5 : 7;
 
     int rc = LBM_OK;
     int dev = 0, clock_khz = 0;
@@ -1102,6 +1226,7 @@ int lbm_batch_run(lbm_batch* b, int nsteps) {
     if (nsteps < 0) return set_error(LBM_EINVAL, "nsteps %d < 0", nsteps);
     if (b->step + nsteps >= INT_MAX) return set_error(LBM_EINVAL, "step counter would overflow");
     if (nsteps == 0) return LBM_OK;
+    if (b->pass) return run_passes(b, nsteps);
     // three steps per pass (any number of triples leaves every live state in the copy of its
     // step's parity), or two in runs of 4 steps (an even number of pairs does); the rest one step
     // per pass
@@ -1240,6 +1365,7 @@ int lbm_batch_set_fusion(lbm_batch* b, int strip_rows) {
     if (!b) return set_error(LBM_ESTATE, "batch is NULL");
     if (strip_rows < 0 || (strip_rows > 0 && (strip_rows % kBatchRing != 0 || strip_rows > (1 << 20))))
         return set_error(LBM_EINVAL, "strip_rows %d: 0 or a positive multiple of %d", strip_rows, kBatchRing);
+    b->pass = 0;
     if (strip_rows == 0) {
         b->fuse = 0;
         return LBM_OK;
@@ -1262,6 +1388,25 @@ int lbm_batch_set_fusion_depth(lbm_batch* b, int steps) {
     if (steps == 3 && !batch3_kernel_p(b->prec))
         return set_error(LBM_EUNSUPPORTED, "three steps per pass need an FP64 or FP32 batch");
     b->depth = steps;
+    b->pass = 0;
+    return LBM_OK;
+}
+
+int lbm_batch_set_pass(lbm_batch* b, int kind) {
+    if (!b) return set_error(LBM_ESTATE, "batch is NULL");
+    if (kind < 0 || kind > 2) return set_error(LBM_EINVAL, "kind of pass %d not in 0..2", kind);
+    if (kind == 1 && !b->d_tasks)
+        return set_error(LBM_EUNSUPPORTED, "an instance is too low, or narrow and of odd width, for walking passes");
+    if (kind == 2 && !resident_takes(b))
+        return set_error(LBM_EUNSUPPORTED, "an instance of %d nodes is too large for resident passes", b->most_cells);
+    b->pass = kind;
+    return LBM_OK;
+}
+
+int lbm_batch_get_pass(lbm_batch* b, int* kind, int* steps) {
+    if (!b) return set_error(LBM_ESTATE, "batch is NULL");
+    if (kind) *kind = b->pass;
+    if (steps) *steps = b->pass == 1 ? b->walk_depth : 0;
     return LBM_OK;
 }
 
@@ -1284,6 +1429,7 @@ int lbm_batch_set_launch(lbm_batch* b, int nodes_per_thread, int groups_per_cu) 
     if (groups_per_cu < 0) return set_error(LBM_EINVAL, "groups_per_cu %d < 0", groups_per_cu);
     b->npt = nodes_per_thread;
     b->gpc = groups_per_cu;
+    b->pass = 0;
     return LBM_OK;
 }
 
@@ -1336,8 +1482,37 @@ int lbm_batch_autotune(lbm_batch* b, int trials, int* nodes_per_thread, int* gro
                 best_depth = k == 4 ? 3 : 2;
             }
         }
+    // passes by ordinary launches; the settings of the persistent ones stay as picked above, also for the
+    // steps that walking passes leave over
+    int best_pass = 0, best_walk = b->walk_depth;
+    auto timed = [&](int steps, int pass, int depth, auto&& launch) {
+        if (rc != LBM_OK) return;
+        launch(1);
+        rc = check_hip(hipEventRecord(e0, b->stream), "hipEventRecord");
+        if (rc == LBM_OK) launch(trials);
+        if (rc == LBM_OK) rc = check_hip(hipGetLastError(), "batch pass launch");
+        if (rc == LBM_OK) rc = check_hip(hipEventRecord(e1, b->stream), "hipEventRecord");
+        if (rc == LBM_OK) rc = check_hip(hipEventSynchronize(e1), "hipEventSynchronize");
+        float ms = 0.f;
+        if (rc == LBM_OK) rc = check_hip(hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime");
+        ms /= (float)steps;
+        if (rc == LBM_OK && ms < best) {
+            best = ms;
+            best_pass = pass;
+            if (depth) best_walk = depth;
+        }
+    };
+    if (b->d_tasks)
+        for (int depth : {5, 7})
+            if (depth == 5 || b->prec != LBM_F16_SHIFTED)
+                timed(depth, 1, depth, [&](int k) { for (; k > 0; --k) walk_pass(b, depth, 0, 0); });
+    if (resident_takes(b)) timed(16, 2, 0, [&](int k) { resident_pass(b, 16 * k, 0); });
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
+    if (rc == LBM_OK) {
+        b->pass = best_pass;
+        b->walk_depth = best_walk;
+    }
     b->npt = rc == LBM_OK ? best_npt : keep_npt;
     b->gpc = rc == LBM_OK ? best_gpc : keep_gpc;
     b->fuse = rc == LBM_OK ? best_fuse : keep_fuse;
@@ -1363,6 +1538,7 @@ void lbm_batch_destroy(lbm_batch* b) {
         if (b->d_xtab[k]) (void)hipFree(b->d_xtab[k]);
         if (b->d_run[k]) (void)hipFree(b->d_run[k]);
     }
+    if (b->d_tasks) (void)hipFree(b->d_tasks);
     if (b->d_lastcopy) (void)hipFree(b->d_lastcopy);
     if (b->d_blowup) (void)hipFree(b->d_blowup);
     if (b->d_active) (void)hipFree(b->d_active);

@@ -1,0 +1,7 @@
+#include "lbm_batch_walk.hpp"
+
+namespace lbm {
+void launch_batch_walk_f64(const BatchPass& p, int depth, const WalkTask* tasks, int ntasks) {
+    launch_batch_walk_p<kF64>(p, depth, tasks, ntasks);
+}
+}  // namespace lbm

@@ -109,8 +109,8 @@ __device__ __forceinline__ void pull_x(int q, const R (&v)[V], R (&out)[V]) {
 // halo columns absorb; rows ys - D + 1 .. and .. ye + D - 2 are collided by both strips
 // that need them.  Every node is computed by the arithmetic of k_step on values of the storage type,
 // so the result is bit-identical to D launches of it.
-// Requires nx >= 64 V and ny >= 2 D (one conditional wrap), x0 + w <= nx, and for x0 + w = nx a w that
-// is a multiple of V (no lane's columns straddle the periodic edge).
+// Requires ny > D (one conditional wrap), x0 + w <= nx, and that no lane's columns straddle the periodic edge:
+// nx a multiple of V, or nx >= 64 V and, for x0 + w = nx, w a multiple of V.
 template <int D, int PREC, typename S, typename R, typename Coll>
 __device__ __forceinline__ void strip_walk(const S* __restrict__ src, S* __restrict__ dst, const Geom& g,
                                            const Ref<R>& ref, int x0, int w, int ys, int ye, int step,
@@ -128,7 +128,8 @@ __device__ __forceinline__ void strip_walk(const S* __restrict__ src, S* __restr
         constexpr int lo = (H - D) / V * V - H;
         const int hi = (H + w + D - 1) / V * V - H;
         int x = x0 + min(max(c0, lo), hi);
-        x = x < 0 ? x + g.nx : (x >= g.nx ? x - g.nx : x);
+        while (x < 0) x += g.nx;
+        while (x >= g.nx) x -= g.nx;
         xo = (unsigned)x * E;
     }
     unsigned long long inside[V];  // lanes whose column j is an output column
@@ -137,7 +138,7 @@ __device__ __forceinline__ void strip_walk(const S* __restrict__ src, S* __restr
 
     auto wrap_row = [&](int a) { return a < 0 ? a + g.ny : (a >= g.ny ? a - g.ny : a); };
     Vec raw[9];
-    auto load_row = [&](int a) {  // the stored populations that step 1 pulls into row a, not yet shifted in x
+    auto load_row = [&](int a) __attribute__((always_inline)) {  // the stored populations that step 1 pulls into row a, not yet shifted in x
         const int yw = wrap_row(a);
         const long long r0 = (long long)yw * g.nx;
         const long long rm = yw == 0 ? (long long)(g.ny - 1) * g.nx : r0 - g.nx;
@@ -162,7 +163,7 @@ __device__ __forceinline__ void strip_walk(const S* __restrict__ src, S* __restr
             for (int j = 0; j < V; ++j) A[k][i][j] = B[0][k][i][j] = B[1][k][i][j] = R(0);
 
     // collide the row h in place (h[q][j]: population q of column j, already pulled)
-    auto collide_row = [&](R(&h)[9][V], int n) {
+    auto collide_row = [&](R(&h)[9][V], int n) __attribute__((always_inline)) {
         unsigned long long bad = 0;
 #pragma unroll
         for (int j = 0; j < V; ++j) {
@@ -183,7 +184,7 @@ __device__ __forceinline__ void strip_walk(const S* __restrict__ src, S* __restr
             if (lane == 0) atomicMin(blowup, n);
         }
     };
-    auto store_row = [&](const R(&h)[9][V], int y) {
+    auto store_row = [&](const R(&h)[9][V], int y) __attribute__((always_inline)) {
         const long long r = (long long)y * g.nx + x0;
         if (c0 >= 0 && c0 + V <= w) {
 #pragma unroll
@@ -205,7 +206,7 @@ __device__ __forceinline__ void strip_walk(const S* __restrict__ src, S* __restr
     };
     // one iteration; with GUARD the steps that the rows above do not reach yet are left out
     const int a0 = ys - D + 1, a1 = ye + D - 2;
-    auto row = [&](auto parity, auto guard, int a) {
+    auto row = [&](auto parity, auto guard, int a) __attribute__((always_inline)) {
         constexpr int P = decltype(parity)::value;
         R h[9][V];
 #pragma unroll
