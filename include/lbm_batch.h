@@ -85,8 +85,8 @@ int lbm_batch_status(lbm_batch* b, long long* step, long long* blowup_steps);
  * An instance that blew up at step b stops at the state its last pass wrote: state b + 1 (the
  * collided state of step b) when that pass took one step, the end of the pair containing b
  * (b + 1 or b + 2) when it took two; either way not a meaningful flow state.  One retired at step
- * r (lbm_batch_set_active) stops at state r.  Synchronises the stream (to read those records),
- * then enqueues the copy. */
+ * r (lbm_batch_set_active) stops at state r.  Enqueues the copy on the batch's stream and does not wait
+ * for it. */
 int lbm_batch_get_state(lbm_batch* b, int instance, double* f);
 
 /* Domain mean of |u|^2 of every instance's current state, the quantity of the stability

@@ -61,6 +61,9 @@ class Batch:
     def state(self, j: int) -> torch.Tensor:
         nx, ny = self.shapes[j]
         f = torch.empty((9, ny, nx), dtype=torch.float64, device=self.device)
+        here = torch.cuda.current_stream(self.device)
+        if here != self.stream:  # work on the caller's stream may still use the memory that f got
+            self.stream.wait_stream(here)
         B.lbm_batch_get_state(self.handle, j, f.data_ptr())
         self.stream.synchronize()
         return f
