@@ -154,14 +154,9 @@ __device__ __forceinline__ void reverse_core(const typename Store<PREC>::R (&h)[
     using R = typename Store<PREC>::R;
     double rho_d;
     const Macro<R> m = macro_of<typename Store<PREC>::S>(h, ref, rho_d);
-    R cb[7] = {R(0), R(0), R(0), R(0), R(0), R(0), R(0)};
+    R cb[7];
     collide_adjoint<MODEL>(h, m, ref, c, N, mu, hb, cb);
-    if (count) {
-        double wn[5];
-        omega_adjoint(cb, wn);
-#pragma unroll
-        for (int k = 0; k < 5; ++k) ws[k] += wn[k];
-    }
+    if (count) omega_adjoint<MODEL>(cb, ws);
 }
 
 // The same node with f_n pulled from `state` and mu gathered from lam_next in memory.

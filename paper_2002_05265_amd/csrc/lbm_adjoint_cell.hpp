@@ -1,20 +1,24 @@
 // Hand-written reverse mode of the per-cell collision in lbm_cell.hpp.
 //
 // Given mu = dL/dh* (the adjoint of the post-collision populations), collide_adjoint returns
-// hb = dL/dh = J_C(h)^T mu and the adjoints of the relaxation coefficients.  The forward pass
-// is recomputed step by step (the "tape" lives in registers) and every statement of
-// lbm_cell.hpp is then reversed in the opposite order:
+// hb = dL/dh = J_C(h)^T mu and the adjoints of the relaxation coefficients.  The forward pass is
+// recomputed step by step (the "tape" lives in registers) and every statement of collide is then
+// reversed in the opposite order:
 //
-//   F1 drho, jx, jy = sums of h            R1 hb_i += drho_b + cx_i jx_b + cy_i jy_b
+//   F1 sums of h, drho, jx, jy             R1 hb_i = mu_i + their adjoints at population i
 //   F2 rho, du, u                          R2 quotient rule, u = U + du
-//   F3 E = hermite_eq(drho, u, du)         R3 eq_adjoint (telescoped monomials)
-//   F4 d = A(h) - E                        R4 neq_adjoint (linear in h, minus E)
-//   F5 n = relax_model(d, u, rho, coef)    R5 per-model reverse
-//   F6 h* = P(drho, jx, jy, E + n)         R6 pop_adjoint (transpose of a linear map)
+//   F3 equilibrium differences, chained    R3 the chain in the opposite order
+//   F4 d = moments of h - E                R4 (linear)
+//   F5 D = relax_model(d, u, rho, coef)    R5 per-model reverse
+//   F6 h* = h + P(D)                       R6 transpose of P
 //
-// Coefficient adjoints cb = (cpp, cpm, c11, c21, c12, c22, om) map to the rates by
-// omega_b(cpp, cpm, c11, om): d/domega_nu = -cpp/2 + cpm/2 - c11 + om,
-// d/domega_b = -cpp/2 - cpm/2, d/domega_21 = -c21, d/domega_12 = -c12, d/domega_22 = -c22.
+// As in the collision only the changes D are carried back, so the identity part of J_C is added at the end
+// and nothing of the equilibrium but its derivative is needed.  What bounds the reverse kernels is the vector
+// ALU: @COUNT
+//
+// Coefficient adjoints cb = (cpp, cpm, c11, c21, c12, c22, om) map to the rates by omega_adjoint:
+// d/domega_nu = -cpp/2 + cpm/2 - c11 + om, d/domega_b = -cpp/2 - cpm/2, d/domega_21 = -c21,
+// d/domega_12 = -c12, d/domega_22 = -c22.
 #pragma once
 
 #include "lbm_cell.hpp"
@@ -30,7 +34,7 @@ __device__ __forceinline__ void zero(MacroBar<R>& b) {
     b.drho = b.rho = b.jx = b.jy = b.ux = b.uy = b.dux = b.duy = R(0);
 }
 
-// R6: transpose of hermite_to_pop.  Outputs the adjoints of drho, jx, jy and of the six
+// Transpose of hermite_to_pop.  Outputs the adjoints of drho, jx, jy and of the six
 // post-collision Hermite differences a20 .. a22.
 template <typename R>
 __device__ __forceinline__ void pop_adjoint(const R (&mu)[9], MacroBar<R>& mb, R (&ab)[6]) {
@@ -61,7 +65,7 @@ __device__ __forceinline__ void pop_adjoint(const R (&mu)[9], MacroBar<R>& mb, R
     ab[5] = M22b;                  // a22
 }
 
-// R3: reverse of hermite_eq.  eb = adjoints of (e20, e02, e11, e21, e12, e22).
+// Reverse of hermite_eq.  eb = adjoints of (e20, e02, e11, e21, e12, e22).
 template <typename R>
 __device__ __forceinline__ void eq_adjoint(const Macro<R>& m, const Ref<R>& r, int N, const R (&eb)[6],
                                            MacroBar<R>& mb) {
@@ -98,224 +102,250 @@ __device__ __forceinline__ void eq_adjoint(const Macro<R>& m, const Ref<R>& r, i
     mb.duy += dbb;
 }
 
-// R4: reverse of hermite_neq (d = A(h) - E).  Adds to hb, mb and eb (eb -= db).
-template <typename R>
-__device__ __forceinline__ void neq_adjoint(const R (&db)[6], R (&hb)[9], MacroBar<R>& mb, R (&eb)[6]) {
-    using L = Lat<R>;
-    for (int k = 0; k < 6; ++k) eb[k] -= db[k];
-    const R a22b = db[5];
-    const R a20b = db[0] - L::cs2 * a22b;
-    const R a02b = db[1] - L::cs2 * a22b;
-    mb.drho -= L::cs2 * (a20b + a02b) + L::cs4 * a22b;
-    mb.jy -= L::cs2 * db[3];
-    mb.jx -= L::cs2 * db[4];
-    const R m20b = a20b, m02b = a02b, m11b = db[2], m21b = db[3], m12b = db[4];
-    const R diagb = a22b + m20b + m02b;
-    hb[1] += m20b;
-    hb[3] += m20b;
-    hb[2] += m02b;
-    hb[4] += m02b;
-    hb[5] += diagb + m11b + m21b + m12b;
-    hb[6] += diagb - m11b + m21b - m12b;
-    hb[7] += diagb + m11b - m21b - m12b;
-    hb[8] += diagb - m11b - m21b + m12b;
-}
-
-// R2 + R1: reverse of macro_of, adding to hb.
-template <typename R>
-__device__ __forceinline__ void macro_adjoint(const Macro<R>& m, const Ref<R>& r, MacroBar<R>& mb,
-                                              R (&hb)[9]) {
-    mb.dux += mb.ux;  // u = U + du
-    mb.duy += mb.uy;
-    const R inv = m.inv_rho;
-    // du = (j - drho U) / rho
-    mb.jx += mb.dux * inv;
-    mb.jy += mb.duy * inv;
-    mb.drho -= (r.ux * mb.dux + r.uy * mb.duy) * inv;
-    mb.rho -= (m.dux * mb.dux + m.duy * mb.duy) * inv;
-    mb.drho += mb.rho;  // rho = rho_s + drho
-    hb[0] += mb.drho;
-    hb[1] += mb.drho + mb.jx;
-    hb[2] += mb.drho + mb.jy;
-    hb[3] += mb.drho - mb.jx;
-    hb[4] += mb.drho - mb.jy;
-    hb[5] += mb.drho + mb.jx + mb.jy;
-    hb[6] += mb.drho - mb.jx + mb.jy;
-    hb[7] += mb.drho - mb.jx - mb.jy;
-    hb[8] += mb.drho + mb.jx - mb.jy;
-}
-
-// Reverse of the whole collision of one cell.  cb: adjoints of (cpp, cpm, c11, c21, c12, c22,
-// om), accumulated (+=).
+// Reverse of the whole collision of one cell.  cb: adjoints of (cpp, cpm, c11, c21, c12, c22, om) (those
+// the model does not have are zero).
 template <int MODEL, typename R>
 __device__ __forceinline__ void collide_adjoint(const R (&h)[9], const Macro<R>& m, const Ref<R>& ref,
                                                 const Coef<R>& c, int N, const R (&mu)[9], R (&hb)[9],
                                                 R (&cb)[7]) {
     using L = Lat<R>;
-    MacroBar<R> mb;
-    zero(mb);
-    R eb[6] = {R(0), R(0), R(0), R(0), R(0), R(0)};
 #pragma unroll
-    for (int i = 0; i < 9; ++i) hb[i] = R(0);
+    for (int k = 0; k < 7; ++k) cb[k] = R(0);
     if constexpr (MODEL == kStreamOnly) {
 #pragma unroll
         for (int i = 0; i < 9; ++i) hb[i] = mu[i];
         return;
     } else {
-        const Eq<R> e = hermite_eq(m, ref, N);
-        if constexpr (MODEL == kBGK) {
-            // h* = h - om (h - heq), heq = P(drho, jx, jy, E)
-            R heq[9];
-            hermite_to_pop(m, e.e20, e.e02, e.e11, e.e21, e.e12, e.e22, heq);
-            R heqb[9];
-            R omb = R(0);
-#pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                hb[i] = (R(1) - c.om) * mu[i];
-                heqb[i] = c.om * mu[i];
-                omb += mu[i] * (heq[i] - h[i]);
+        constexpr bool kShifted = sizeof(R) == 4;
+        constexpr bool kCentral = MODEL == kCM || MODEL == kCHM || MODEL == kK;
+        constexpr bool kRawX = MODEL == kBGK || MODEL == kRM || MODEL == kCM;  // as in collide
+        const R ux = m.ux, uy = m.uy;
+        // F3, F4
+        R e20 = m.jx * ux, e02 = m.jy * uy;
+        R d11 = fmadd(-m.jx, uy, m.s.m11);
+        if constexpr (kShifted) {
+            e20 = fmadd(ref.jx, m.dux, e20);
+            e02 = fmadd(ref.jy, m.duy, e02);
+            d11 = fmadd(-ref.jx, m.duy, d11);
+        }
+        const R a20 = fmadd(-L::cs2, m.drho, m.s.s13 + m.s.m22);
+        const R a02 = fmadd(-L::cs2, m.drho, m.s.s24 + m.s.m22);
+        const R d20 = a20 - e20, d02 = a02 - e02;
+        R d21 = fmadd(-L::cs2, m.jy, m.s.m21);
+        R d12 = fmadd(-L::cs2, m.jx, m.s.m12);
+        R d22 = fmadd(-L::cs2, kRawX ? e20 + e02 : a20 + a02, fmadd(-L::cs4, m.drho, m.s.m22));
+        R e21 = R(0);
+        if (kCentral || N >= 3) {
+            e21 = e20 * uy;
+            d12 = fmadd(-e02, ux, d12);
+            if constexpr (kShifted) {
+                e21 = fmadd(ref.a20, m.duy, e21);
+                d12 = fmadd(-ref.a02, m.dux, d12);
             }
-            cb[6] += omb;
-            R ab[6];
-            pop_adjoint(heqb, mb, ab);
-            for (int k = 0; k < 6; ++k) eb[k] += ab[k];
+            d21 = d21 - e21;
+            if (kCentral || N >= 4) {
+                d22 = fmadd(-e21, uy, d22);
+                if constexpr (kShifted) d22 = fmadd(-ref.a21, m.duy, d22);
+            }
+        }
+        // R6: adjoints of the changes
+        const Sums<R> w = sums_of(mu);
+        R D20b = fmadd(R(0.5), w.s13, -mu[0]);
+        R D02b = fmadd(R(0.5), w.s24, -mu[0]);
+        R D11b = R(0.25) * w.m11;
+        R D21b = fmadd(R(0.25), w.m21, R(-0.5) * w.d24);
+        R D12b = fmadd(R(0.25), w.m12, R(-0.5) * w.d13);
+        const R M22b = fmadd(R(-0.5), w.s13 + w.s24, fmadd(R(0.25), w.m22, mu[0]));
+        // R5: adjoints of d (and of u and, in K, of 1 / rho)
+        R d20b, d02b, d11b, d21b, d12b, d22b, uxb = R(0), uyb = R(0), invb = R(0);
+        if constexpr (MODEL == kBGK) {
+            d20b = -c.om * D20b;
+            d02b = -c.om * D02b;
+            d11b = -c.om * D11b;
+            d21b = -c.om * D21b;
+            d12b = -c.om * D12b;
+            d22b = -c.om * M22b;
+            cb[6] = -fmadd(d20, D20b, fmadd(d02, D02b, fmadd(d11, D11b, fmadd(d21, D21b, fmadd(d12, D12b, d22 * M22b)))));
         } else {
-            const Neq<R> d = hermite_neq(h, m, e);
-            // forward of the relaxation (the tape)
-            const R n20 = c.cpp * d.d20 + c.cpm * d.d02;
-            const R n02 = c.cpm * d.d20 + c.cpp * d.d02;
-            const R n11 = c.c11 * d.d11;
-            // R6: post-collision populations
-            R ab[6];
-            pop_adjoint(mu, mb, ab);
-            // A* = E + n
-            for (int k = 0; k < 6; ++k) eb[k] += ab[k];
-            R n20b = ab[0], n02b = ab[1], n11b = ab[2];
-            const R n21b = ab[3], n12b = ab[4], n22b = ab[5];
-            R d20b = R(0), d02b = R(0), d11b = R(0), d21b = R(0), d12b = R(0), d22b = R(0);
-            const R ux = m.ux, uy = m.uy;
-            if constexpr (MODEL == kHM) {
-                d21b += c.c21 * n21b; cb[3] += d.d21 * n21b;
-                d12b += c.c12 * n12b; cb[4] += d.d12 * n12b;
-                d22b += c.c22 * n22b; cb[5] += d.d22 * n22b;
+            d20b = d02b = d11b = R(0);
+            if constexpr (MODEL == kHM || MODEL == kRM) {
+                d21b = c.k21 * D21b;
+                d12b = c.k12 * D12b;
+                d22b = c.k22 * M22b;
+                cb[3] = d21 * D21b;
+                cb[4] = d12 * D12b;
+                cb[5] = d22 * M22b;
             } else if constexpr (MODEL == kPR) {
-                // n21 = n12 = n22 = 0
-            } else if constexpr (MODEL == kRM) {
-                d21b += c.c21 * n21b; cb[3] += d.d21 * n21b;
-                d12b += c.c12 * n12b; cb[4] += d.d12 * n12b;
-                // n22 = c22 (d22 + cs2 (d20 + d02)) - cs2 (n20 + n02)
-                const R x22 = d.d22 + L::cs2 * (d.d20 + d.d02);
-                cb[5] += x22 * n22b;
-                d22b += c.c22 * n22b;
-                d20b += c.c22 * L::cs2 * n22b;
-                d02b += c.c22 * L::cs2 * n22b;
-                n20b -= L::cs2 * n22b;
-                n02b -= L::cs2 * n22b;
+                d21b = -D21b;
+                d12b = -D12b;
+                d22b = -M22b;
             } else if constexpr (MODEL == kRR) {
-                const R r21 = uy * d.d20 + R(2) * ux * d.d11;
-                const R r12 = ux * d.d02 + R(2) * uy * d.d11;
-                const R r22 = uy * uy * d.d20 + ux * ux * d.d02 + R(4) * ux * uy * d.d11;
-                cb[3] += r21 * n21b; cb[4] += r12 * n12b; cb[5] += r22 * n22b;
-                const R r21b = c.c21 * n21b, r12b = c.c12 * n12b, r22b = c.c22 * n22b;
-                d20b += uy * r21b + uy * uy * r22b;
-                d02b += ux * r12b + ux * ux * r22b;
-                d11b += R(2) * ux * r21b + R(2) * uy * r12b + R(4) * ux * uy * r22b;
-                mb.uy += d.d20 * r21b + R(2) * d.d11 * r12b + (R(2) * uy * d.d20 + R(4) * ux * d.d11) * r22b;
-                mb.ux += R(2) * d.d11 * r21b + d.d02 * r12b + (R(2) * ux * d.d02 + R(4) * uy * d.d11) * r22b;
-            } else {  // kCM, kCHM, kK
-                const R t21 = d.d21 - uy * d.d20 - R(2) * ux * d.d11;
-                const R t12 = d.d12 - ux * d.d02 - R(2) * uy * d.d11;
-                const R t22 = d.d22 - R(2) * (uy * d.d21 + ux * d.d12) + uy * uy * d.d20 +
-                              ux * ux * d.d02 + R(4) * ux * uy * d.d11;
-                const R s21 = c.c21 * t21;
-                const R s12 = c.c12 * t12;
-                // n21 = s21 + uy n20 + 2 ux n11 ; n12 = s12 + ux n02 + 2 uy n11
-                // n22 = s22 + 2 (uy s21 + ux s12) + uy^2 n20 + ux^2 n02 + 4 ux uy n11
-                const R s22b = n22b;
-                const R s21b = n21b + R(2) * uy * n22b;
-                const R s12b = n12b + R(2) * ux * n22b;
-                n20b += uy * n21b + uy * uy * n22b;
-                n02b += ux * n12b + ux * ux * n22b;
-                n11b += R(2) * ux * n21b + R(2) * uy * n12b + R(4) * ux * uy * n22b;
-                mb.uy += n20 * n21b + R(2) * n11 * n12b + (R(2) * s21 + R(2) * uy * n20 + R(4) * ux * n11) * n22b;
-                mb.ux += R(2) * n11 * n21b + n02 * n12b + (R(2) * s12 + R(2) * ux * n02 + R(4) * uy * n11) * n22b;
-                R t22b = R(0);
-                if constexpr (MODEL == kCHM) {
-                    cb[5] += t22 * s22b;
-                    t22b += c.c22 * s22b;
-                } else if constexpr (MODEL == kCM) {
-                    const R x22 = t22 + L::cs2 * (d.d20 + d.d02);
-                    cb[5] += x22 * s22b;
-                    t22b += c.c22 * s22b;
-                    d20b += c.c22 * L::cs2 * s22b;
-                    d02b += c.c22 * L::cs2 * s22b;
-                    n20b -= L::cs2 * s22b;
-                    n02b -= L::cs2 * s22b;
-                } else {  // kK
-                    const R inv = m.inv_rho;
-                    const R P = d.d20 * d.d02 + R(2) * d.d11 * d.d11;
-                    const R Q = n20 * n02 + R(2) * n11 * n11;
-                    cb[5] += (t22 - P * inv) * s22b;
-                    t22b += c.c22 * s22b;
-                    const R Pb = -c.c22 * inv * s22b;
-                    const R Qb = inv * s22b;
-                    const R invb = (Q - c.c22 * P) * s22b;
-                    d20b += Pb * d.d02;
-                    d02b += Pb * d.d20;
-                    d11b += R(4) * Pb * d.d11;
-                    n20b += Qb * n02;
-                    n02b += Qb * n20;
-                    n11b += R(4) * Qb * n11;
-                    mb.rho -= invb * inv * inv;
+                const R f11 = d11 + d11;
+                const R r21 = fmadd(ux, f11, uy * d20);
+                const R r12 = fmadd(uy, f11, ux * d02);
+                const R r22 = fmadd(ux, r12, uy * r21);
+                d21b = -D21b;
+                d12b = -D12b;
+                d22b = -M22b;
+                cb[3] = r21 * D21b;
+                cb[4] = r12 * D12b;
+                cb[5] = r22 * M22b;
+                const R r22b = c.c22 * M22b;
+                const R r21b = fmadd(uy, r22b, c.c21 * D21b);
+                const R r12b = fmadd(ux, r22b, c.c12 * D12b);
+                uxb = fmadd(r12, r22b, fmadd(f11, r21b, d02 * r12b));
+                uyb = fmadd(r21, r22b, fmadd(f11, r12b, d20 * r21b));
+                d20b = uy * r21b;
+                d02b = ux * r12b;
+                const R f11b = fmadd(ux, r21b, uy * r12b);
+                d11b = f11b + f11b;
+            } else {
+                const R vx = ux + ux, vy = uy + uy;
+                const R t21 = fmadd(-vx, d11, fmadd(-uy, d20, d21));
+                const R t12 = fmadd(-vy, d11, fmadd(-ux, d02, d12));
+                const R q21 = d21 + t21, q12 = d12 + t12;
+                const R t22 = fmadd(-ux, q12, fmadd(-uy, q21, d22));
+                const R D20 = fmadd(c.kpp, d20, c.cpm * d02);
+                const R D02 = fmadd(c.kpp, d02, c.cpm * d20);
+                const R D11 = c.k11 * d11;
+                const R s21 = c.k21 * t21, s12 = c.k12 * t12;
+                const R D21 = fmadd(vx, D11, fmadd(uy, D20, s21));
+                const R D12 = fmadd(vy, D11, fmadd(ux, D02, s12));
+                // M22 = s22 + uy (s21 + D21) + ux (s12 + D12)
+                const R gy = uy * M22b, gx = ux * M22b;
+                D21b += gy;
+                D12b += gx;
+                const R s21b = gy + D21b, s12b = gx + D12b;
+                const R g11 = D11 + D11;
+                uyb = fmadd(s21 + D21, M22b, fmadd(D20, D21b, g11 * D12b));
+                uxb = fmadd(s12 + D12, M22b, fmadd(D02, D12b, g11 * D21b));
+                D20b = fmadd(uy, D21b, D20b);
+                D02b = fmadd(ux, D12b, D02b);
+                D11b = fmadd(vx, D21b, fmadd(vy, D12b, D11b));
+                const R t22b = c.k22 * M22b;
+                if constexpr (MODEL == kK) {
+                    const R n20 = d20 + D20, n02 = d02 + D02, n11 = d11 + D11;
+                    const R p = fmadd(d11 + d11, d11, d20 * d02);
+                    const R q = fmadd(n11 + n11, n11, n20 * n02);
+                    cb[5] = fmadd(-p, m.inv_rho, t22) * M22b;
+                    invb = fmadd(-c.c22, p, q) * M22b;
+                    const R qb = m.inv_rho * M22b, pb = -c.c22 * qb;
+                    const R n20b = qb * n02, n02b = qb * n20, n11b = (R(4) * qb) * n11;
+                    D20b += n20b;
+                    D02b += n02b;
+                    D11b += n11b;
+                    d20b = fmadd(pb, d02, n20b);
+                    d02b = fmadd(pb, d20, n02b);
+                    d11b = fmadd(R(4) * pb, d11, n11b);
+                } else {
+                    cb[5] = t22 * M22b;
                 }
-                const R t21b = c.c21 * s21b;
-                const R t12b = c.c12 * s12b;
-                cb[3] += t21 * s21b;
-                cb[4] += t12 * s12b;
-                // t22
-                d22b += t22b;
-                d21b -= R(2) * uy * t22b;
-                d12b -= R(2) * ux * t22b;
-                d20b += uy * uy * t22b;
-                d02b += ux * ux * t22b;
-                d11b += R(4) * ux * uy * t22b;
-                mb.uy += (R(2) * uy * d.d20 - R(2) * d.d21 + R(4) * ux * d.d11) * t22b;
-                mb.ux += (R(2) * ux * d.d02 - R(2) * d.d12 + R(4) * uy * d.d11) * t22b;
-                // t21, t12
-                d21b += t21b;
-                d20b -= uy * t21b;
-                d11b -= R(2) * ux * t21b;
-                mb.uy -= d.d20 * t21b;
-                mb.ux -= R(2) * d.d11 * t21b;
-                d12b += t12b;
-                d02b -= ux * t12b;
-                d11b -= R(2) * uy * t12b;
-                mb.ux -= d.d02 * t12b;
-                mb.uy -= R(2) * d.d11 * t12b;
+                cb[3] = t21 * s21b;
+                cb[4] = t12 * s12b;
+                // t22 = d22 - uy (d21 + t21) - ux (d12 + t12)
+                d22b = t22b;
+                const R ky = uy * t22b, kx = ux * t22b;
+                const R t21b = fmadd(c.k21, s21b, -ky), t12b = fmadd(c.k12, s12b, -kx);
+                d21b = t21b - ky;
+                d12b = t12b - kx;
+                uyb = fmadd(-q21, t22b, uyb);
+                uxb = fmadd(-q12, t22b, uxb);
+                // t21 = d21 - uy d20 - 2 ux d11, t12 = d12 - ux d02 - 2 uy d11
+                const R f11 = d11 + d11;
+                d20b = fmadd(-uy, t21b, d20b);
+                d02b = fmadd(-ux, t12b, d02b);
+                d11b = fmadd(-vx, t21b, fmadd(-vy, t12b, d11b));
+                uyb = fmadd(-d20, t21b, fmadd(-f11, t12b, uyb));
+                uxb = fmadd(-d02, t12b, fmadd(-f11, t21b, uxb));
+            }
+            if constexpr (!kRawX) {  // M22 has cs^2 (D20 + D02)
+                D20b = fmadd(L::cs2, M22b, D20b);
+                D02b = fmadd(L::cs2, M22b, D02b);
             }
             // second-order block, common to every moment space
-            d20b += c.cpp * n20b + c.cpm * n02b;
-            d02b += c.cpm * n20b + c.cpp * n02b;
-            d11b += c.c11 * n11b;
-            cb[0] += n20b * d.d20 + n02b * d.d02;
-            cb[1] += n20b * d.d02 + n02b * d.d20;
-            cb[2] += n11b * d.d11;
-            const R dbv[6] = {d20b, d02b, d11b, d21b, d12b, d22b};
-            neq_adjoint(dbv, hb, mb, eb);
+            d20b = fmadd(c.kpp, D20b, fmadd(c.cpm, D02b, d20b));
+            d02b = fmadd(c.kpp, D02b, fmadd(c.cpm, D20b, d02b));
+            d11b = fmadd(c.k11, D11b, d11b);
+            cb[0] = fmadd(D20b, d20, D02b * d02);
+            cb[1] = fmadd(D20b, d02, D02b * d20);
+            cb[2] = D11b * d11;
         }
-        eq_adjoint(m, ref, N, eb, mb);
-        macro_adjoint(m, ref, mb, hb);
+        // R4, R3
+        R A20b = d20b, A02b = d02b, e20b = -d20b, e02b = -d02b;
+        if constexpr (kRawX) {
+            e20b = fmadd(-L::cs2, d22b, e20b);
+            e02b = fmadd(-L::cs2, d22b, e02b);
+        } else {
+            A20b = fmadd(-L::cs2, d22b, A20b);
+            A02b = fmadd(-L::cs2, d22b, A02b);
+        }
+        R duxb = R(0), duyb = R(0);
+        if (kCentral || N >= 3) {
+            R e21b = -d21b;
+            if (kCentral || N >= 4) {
+                e21b = fmadd(-uy, d22b, e21b);
+                uyb = fmadd(-e21, d22b, uyb);
+                if constexpr (kShifted) duyb = -ref.a21 * d22b;
+            }
+            e20b = fmadd(uy, e21b, e20b);
+            uyb = fmadd(e20, e21b, uyb);
+            e02b = fmadd(-ux, d12b, e02b);
+            uxb = fmadd(-e02, d12b, uxb);
+            if constexpr (kShifted) {
+                duyb = fmadd(ref.a20, e21b, duyb);
+                duxb = -ref.a02 * d12b;
+            }
+        }
+        R jxb = fmadd(ux, e20b, fmadd(-uy, d11b, -L::cs2 * d12b));
+        R jyb = fmadd(uy, e02b, -L::cs2 * d21b);
+        uxb = fmadd(m.jx, e20b, uxb);
+        uyb = fmadd(m.jy, e02b, fmadd(-m.jx, d11b, uyb));
+        if constexpr (kShifted) {
+            duxb = fmadd(ref.jx, e20b, duxb);
+            duyb = fmadd(ref.jy, e02b, fmadd(-ref.jx, d11b, duyb));
+        }
+        const R A22b = A20b + A02b;
+        R drhob = fmadd(-L::cs4, d22b, -L::cs2 * A22b);
+        // R2: u = U + du, du = (j - drho U) / rho, rho = rho_s + drho
+        const R tx = (duxb + uxb) * m.inv_rho, ty = (duyb + uyb) * m.inv_rho;
+        jxb += tx;
+        jyb += ty;
+        if constexpr (kShifted) drhob = fmadd(-ref.ux, tx, fmadd(-ref.uy, ty, drhob));
+        drhob = fmadd(-m.dux, tx, fmadd(-m.duy, ty, drhob));
+        if constexpr (MODEL == kK) drhob = fmadd(-(m.inv_rho * m.inv_rho), invb, drhob);
+        // R1
+        const R xb = drhob + A20b, yb = drhob + A02b, zb = drhob + (d22b + A22b);
+        const R m12b = d12b + jxb, m21b = d21b + jyb;
+        const R P = zb + d11b, Q = zb - d11b, S = m12b + m21b, T = m12b - m21b;
+        hb[0] = mu[0] + drhob;
+        hb[1] = mu[1] + (xb + jxb);
+        hb[3] = mu[3] + (xb - jxb);
+        hb[2] = mu[2] + (yb + jyb);
+        hb[4] = mu[4] + (yb - jyb);
+        hb[5] = mu[5] + (P + S);
+        hb[7] = mu[7] + (P - S);
+        hb[6] = mu[6] + (Q - T);
+        hb[8] = mu[8] + (Q + T);
     }
 }
 
-// Adjoints of the five rates from the coefficient adjoints.
-template <typename R>
-__device__ __forceinline__ void omega_adjoint(const R (&cb)[7], double (&wb)[5]) {
-    wb[0] = -0.5 * (double)cb[0] + 0.5 * (double)cb[1] - (double)cb[2] + (double)cb[6];
-    wb[1] = -0.5 * (double)cb[0] - 0.5 * (double)cb[1];
-    wb[2] = -(double)cb[3];
-    wb[3] = -(double)cb[4];
-    wb[4] = -(double)cb[5];
+// Adds the adjoints of the five rates, from the coefficient adjoints, to ws.
+template <int MODEL, typename R>
+__device__ __forceinline__ void omega_adjoint(const R (&cb)[7], double (&ws)[5]) {
+    if constexpr (MODEL == kStreamOnly) {
+        return;
+    } else if constexpr (MODEL == kBGK) {
+        ws[0] += (double)cb[6];
+    } else {
+        const double p = (double)cb[0], q = (double)cb[1];
+        ws[0] += fma(0.5, q - p, -(double)cb[2]);
+        ws[1] = fma(-0.5, p + q, ws[1]);
+        if constexpr (MODEL != kPR) {
+            ws[2] -= (double)cb[3];
+            ws[3] -= (double)cb[4];
+            ws[4] -= (double)cb[5];
+        }
+    }
 }
 
 }  // namespace lbm

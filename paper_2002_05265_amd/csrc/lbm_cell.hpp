@@ -209,34 +209,6 @@ __host__ __device__ __forceinline__ void hermite_to_pop(const Macro<R>& m, R a20
     h[8] = fmadd(R(0.25), B + D, r5);
 }
 
-// Hermite non-equilibrium moments d_pq = A_pq - A^eq_pq of the shifted populations.
-template <typename R> struct Neq {
-    R d20, d02, d11, d21, d12, d22;
-};
-
-template <typename R>
-__device__ __forceinline__ Neq<R> hermite_neq(const R (&h)[9], const Macro<R>& m, const Eq<R>& e) {
-    using L = Lat<R>;
-    const R s58 = h[5] + h[8], s67 = h[6] + h[7];
-    const R diag = s58 + s67;                                  // m22
-    const R m20 = (h[1] + h[3]) + diag;
-    const R m02 = (h[2] + h[4]) + diag;
-    const R m11 = (h[5] + h[7]) - (h[6] + h[8]);
-    const R m21 = (h[5] + h[6]) - (h[7] + h[8]);
-    const R m12 = s58 - s67;
-    const R a20 = m20 - m.drho * L::cs2;
-    const R a02 = m02 - m.drho * L::cs2;
-    const R a22 = (diag - m.drho * L::cs4) - L::cs2 * (a20 + a02);
-    Neq<R> d;
-    d.d20 = a20 - e.e20;
-    d.d02 = a02 - e.e02;
-    d.d11 = m11 - e.e11;
-    d.d21 = (m21 - L::cs2 * m.jy) - e.e21;
-    d.d12 = (m12 - L::cs2 * m.jx) - e.e12;
-    d.d22 = a22 - e.e22;
-    return d;
-}
-
 // h += scale * P(D): the populations of the moment changes (D20, D02, D11, D21, D12) and of the raw
 // fourth-moment change M22, density and momentum unchanged (eq. HM2RM_Q9, eq. Q9postCollVDF_RM); the
 // pairs of opposite populations share their sums and differences.

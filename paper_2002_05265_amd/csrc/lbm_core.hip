@@ -80,6 +80,37 @@ int scratch_address(int device, double** out) {
     return LBM_OK;
 }
 
+// Host memory that lbm_moments' reductions write their totals to: one page for the process, allocated with the
+// first context (an allocation costs 13-88 us, as much as some contexts' whole use) and handed out in slots
+// of eight doubles, which a context holds until it is destroyed.  Contexts past the last slot copy the
+// totals instead.
+constexpr int kTotalSlots = 64;
+std::mutex g_total_mu;
+double* g_total_page = nullptr;
+unsigned long long g_total_used = 0;  // bit k: slot k is taken
+
+double* take_total_slot() {
+    std::lock_guard<std::mutex> lock(g_total_mu);
+    if (!g_total_page) {
+        void* p = nullptr;
+        if (hipHostMalloc(&p, sizeof(double) * 8 * kTotalSlots, hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        g_total_page = static_cast<double*>(p);
+    }
+    if (~g_total_used == 0ull) return nullptr;
+    const int k = __builtin_ctzll(~g_total_used);
+    g_total_used |= 1ull << k;
+    return g_total_page + 8 * k;
+}
+
+void give_total_slot(double* slot) {
+    if (!slot) return;
+    std::lock_guard<std::mutex> lock(g_total_mu);
+    g_total_used &= ~(1ull << ((slot - g_total_page) / 8));
+}
+
 }  // namespace
 
 Launch launch_for(int nx, int ny) {
@@ -1043,7 +1074,7 @@ int lbm_init_shifted(lbm_ctx** out, int nx, int ny, int prec, int eq_order, doub
     if (rc == LBM_OK)
         rc = check_hip(hipMalloc(&ctx->d_part, sizeof(double) * 5 * (size_t)ctx->nblocks), "hipMalloc(partials)");
     if (rc == LBM_OK) rc = check_hip(hipMalloc(&ctx->d_tot, sizeof(double) * 5), "hipMalloc(totals)");
-    if (rc == LBM_OK) rc = check_hip(hipHostMalloc(&ctx->h_tot, sizeof(double) * 5, hipHostMallocMapped), "hipHostMalloc(totals)");
+    ctx->h_tot = take_total_slot();
     if (rc == LBM_OK) rc = reset_flag(ctx);
     if (rc == LBM_OK) {
         LBM_DISPATCH_PREC(prec, launch_init_p, ctx, rho, ux, uy);
@@ -1195,12 +1226,17 @@ int lbm_moments(lbm_ctx* ctx, double* rho, double* ux, double* uy, double* total
     const int nb = launch_moments(ctx, rho, ux, uy, ctx->d_part);
     int rc = check_hip(hipGetLastError(), "moments kernel launch");
     if (rc != LBM_OK || !totals) return rc;
-    // the sums go straight to host memory: a copy of 40 bytes and its wait take 21 us, the wait alone 11
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kFinalizeThreads), 0, ctx->stream, ctx->d_part, nb, ctx->h_tot);
+    // with a slot the sums go straight to host memory: a copy of 40 bytes and its wait take 21 us, the wait
+    // alone 11
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kFinalizeThreads), 0, ctx->stream, ctx->d_part, nb,
+                       ctx->h_tot ? ctx->h_tot : ctx->d_tot);
     rc = check_hip(hipGetLastError(), "finalize kernel launch");
+    double t[5];
+    if (rc == LBM_OK && !ctx->h_tot)
+        rc = check_hip(hipMemcpyAsync(t, ctx->d_tot, sizeof(t), hipMemcpyDeviceToHost, ctx->stream), "copy totals");
     if (rc == LBM_OK) rc = check_hip(hipStreamSynchronize(ctx->stream), "synchronise");
     if (rc != LBM_OK) return rc;
-    const double* t = ctx->h_tot;
+    if (ctx->h_tot) std::copy(ctx->h_tot, ctx->h_tot + 5, t);
     for (int k = 0; k < 4; ++k) totals[k] = t[k];
     totals[4] = t[4] / ((double)ctx->nx * (double)ctx->ny);
     totals[5] = (double)ctx->step;
@@ -1467,7 +1503,7 @@ void lbm_destroy(lbm_ctx* ctx) {
     if (ctx->d_flag) (void)hipFree(ctx->d_flag);
     if (ctx->d_part) (void)hipFree(ctx->d_part);
     if (ctx->d_tot) (void)hipFree(ctx->d_tot);
-    if (ctx->h_tot) (void)hipHostFree(ctx->h_tot);
+    give_total_slot(ctx->h_tot);
     if (ctx->d_wslots) (void)hipFree(ctx->d_wslots);
     delete ctx;
 }

@@ -88,7 +88,7 @@ __global__ void k_lsa_jacobian(const lbm_lsa_point* __restrict__ pts, double* __
     double rho_d;
     const Macro<double> m = macro_of<double>(h, ref, rho_d);
     const Coef<double> c = make_coef<double>(q.omega);
-    double mu[9], hb[9], cb[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    double mu[9], hb[9], cb[7];
 #pragma unroll
     for (int j = 0; j < 9; ++j) mu[j] = j == i ? 1.0 : 0.0;
     collide_adjoint_model(q.model, h, m, ref, c, q.eq_order, mu, hb, cb);
