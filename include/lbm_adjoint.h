@@ -82,6 +82,17 @@ int lbm_step2_raw_many(lbm_ctx* ctx, int model, const double* omega, const void*
 int lbm_step3_raw_many(lbm_ctx* ctx, int model, const double* omega, const void* const* src,
                        void* const* dst, int count, long long step0);
 
+/* count (>= 0) raw steps from the state src (step step0) by the context's walking or tile launches
+ * (lbm_get_walk, lbm_get_tile), several steps each: dst[k] receives the state after step k + 1 unless it is
+ * NULL; the last must not be.  Tile launches write the states that are kept on the way; walking launches
+ * take the steps between kept states that are four or more apart, pairs and triples of steps the others.
+ * tmp holds two scratch states for ends of launches that are not kept (it may be NULL if every state is
+ * kept); all states must be distinct.  The states written are bit-identical to those of lbm_step_raw.
+ * moved (may be NULL) receives the number of states that the launches read and wrote in all.
+ * LBM_EUNSUPPORTED if the model takes neither kind of launch on this context. */
+int lbm_step_raw_chain(lbm_ctx* ctx, int model, const double* omega, const void* src, void* const* dst, int count,
+                       void* const* tmp, long long step0, int* moved);
+
 /* Seed of the velocity loss L = || u(f) - u_target ||_2 (sum over nodes and both
  * components) for the current state f:
  *   ux_t, uy_t  device, nx*ny FP64 [y][x]: the target velocity

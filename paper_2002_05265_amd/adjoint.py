@@ -6,9 +6,9 @@ L = || u(f_T) - u_target ||_2; its backward pass runs the hand-written discrete 
 and dL/domega (all five rates; the four higher-order ones are omega[1:]).
 
 The forward states needed in reverse order are rebuilt from checkpoints of the raw device
-state; steps between checkpoints run out-of-place (``lbm_step_raw``, or pairs of them as one
-two-step launch, ``lbm_step2_raw_many``, when the context runs the model two or three steps per
-launch) straight into the buffer that keeps their result, so no state is ever copied:
+state; steps between checkpoints run out-of-place (``lbm_step_raw_chain`` where the context takes
+many steps per launch, else ``lbm_step_raw``, or pairs of them as one two-step launch,
+``lbm_step2_raw_many``, when it runs the model two or three steps per launch) straight into the buffer that keeps their result, so no state is ever copied:
   "sqrt"       ceil(sqrt(n)) evenly spaced checkpoints, each segment recomputed once into a
                ring of at most ceil(sqrt(n)) states (about n extra steps, 2 sqrt(n) states)
   "revolve"    binomial checkpointing with `slots` state buffers (Griewank's schedule: the
@@ -229,10 +229,23 @@ class _Run:
     # released meanwhile may be reused by later queued work because everything runs in stream
     # order on one stream.
     def _flush_steps(self):
-        if self.q_src:
-            B.lbm_step_raw_many(self.ctx, self.model, self.omega, self.q_src, self.q_dst, self.q_step0)
-            self.node_bytes += 18 * self.s * len(self.q_src)
-            self.q_src, self.q_dst = [], []
+        if not self.q_src:
+            return
+        src, dst = self.q_src, self.q_dst
+        self.q_src, self.q_dst = [], []
+        if self._long() and len(self.pool) >= 2 and all(a == b for a, b in zip(src[1:], dst)):
+            # one chain: only the states that are pinned or current and not written again are kept (the
+            # buffers of the others, free by now, serve as scratch)
+            held = {b.data_ptr() for b in self.saved.values()} | {self.cur.data_ptr()}
+            last = {p: k for k, p in enumerate(dst)}
+            keep = [p if p in held and last[p] == k else None for k, p in enumerate(dst)]
+            tmp = [b.data_ptr() for b in self.pool[-2:]]
+            if keep[-1] is not None and src[0] not in keep and src[0] not in tmp:
+                moved = B.lbm_step_raw_chain(self.ctx, self.model, self.omega, src[0], keep, tmp, self.q_step0)
+                self.node_bytes += 9 * self.s * moved
+                return
+        B.lbm_step_raw_many(self.ctx, self.model, self.omega, src, dst, self.q_step0)
+        self.node_bytes += 18 * self.s * len(src)
 
     def _reverse(self, states):
         """Reverse steps at the raw states `states` (device pointers, in reverse-step order) from
@@ -273,6 +286,12 @@ class _Run:
         return (B.lbm_get_fusion_depth(self.ctx, self.model) == 3 and
                 B.lbm_get_fusion(self.ctx, self.model)[0] in (4, 8))
 
+    def _long(self) -> bool:
+        """Whether the context advances this model by walking or tile launches (then chains of forward
+        steps go through lbm_step_raw_chain; the states written are the same bit for bit)."""
+        return self.ctx is not None and (B.lbm_get_tile(self.ctx, self.model)[0] > 0 or
+                                         B.lbm_get_walk(self.ctx, self.model)[0] > 0)
+
     def _run_chain(self, chain, step0: int):
         """Advance along chain = [b_0, b_1, ..., b_m] (b_t receives state step0 + t; None = not
         kept, a scratch buffer is used): three steps as one three-step launch where the two states
@@ -283,6 +302,13 @@ class _Run:
         cur = chain[0]
         scratch = self._scratch
         t, m = 1, len(chain) - 1
+        if m > 0 and self._long():
+            ptr = [None if b is None else b.data_ptr() for b in chain]
+            tmp = None if scratch[0] is None else [b.data_ptr() for b in scratch]
+            moved = B.lbm_step_raw_chain(self.ctx, self.model, self.omega, ptr[0], ptr[1:], tmp, step0)
+            self.node_bytes += 9 * self.s * moved
+            self.steps_run += m
+            return chain[m]
         pairs = self._two_step()
         triples = self._three_step()
 

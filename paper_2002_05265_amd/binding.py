@@ -33,7 +33,8 @@ EXPORTS = (
     "lbm_batch_set_pass", "lbm_batch_get_pass",
     "lbm_batch_autotune", "lbm_batch_residency", "lbm_batch_destroy",
     "lbm_state_bytes", "lbm_adjoint_bytes", "lbm_save_state", "lbm_load_state", "lbm_step_raw",
-    "lbm_step_raw_many", "lbm_step2_raw_many", "lbm_step3_raw_many", "lbm_adjoint_many", "lbm_adjoint_flush",
+    "lbm_step_raw_many", "lbm_step2_raw_many", "lbm_step3_raw_many", "lbm_step_raw_chain",
+    "lbm_adjoint_many", "lbm_adjoint_flush",
     "lbm_set_adjoint_depth", "lbm_get_adjoint_depth",
     "lbm_adjoint_seed_velocity_l2", "lbm_adjoint_step", "lbm_eq_vjp",
     "lbm_lsa_jacobian", "lbm_lsa_eigenvalues", "lbm_lsa_radius", "lbm_lsa_dvbe_growth",
@@ -118,6 +119,8 @@ def _declare(L: ctypes.CDLL):
         "lbm_step2_raw_many": (_i, [_vp, _i, _dp, ctypes.POINTER(_vp), ctypes.POINTER(_vp), ctypes.POINTER(_vp), _i,
                                     _ll]),
         "lbm_step3_raw_many": (_i, [_vp, _i, _dp, ctypes.POINTER(_vp), ctypes.POINTER(_vp), _i, _ll]),
+        "lbm_step_raw_chain": (_i, [_vp, _i, _dp, _vp, ctypes.POINTER(_vp), _i, ctypes.POINTER(_vp), _ll,
+                                    ctypes.POINTER(_i)]),
         "lbm_adjoint_many": (_i, [_vp, _i, _dp, ctypes.POINTER(_vp), _i, ctypes.POINTER(_vp), _vp]),
         "lbm_adjoint_flush": (_i, [_vp, _vp]),
         "lbm_set_adjoint_depth": (_i, [_vp, _i]),
@@ -393,6 +396,16 @@ def _ptrs(seq):
 def lbm_step_raw_many(ctx: int, model: int, omega, src, dst, step0: int):
     _check(lib().lbm_step_raw_many(ctx, model, _omega(omega), _ptrs(src), _ptrs(dst), len(src), step0),
            "lbm_step_raw_many")
+
+
+def lbm_step_raw_chain(ctx: int, model: int, omega, src: int, dst, tmp, step0: int) -> int:
+    """Raw steps src -> dst[0] -> dst[1] ...; a dst of 0 / None is not kept (tmp: two scratch states).
+    Returns the number of states read and written."""
+    moved = _i(0)
+    tmps = None if tmp is None else _ptrs([t or 0 for t in tmp])
+    _check(lib().lbm_step_raw_chain(ctx, model, _omega(omega), src, _ptrs([d or 0 for d in dst]), len(dst), tmps, step0,
+                                    ctypes.byref(moved)), "lbm_step_raw_chain")
+    return moved.value
 
 
 def lbm_step2_raw_many(ctx: int, model: int, omega, src, mid, dst, step0: int):

@@ -14,7 +14,8 @@
 //
 // As in the collision only the changes D are carried back, so the identity part of J_C is added at the end
 // and nothing of the equilibrium but its derivative is needed.  What bounds the reverse kernels is the vector
-// ALU: @COUNT
+// ALU: 304 instructions per node in FP32 for CM, 266 in FP64 (441 and 412 with
+// the whole equilibrium carried back).
 //
 // Coefficient adjoints cb = (cpp, cpm, c11, c21, c12, c22, om) map to the rates by omega_adjoint:
 // d/domega_nu = -cpp/2 + cpm/2 - c11 + om, d/domega_b = -cpp/2 - cpm/2, d/domega_21 = -c21,

@@ -20,6 +20,7 @@
 #include <mutex>
 #include <string>
 #include <type_traits>
+#include <vector>
 
 #include "lbm.h"
 #include "lbm_cell.hpp"
@@ -877,12 +878,12 @@ void launch_init_p(lbm_ctx* ctx, const double* rho, const double* ux, const doub
         }                                                     \
     } while (0)
 
-// `depth` steps of the whole grid in one walking launch src -> dst.
-void launch_walk(lbm_ctx* ctx, int model, const double* w, int depth, const void* src, void* dst) {
+// `depth` steps of the whole grid in one walking launch src -> dst from step `step`.
+void launch_walk(lbm_ctx* ctx, int model, const double* w, int depth, const void* src, void* dst, int step) {
     switch (ctx->prec) {
-        case LBM_F64: launch_walk_f64(ctx, model, w, depth, ctx->walk_rows, src, dst, (int)ctx->step); break;
-        case LBM_F32_SHIFTED: launch_walk_f32(ctx, model, w, depth, ctx->walk_rows, src, dst, (int)ctx->step); break;
-        default: launch_walk_f16(ctx, model, w, depth, ctx->walk_rows, src, dst, (int)ctx->step); break;
+        case LBM_F64: launch_walk_f64(ctx, model, w, depth, ctx->walk_rows, src, dst, step); break;
+        case LBM_F32_SHIFTED: launch_walk_f32(ctx, model, w, depth, ctx->walk_rows, src, dst, step); break;
+        default: launch_walk_f16(ctx, model, w, depth, ctx->walk_rows, src, dst, step); break;
     }
 }
 
@@ -898,12 +899,13 @@ int strip_launches(const lbm_ctx* ctx, int model, int n) {
     return (n + most - 1) / most;
 }
 
-// `nsteps` steps of the whole grid in one tile launch src -> dst.
-void launch_tile(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst) {
+// `nsteps` steps of the whole grid in one tile launch src -> dst from step `step`.
+void launch_tile(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst, int step,
+                 const TileKeep* keep = nullptr) {
     switch (ctx->prec) {
-        case LBM_F64: launch_tile_f64(ctx, model, w, nsteps, src, dst, (int)ctx->step); break;
-        case LBM_F32_SHIFTED: launch_tile_f32(ctx, model, w, nsteps, src, dst, (int)ctx->step); break;
-        default: launch_tile_f16(ctx, model, w, nsteps, src, dst, (int)ctx->step); break;
+        case LBM_F64: launch_tile_f64(ctx, model, w, nsteps, src, dst, step, keep); break;
+        case LBM_F32_SHIFTED: launch_tile_f32(ctx, model, w, nsteps, src, dst, step, keep); break;
+        default: launch_tile_f16(ctx, model, w, nsteps, src, dst, step, keep); break;
     }
 }
 
@@ -1112,9 +1114,9 @@ int lbm_step(lbm_ctx* ctx, int model, const double* omega, int nsteps) {
     auto launch = [&](int d) {
         if (d < (depth ? 4 : 2)) return step_strips(ctx, model, omega, d);
         if (depth)
-            launch_walk(ctx, model, omega, d, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1));
+            launch_walk(ctx, model, omega, d, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1), (int)ctx->step);
         else
-            launch_tile(ctx, model, omega, d, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1));
+            launch_tile(ctx, model, omega, d, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1), (int)ctx->step);
         ctx->cur ^= 1;
         ctx->step += d;
     };
@@ -1219,6 +1221,76 @@ int lbm_step3_raw_many(lbm_ctx* ctx, int model, const double* omega, const void*
         LBM_DISPATCH_PREC(ctx->prec, launch_step3_p, ctx, model, omega, ring, hs, src[k], dst[k],
                           (int)(step0 + 3LL * k));
     return check_hip(hipGetLastError(), "raw three-step kernel launch");
+}
+
+int lbm_step_raw_chain(lbm_ctx* ctx, int model, const double* omega, const void* src, void* const* dst, int count,
+                       void* const* tmp, long long step0, int* moved) {
+    if (!ctx) return set_error(LBM_ESTATE, "context is NULL");
+    if (moved) *moved = 0;
+    if (count < 0) return set_error(LBM_EINVAL, "count %d < 0", count);
+    if (count == 0) return LBM_OK;
+    if (!src || !dst || !dst[count - 1]) return set_error(LBM_EINVAL, "NULL state pointer");
+    if (step0 < 0 || step0 + count >= INT_MAX) return set_error(LBM_EINVAL, "step %lld out of range", step0);
+    int rc = validate_model(model, ctx->eq_order);
+    if (rc == LBM_OK) rc = validate_omega(omega);
+    if (rc != LBM_OK) return rc;
+    const int slot = lbm_ctx::slot(model), depth = ctx->walk_depth[slot], tile = ctx->tile_steps[slot];
+    if (!depth && !tile)
+        return set_error(LBM_EUNSUPPORTED, "model %d takes neither walking nor tile launches on this context", model);
+    void* scratch[2] = {tmp ? tmp[0] : nullptr, tmp ? tmp[1] : nullptr};
+    std::vector<const void*> all{src};
+    for (int k = 0; k < count; ++k)
+        if (dst[k]) all.push_back(dst[k]);
+    if (all.size() <= (size_t)count) {  // some states are not kept
+        if (!scratch[0] || !scratch[1]) return set_error(LBM_EINVAL, "states that are not kept need two scratch states");
+        all.insert(all.end(), scratch, scratch + 2);
+    }
+    std::sort(all.begin(), all.end());
+    if (std::adjacent_find(all.begin(), all.end()) != all.end())
+        return set_error(LBM_EINVAL, "the states of a chain must be distinct");
+    const unsigned pieces = strip_pieces(ctx, model);
+    const StepShape sh = ctx->shape_of(model);
+    const int fs = ctx->tail_ring[slot] == 8 ? ctx->tail_strip[slot] : ctx->fuse_strip[slot];
+    const void* cur = src;
+    int states = 0;
+    for (int at = 0, d; at < count; at += d) {
+        const int left = count - at, step = (int)(step0 + at);
+        int kept = 0;  // steps to the next state that is kept
+        while (!dst[at + kept++]) {}
+        if (tile) {
+            // as few launches as there can be, of nearly equal numbers of steps, whatever is kept
+            const int k = (left + tile - 1) / tile;
+            d = (left + k - 1) / k;
+        } else if (kept >= 4) {
+            signed char plan[kPlanMax];
+            d = kept > kPlanMax ? depth : (plan_walk(ctx->prec, depth, kept, pieces, -1, plan), plan[0]);
+        } else {
+            // three steps where the two states between are not kept, else pairs, which also write the state
+            // between them
+            d = kept == 3 && (pieces & 8) ? 3 : (left >= 2 && (pieces & 4) ? 2 : 1);
+        }
+        void* out = dst[at + d - 1] ? dst[at + d - 1] : scratch[cur == scratch[0]];
+        states += 2;
+        if (d == 1) {
+            LBM_DISPATCH_PREC(ctx->prec, launch_step_raw_p, ctx, model, omega, sh, cur, out, step);
+        } else if (tile) {
+            TileKeep keep{};
+            for (int s = 0; s < d - 1; ++s)
+                if ((keep.state[s] = dst[at + s])) ++states;
+            launch_tile(ctx, model, omega, d, cur, out, step, kept < d ? &keep : nullptr);
+        } else if (d >= 4) {
+            launch_walk(ctx, model, omega, d, cur, out, step);
+        } else if (d == 3) {
+            LBM_DISPATCH_PREC(ctx->prec, launch_step3_p, ctx, model, omega, ctx->fuse_ring[slot], ctx->fuse_strip[slot], cur,
+                              out, step);
+        } else {
+            if (dst[at]) ++states;
+            LBM_DISPATCH_PREC(ctx->prec, launch_step2_raw_p, ctx, model, omega, fs > 0 ? fs : 16, cur, dst[at], out, step);
+        }
+        cur = out;
+    }
+    if (moved) *moved = states;
+    return check_hip(hipGetLastError(), "raw chain kernel launch");
 }
 
 int lbm_moments(lbm_ctx* ctx, double* rho, double* ux, double* uy, double* totals) {
@@ -1455,7 +1527,7 @@ int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* 
     int best_walk = 0;
     for (int depth = 4; depth <= 8 && rc == LBM_OK && ctx->walk_rows > 0; depth += 2) {
         if (depth == 8 && ctx->prec == LBM_F16_SHIFTED) continue;
-        const float ms = timed([&] { launch_walk(ctx, model, omega, depth, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1)); }) / (float)depth;
+        const float ms = timed([&] { launch_walk(ctx, model, omega, depth, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1), (int)ctx->step); }) / (float)depth;
         if (rc == LBM_OK && ms < best) {
             best = ms;
             best_walk = depth;
@@ -1465,7 +1537,7 @@ int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* 
     int best_tile = 0;
     if (rc == LBM_OK && ctx->tile_patch > 0) {
         const int most = ctx->tile_most;
-        const float ms = timed([&] { launch_tile(ctx, model, omega, most, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1)); }) / (float)most;
+        const float ms = timed([&] { launch_tile(ctx, model, omega, most, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1), (int)ctx->step); }) / (float)most;
         if (rc == LBM_OK && ms < best) {
             best = ms;
             best_tile = most;

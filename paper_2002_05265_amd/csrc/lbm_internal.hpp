@@ -331,11 +331,19 @@ int reduce_partials(lbm_ctx* ctx);  // d_tot[0..4] := sum over blocks of d_part 
 void launch_walk_f64(lbm_ctx* ctx, int model, const double* w, int depth, int hs, const void* src, void* dst, int step);
 void launch_walk_f32(lbm_ctx* ctx, int model, const double* w, int depth, int hs, const void* src, void* dst, int step);
 void launch_walk_f16(lbm_ctx* ctx, int model, const double* w, int depth, int hs, const void* src, void* dst, int step);
+// Where a tile launch also writes the states after its steps but the last (NULL: not).
+constexpr int kTileMost = 21;
+struct TileKeep {
+    void* state[kTileMost - 1];
+};
 // One launch of the tile kernel: nsteps steps src -> dst of the whole grid on patches of ctx->tile_patch
-// nodes a side (lbm_tile_kernel.hpp; 1 <= nsteps <= tile_patch / 2).
-void launch_tile_f64(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst, int step);
-void launch_tile_f32(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst, int step);
-void launch_tile_f16(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst, int step);
+// nodes a side (lbm_tile_kernel.hpp; 1 <= nsteps < tile_patch / 2); keep may be NULL.
+void launch_tile_f64(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst, int step,
+                     const TileKeep* keep);
+void launch_tile_f32(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst, int step,
+                     const TileKeep* keep);
+void launch_tile_f16(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst, int step,
+                     const TileKeep* keep);
 }  // namespace lbm
 
 struct lbm_ctx {

@@ -24,6 +24,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "lbm.h"
 #include "lbm_cell.hpp"
 #include "lbm_internal.hpp"
@@ -31,11 +33,14 @@
 namespace lbm {
 namespace {
 
-template <int MODEL, int PREC, int PW, int NT>
+// With KEEP the state after step s + 1 of the launch is also written to keep.state[s] where that is not NULL
+// (each workgroup its tile): a run whose every state is kept costs its writes and nothing else.
+template <int MODEL, int PREC, int PW, int NT, bool KEEP>
 __global__ __launch_bounds__(NT) void k_tile(const typename Store<PREC>::S* __restrict__ src,
                                              typename Store<PREC>::S* __restrict__ dst, Geom g,
                                              Coef<typename Store<PREC>::R> c, Ref<typename Store<PREC>::R> ref, int N,
-                                             int step, int* __restrict__ blowup, int nsteps, unsigned gx) {
+                                             int step, int* __restrict__ blowup, int nsteps, unsigned gx,
+                                             std::conditional_t<KEEP, TileKeep, int> keep) {
     using S = typename Store<PREC>::S;
     using R = typename Store<PREC>::R;
     constexpr int kNodes = PW * PW, kEach = (kNodes + NT - 1) / NT;
@@ -74,6 +79,17 @@ __global__ __launch_bounds__(NT) void k_tile(const typename Store<PREC>::S* __re
             }
         flag_bad(bad, blowup, step + s);
         if (s == e) break;
+        if constexpr (KEEP) {
+            if (keep.state[s]) {
+#pragma unroll
+                for (int k = 0; k < kEach; ++k) {
+                    const int x = x0 + pi[k] - e, y = y0 + pj[k] - e;
+                    if (inside(k, e) && x < g.nx && y < g.ny)
+                        store_cell<S, R, false>(static_cast<S*>(keep.state[s]), g.plane,
+                                                (unsigned)y * (unsigned)g.nx + (unsigned)x, h[k]);
+                }
+            }
+        }
         if (s > 0) __syncthreads();  // the last step's values have been read
 #pragma unroll
         for (int k = 0; k < kEach; ++k)
@@ -101,37 +117,45 @@ __global__ __launch_bounds__(NT) void k_tile(const typename Store<PREC>::S* __re
 }
 
 template <int MODEL, int PREC, int PW, int NT>
-void launch_tile_w(lbm_ctx* ctx, const double* w, int nsteps, const void* src, void* dst, int step) {
+void launch_tile_w(lbm_ctx* ctx, const double* w, int nsteps, const void* src, void* dst, int step,
+                   const TileKeep* keep) {
     using S = typename Store<PREC>::S;
     using R = typename Store<PREC>::R;
     const int tw = PW - 2 * (nsteps - 1);
     const unsigned gx = (unsigned)((ctx->nx + tw - 1) / tw), gy = (unsigned)((ctx->ny + tw - 1) / tw);
-    hipLaunchKernelGGL((k_tile<MODEL, PREC, PW, NT>), dim3(gx * gy), dim3(NT), 0, ctx->stream,
-                       reinterpret_cast<const S*>(src), reinterpret_cast<S*>(dst), ctx->geom(), make_coef<R>(w),
-                       ref_as<R>(ctx->ref), ctx->eq_order, step, ctx->d_flag, nsteps, gx);
+    if (keep)
+        hipLaunchKernelGGL((k_tile<MODEL, PREC, PW, NT, true>), dim3(gx * gy), dim3(NT), 0, ctx->stream,
+                           reinterpret_cast<const S*>(src), reinterpret_cast<S*>(dst), ctx->geom(), make_coef<R>(w),
+                           ref_as<R>(ctx->ref), ctx->eq_order, step, ctx->d_flag, nsteps, gx, *keep);
+    else
+        hipLaunchKernelGGL((k_tile<MODEL, PREC, PW, NT, false>), dim3(gx * gy), dim3(NT), 0, ctx->stream,
+                           reinterpret_cast<const S*>(src), reinterpret_cast<S*>(dst), ctx->geom(), make_coef<R>(w),
+                           ref_as<R>(ctx->ref), ctx->eq_order, step, ctx->d_flag, nsteps, gx, 0);
 }
 
 template <int MODEL, int PREC>
-void launch_tile_m(lbm_ctx* ctx, const double* w, int nsteps, const void* src, void* dst, int step) {
+void launch_tile_m(lbm_ctx* ctx, const double* w, int nsteps, const void* src, void* dst, int step,
+                   const TileKeep* keep) {
     switch (ctx->tile_patch) {
-        case 22: launch_tile_w<MODEL, PREC, 22, 512>(ctx, w, nsteps, src, dst, step); break;
-        case 32: launch_tile_w<MODEL, PREC, 32, 1024>(ctx, w, nsteps, src, dst, step); break;
-        default: launch_tile_w<MODEL, PREC, 44, 1024>(ctx, w, nsteps, src, dst, step); break;
+        case 22: launch_tile_w<MODEL, PREC, 22, 512>(ctx, w, nsteps, src, dst, step, keep); break;
+        case 32: launch_tile_w<MODEL, PREC, 32, 1024>(ctx, w, nsteps, src, dst, step, keep); break;
+        default: launch_tile_w<MODEL, PREC, 44, 1024>(ctx, w, nsteps, src, dst, step, keep); break;
     }
 }
 
 template <int PREC>
-void launch_tile_p(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst, int step) {
+void launch_tile_p(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst, int step,
+                   const TileKeep* keep) {
     switch (model) {
-        case LBM_BGK: launch_tile_m<kBGK, PREC>(ctx, w, nsteps, src, dst, step); break;
-        case LBM_RM: launch_tile_m<kRM, PREC>(ctx, w, nsteps, src, dst, step); break;
-        case LBM_HM: launch_tile_m<kHM, PREC>(ctx, w, nsteps, src, dst, step); break;
-        case LBM_CM: launch_tile_m<kCM, PREC>(ctx, w, nsteps, src, dst, step); break;
-        case LBM_CHM: launch_tile_m<kCHM, PREC>(ctx, w, nsteps, src, dst, step); break;
-        case LBM_K: launch_tile_m<kK, PREC>(ctx, w, nsteps, src, dst, step); break;
-        case LBM_PR: launch_tile_m<kPR, PREC>(ctx, w, nsteps, src, dst, step); break;
-        case LBM_RR: launch_tile_m<kRR, PREC>(ctx, w, nsteps, src, dst, step); break;
-        default: launch_tile_m<kStreamOnly, PREC>(ctx, w, nsteps, src, dst, step); break;
+        case LBM_BGK: launch_tile_m<kBGK, PREC>(ctx, w, nsteps, src, dst, step, keep); break;
+        case LBM_RM: launch_tile_m<kRM, PREC>(ctx, w, nsteps, src, dst, step, keep); break;
+        case LBM_HM: launch_tile_m<kHM, PREC>(ctx, w, nsteps, src, dst, step, keep); break;
+        case LBM_CM: launch_tile_m<kCM, PREC>(ctx, w, nsteps, src, dst, step, keep); break;
+        case LBM_CHM: launch_tile_m<kCHM, PREC>(ctx, w, nsteps, src, dst, step, keep); break;
+        case LBM_K: launch_tile_m<kK, PREC>(ctx, w, nsteps, src, dst, step, keep); break;
+        case LBM_PR: launch_tile_m<kPR, PREC>(ctx, w, nsteps, src, dst, step, keep); break;
+        case LBM_RR: launch_tile_m<kRR, PREC>(ctx, w, nsteps, src, dst, step, keep); break;
+        default: launch_tile_m<kStreamOnly, PREC>(ctx, w, nsteps, src, dst, step, keep); break;
     }
 }
 
