@@ -10,6 +10,7 @@
 
 #include <climits>
 #include <cmath>
+#include <type_traits>
 
 #include "lbm.h"
 #include "lbm_adjoint.h"
@@ -24,9 +25,10 @@ namespace {
 // Every reverse step walks the grid in strips of 64 columns and AdjShape::hs rows, one
 // workgroup of kAdjWaves waves per strip (lane l takes column x0 + l), and the strip is the unit
 // of the rate-gradient sums: the workgroup of block b adds its strip's FP64 sum to slot b.  Wave w
-// takes rows ys + w, ys + w + kAdjWaves, ... of its strip in increasing order, in the one-step
-// and the two-step kernel alike, so both add up every step's terms of a slot in the same order and
-// the gradients do not depend on which reverse steps were paired in one launch.
+// takes rows ys + w, ys + w + kAdjWaves, ... of its strip in increasing order (on small grids, AdjShape::low,
+// there are kAdjRing waves with a row each), in the one-step and the two-step kernel alike, so both add up
+// every step's terms of a slot in the same order and the gradients do not depend on which reverse steps were
+// paired in one launch.
 #ifndef LBM_ADJ_WAVES
 #define LBM_ADJ_WAVES 4
 #endif
@@ -52,7 +54,15 @@ constexpr int kAdjUnroll = LBM_ADJ_UNROLL;  // rows per wave and iteration of th
 struct AdjShape {
     int hs;           // strip rows, a multiple of kAdjRing
     unsigned sx, nb;  // strips across, strips in all
+    bool low;         // strips of one pass with a wave per row, in the one-step and the two-step kernel
 };
+
+// Strips of kAdjRing rows run their rows side by side (k_adjoint_pass2) while all of their workgroups fit the
+// device's 256 CUs at once, two per CU in FP32 and FP16 and one in FP64, by their registers.  Measured (two
+// steps per launch, us per step, CM) against four waves per strip: 256 strips or fewer (256^2) FP32 3.2 against
+// 4.6, FP64 4.3 against 5.7; 288 (384^2) FP32 4.9 against 5.5, FP64 8.5 against 7.5; 512 (512^2) FP32 5.5 against
+// 6.2, FP64 9.5 against 10.0; 800 (640^2) FP32 8.6 against 8.1, FP64 18.2 against 17.2.
+constexpr unsigned kLowStrips = 512, kLowStrips64 = 256;
 
 AdjShape adjoint_shape(const lbm_ctx* ctx) {
     AdjShape a;
@@ -62,6 +72,7 @@ AdjShape adjoint_shape(const lbm_ctx* ctx) {
     const long long h = (target + kAdjRing / 2) / kAdjRing * kAdjRing;
     a.hs = (int)(h < kAdjRing ? kAdjRing : (h > LBM_ADJ_MAX_ROWS ? LBM_ADJ_MAX_ROWS : h));
     a.nb = a.sx * (unsigned)((ctx->ny + a.hs - 1) / a.hs);
+    a.low = a.hs == kAdjRing && a.nb <= (ctx->prec == LBM_F64 ? kLowStrips64 : kLowStrips);
     return a;
 }
 
@@ -105,28 +116,73 @@ __device__ __forceinline__ void push_gather(const T* __restrict__ lam, long long
     mu[8] = R(*plane_at(lam, plane, 8, rm + xp));
 }
 
-// Rate-gradient slots: block b adds (accumulate = 1) or writes (0) its strip's FP64 sums to slot
-// b, the first reverse step's before the second's (two reverse steps per launch: a, then b), as
-// two one-step launches would.  A slot is touched by one block per launch and launches are
-// stream-ordered, so no atomics or fences are needed; one k_finalize_add per host call folds the
-// slots into domega.
-template <bool TWO>
-__device__ __forceinline__ void slots_add(double (&a)[5], double (&b)[5], double* __restrict__ slots,
-                                          int accumulate) {
-    __shared__ double ta[5], tb[5];
-    block_sum<5>(a, ta);
-    __syncthreads();
-    if constexpr (TWO) {
-        block_sum<5>(b, tb);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        double* p = slots + 5 * (size_t)blockIdx.x;
-        for (int k = 0; k < 5; ++k) {
-            double v = (accumulate ? p[k] : 0.0) + ta[k];
-            if constexpr (TWO) v += tb[k];
-            p[k] = v;
+// Sum each of N values (N <= P, a power of two) over the wave's lanes: in the first log2 P stages a lane
+// passes on half of its values and adds up the other half, so that lane l ends with the sum of value
+// slot_index(l) only: 10 exchanges for 5 values and 17 for 10, against 30 and 60 of one butterfly per value.  Every value is added up in the same order of lanes, whatever N and P.
+template <int P>
+__device__ __forceinline__ double wave_sums(double (&v)[P], int lane) {
+    int n = P;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        if (n > 1) {
+            n >>= 1;
+            const bool up = (lane & off) != 0;
+#pragma unroll
+            for (int k = 0; k < P / 2; ++k)
+                if (k < n) {
+                    double lo = v[k], hi = v[k + n];
+                    asm("" : "+v"(lo), "+v"(hi));  // two values, not one of an indexed array
+                    v[k] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, off, 64);
+                }
+        } else {
+            v[0] += __shfl_xor(v[0], off, 64);
         }
+    }
+    return v[0];
+}
+template <int P>
+__device__ __forceinline__ int slot_index(int lane) {
+    int k = 0;
+#pragma unroll
+    for (int n = P / 2, bit = 1; n > 0; n >>= 1, bit <<= 1) k += lane & bit ? n : 0;
+    return k;
+}
+
+// What slot value the thread that adds to it starts from: read at the start of a launch, where nothing waits
+// for it (threads 0 .. 4 of the block).
+__device__ __forceinline__ double slot_before(const double* __restrict__ slots, int accumulate) {
+    return accumulate && threadIdx.x < 5 ? slots[5 * (size_t)blockIdx.x + threadIdx.x] : 0.0;
+}
+
+// Rate-gradient slots: block b sets slot b to what it held before (0 at the start of a sweep) plus its strip's
+// FP64 sums, the first reverse step's (a) before the second's (two reverse steps per launch: a, then b), as
+// two one-step launches would.  Waves past WAVES have nothing to add.  A slot is touched by one block per
+// launch and launches are stream-ordered, so no atomics or fences are needed; one k_finalize_add per host
+// call folds the slots into domega.
+template <bool TWO, int WAVES>
+__device__ __forceinline__ void slots_add(const double (&a)[5], const double (&b)[5], double* __restrict__ slots,
+                                          double before) {
+    constexpr int P = TWO ? 16 : 8;
+    __shared__ double sh[WAVES][P];
+    const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x >> 6);
+    if (wave < WAVES) {
+        double v[P];
+#pragma unroll
+        for (int k = 0; k < P; ++k) v[k] = k < 5 ? a[k < 5 ? k : 0] : (TWO && k >= 8 && k < 13 ? b[k >= 8 && k < 13 ? k - 8 : 0] : 0.0);
+        const double t = wave_sums<P>(v, lane);
+        if (lane < P) sh[wave][slot_index<P>(lane)] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < 5) {
+        double ta = 0.0, tb = 0.0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            ta += sh[w][threadIdx.x];
+            if constexpr (TWO) tb += sh[w][8 + threadIdx.x];
+        }
+        double v = before + ta;
+        if constexpr (TWO) v += tb;
+        slots[5 * (size_t)blockIdx.x + threadIdx.x] = v;
     }
 }
 
@@ -183,9 +239,9 @@ __device__ __forceinline__ void store_lam(T* __restrict__ lam, const Geom& g, in
     for (int i = 0; i < 9; ++i) st<T>(plane_at(lam, g.plane, i, o), T(hb[i]));
 }
 
-// One reverse step (lambda_{n+1} -> lambda_n at state f_n) over one strip per workgroup.
-template <int MODEL, int PREC>
-__global__ __launch_bounds__(64 * kAdjWaves) void k_adjoint_strip1(
+// One reverse step (lambda_{n+1} -> lambda_n at state f_n) over one strip per workgroup of WAVES waves.
+template <int MODEL, int PREC, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_adjoint_strip1(
     const typename Store<PREC>::S* __restrict__ state, const typename AdjT<PREC>::T* __restrict__ lam_next,
     typename AdjT<PREC>::T* __restrict__ lam, Geom g, Coef<typename Store<PREC>::R> c,
     Ref<typename Store<PREC>::R> ref, int N, double* __restrict__ slots, int accumulate, int hs, unsigned sx,
@@ -196,12 +252,13 @@ __global__ __launch_bounds__(64 * kAdjWaves) void k_adjoint_strip1(
     const int x = (int)bx * 64 + (int)(threadIdx.x & 63u);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int ys = (int)by * hs, ye = min(ys + hs, g.ny);
+    const double before = slot_before(slots, accumulate);
     double ws[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     if (x < g.nx) {
-        for (int yb = ys + wave; yb < ye; yb += kAdjWaves * kAdjUnroll) {
+        for (int yb = ys + wave; yb < ye; yb += WAVES * kAdjUnroll) {
 #pragma unroll
             for (int u = 0; u < kAdjUnroll; ++u) {
-                const int y = yb + u * kAdjWaves;
+                const int y = yb + u * WAVES;
                 if (y < ye) {
                     R hb[9];
                     reverse_node<MODEL, PREC>(state, lam_next, g, x, y, c, ref, N, hb, ws, true);
@@ -210,7 +267,7 @@ __global__ __launch_bounds__(64 * kAdjWaves) void k_adjoint_strip1(
             }
         }
     }
-    slots_add<false>(ws, ws, slots, accumulate);
+    slots_add<false, WAVES>(ws, ws, slots, before);
 }
 
 // Two reverse steps per pass over one strip per workgroup: lambda_{n+1} -> lambda_n at f_n (the
@@ -247,6 +304,7 @@ __global__ __launch_bounds__(64 * kAdjWaves) void k_adjoint_strip2(
     // ring column 0 holds grid column x0 - 1, column 1 + l column x0 + l, column w + 1 x0 + w
     const int xl = x0 == 0 ? g.nx - 1 : x0 - 1;
     const int xr = x0 + w == g.nx ? 0 : x0 + w;
+    const double before = slot_before(slots, accumulate);
     double wa[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, wb[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     // first step at grid column xg and strip row r (ys - 1 <= r <= ye, wrapped here) into ring
     // column cc
@@ -304,7 +362,71 @@ __global__ __launch_bounds__(64 * kAdjWaves) void k_adjoint_strip2(
         }
         __syncthreads();
     }
-    slots_add<true>(wa, wb, slots, accumulate);
+    slots_add<true, kAdjWaves>(wa, wb, slots, before);
+}
+
+// The same two reverse steps on strips of kAdjRing rows, which small grids are cut into: every row has a wave of
+// its own, and so have the two halo rows and the halo columns, so that each step is one collision deep and the
+// second step's state is on its way while the first runs.  What bounds it on the smallest grids is the
+// latency of one launch, load, collision and barrier after the other, and from 512^2 on the vector ALU.  Measured
+// on MI355X (us per reverse step, CM, four waves per strip and one butterfly per gradient sum before, now):
+// 64^2 FP32 5.6 -> 2.9, FP64 6.0 -> 3.4; 256^2 FP32 6.1 -> 3.2, FP64 7.3 -> 4.3; 512^2 FP32 8.0 -> 5.5.  Of it the
+// sums take 0.7 us where they took over 2.
+template <int MODEL, int PREC>
+__global__ __launch_bounds__(64 * (kAdjRing + 3)) void k_adjoint_pass2(
+    const typename Store<PREC>::S* __restrict__ state_n, const typename Store<PREC>::S* __restrict__ state_m,
+    const typename AdjT<PREC>::T* __restrict__ lam_next, typename AdjT<PREC>::T* __restrict__ lam, Geom g,
+    Coef<typename Store<PREC>::R> c, Ref<typename Store<PREC>::R> ref, int N, double* __restrict__ slots,
+    int accumulate, unsigned sx, unsigned nb, int xcd) {
+    using R = typename Store<PREC>::R;
+    using T = typename AdjT<PREC>::T;
+    constexpr int NR = kAdjRing + 2;
+    __shared__ T ring[9][NR][66];
+    unsigned bx, by;
+    strip_of_block<PREC>(blockIdx.x, sx, nb, xcd, bx, by);
+    const int x0 = (int)bx * 64, ys = (int)by * kAdjRing, ye = min(ys + kAdjRing, g.ny);
+    const int lane = (int)(threadIdx.x & 63u);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int w = min(64, g.nx - x0);
+    const double before = slot_before(slots, accumulate);
+    double wa[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, wb[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    // first step: waves 0 .. kAdjRing - 1 take the strip's rows (whose terms count), the next two the halo rows
+    // ys - 1 and ye, the last one the halo columns of them all, two lanes per row
+    const bool own = wave < kAdjRing && ys + wave < ye && lane < w;
+    int r, cc, x;
+    bool on;
+    if (wave <= kAdjRing + 1) {
+        r = wave < kAdjRing ? ys + wave : (wave == kAdjRing ? ys - 1 : ye);
+        cc = lane + 1;
+        x = x0 + lane;
+        on = lane < w && (wave >= kAdjRing || r < ye);
+    } else {
+        r = ys - 1 + (lane >> 1);
+        cc = lane & 1 ? w + 1 : 0;
+        x = lane & 1 ? (x0 + w == g.nx ? 0 : x0 + w) : (x0 == 0 ? g.nx - 1 : x0 - 1);
+        on = r <= ye;
+    }
+    R hm[9];
+    if (on) {
+        const int yw = r < 0 ? r + g.ny : (r >= g.ny ? r - g.ny : r);
+        const Nbr n = neighbours(x, yw, g.nx, g.ny);
+        R h[9], mu[9], hb[9];
+        pull_load(state_n, g.plane, n, h);
+        push_gather(lam_next, g.plane, n, mu);
+        if (own) pull_load(state_m, g.plane, n, hm);
+        reverse_core<MODEL, PREC>(h, mu, c, ref, N, hb, wa, own);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) ring[i][r - ys + 1][cc] = T(hb[i]);
+    }
+    __syncthreads();
+    if (own) {
+        R mu[9], hb[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) mu[i] = R(ring[i][wave + 1 + cy(i)][lane + 1 + cx(i)]);
+        reverse_core<MODEL, PREC>(hm, mu, c, ref, N, hb, wb, true);
+        store_lam(lam, g, x, r, hb);
+    }
+    slots_add<true, kAdjRing>(wa, wb, slots, before);
 }
 
 // Velocity of the current state in FP64 (pull).
@@ -393,17 +515,31 @@ void launch_adj_t(lbm_ctx* ctx, const double* w, const void* state_n, const void
     using R = typename Store<PREC>::R;
     using T = typename AdjT<PREC>::T;
     const AdjShape a = adjoint_shape(ctx);
-    if (state_m)
+    if (state_m && a.low)
+        hipLaunchKernelGGL((k_adjoint_pass2<MODEL, PREC>), dim3(a.nb), dim3(64 * (kAdjRing + 3)), 0, ctx->stream,
+                           reinterpret_cast<const S*>(state_n), reinterpret_cast<const S*>(state_m),
+                           reinterpret_cast<const T*>(lam_next), reinterpret_cast<T*>(lam), ctx->geom(),
+                           make_coef<R>(w), ref_as<R>(ctx->ref), ctx->eq_order, ctx->d_wslots, accumulate, a.sx, a.nb,
+                           LBM_ADJ_XCD);
+    else if (state_m)
         hipLaunchKernelGGL((k_adjoint_strip2<MODEL, PREC>), dim3(a.nb), dim3(64 * kAdjWaves), 0, ctx->stream,
                            reinterpret_cast<const S*>(state_n), reinterpret_cast<const S*>(state_m),
                            reinterpret_cast<const T*>(lam_next), reinterpret_cast<T*>(lam), ctx->geom(),
                            make_coef<R>(w), ref_as<R>(ctx->ref), ctx->eq_order, ctx->d_wslots, accumulate, a.hs,
                            a.sx, a.nb, LBM_ADJ_XCD);
-    else
-        hipLaunchKernelGGL((k_adjoint_strip1<MODEL, PREC>), dim3(a.nb), dim3(64 * kAdjWaves), 0, ctx->stream,
-                           reinterpret_cast<const S*>(state_n), reinterpret_cast<const T*>(lam_next),
-                           reinterpret_cast<T*>(lam), ctx->geom(), make_coef<R>(w), ref_as<R>(ctx->ref),
-                           ctx->eq_order, ctx->d_wslots, accumulate, a.hs, a.sx, a.nb, LBM_ADJ_XCD);
+    else {
+        auto launch = [&](auto waves) {
+            constexpr int W = decltype(waves)::value;
+            hipLaunchKernelGGL((k_adjoint_strip1<MODEL, PREC, W>), dim3(a.nb), dim3(64 * W), 0, ctx->stream,
+                               reinterpret_cast<const S*>(state_n), reinterpret_cast<const T*>(lam_next),
+                               reinterpret_cast<T*>(lam), ctx->geom(), make_coef<R>(w), ref_as<R>(ctx->ref),
+                               ctx->eq_order, ctx->d_wslots, accumulate, a.hs, a.sx, a.nb, LBM_ADJ_XCD);
+        };
+        if (a.low)
+            launch(std::integral_constant<int, kAdjRing>{});
+        else
+            launch(std::integral_constant<int, kAdjWaves>{});
+    }
 }
 
 template <int PREC>
