@@ -667,24 +667,29 @@ bool walk_takes(const lbm_instance_desc& d) {
     return d.ny >= kWalkHalo && (d.nx % 2 == 0 || d.nx >= 64 * walk_cols<kF64>());
 }
 
-// The tasks of the live instances, in order of the model, cut at about hs rows (an even number, spread
-// evenly over the segments); with `out` null only counted.  `rows` receives the rows of all of them with the
-// 2 (D - 1) that fill up a task's steps, `longest` the most of one.
-long long walk_tasks(const lbm_batch* b, const std::vector<char>& live, int hs, int depth, std::vector<WalkTask>* out,
-                     long long& rows, int& longest) {
+// Time of a row of a walking task by model, BGK = 1 (a grid of 1400^2 in FP64, 10.9 to 13.5 us per step).
+constexpr double kWalkRow[8] = {1.0, 1.065, 1.077, 1.137, 1.166, 1.24, 1.05, 1.12};
+
+// The tasks of the live instances, in order of the model, cut at about hs rows of BGK (an even number, spread
+// evenly over the segments) or as many fewer of a heavier model as last as long; with `out` null only
+// counted.  `rows` receives the rows of all of them with the 2 (D - 1) that fill up a task's steps, `longest` the
+// most of one, both in the time of BGK's.
+long long walk_tasks(const lbm_batch* b, const std::vector<char>& live, int height, int depth, std::vector<WalkTask>* out,
+                     double& rows, double& longest) {
     long long count = 0;
-    rows = 0;
-    longest = 0;
+    rows = 0.0;
+    longest = 0.0;
     for (int model = 0; model < 8; ++model)
         for (int j = 0; j < b->n; ++j) {
             const lbm_instance_desc& d = b->hdesc[j];
             if (!live[j] || d.model != model) continue;
             const int sx = walk_strips(d.nx, walk_width<kF64>(), walk_cols<kF64>());
+            const int hs = std::max(2, (int)((double)height / kWalkRow[model]));
             const int pieces = (d.ny + hs - 1) / hs, h = ((d.ny + pieces - 1) / pieces + 1) / 2 * 2;
             const int segments = (d.ny + h - 1) / h;
             count += (long long)sx * segments;
-            rows += (long long)sx * (d.ny + 2LL * (depth - 1) * segments);
-            longest = std::max(longest, std::min(h, d.ny) + 2 * (depth - 1));
+            rows += kWalkRow[model] * (double)((long long)sx * (d.ny + 2LL * (depth - 1) * segments));
+            longest = std::max(longest, kWalkRow[model] * (std::min(h, d.ny) + 2 * (depth - 1)));
             if (out)
                 for (int y = 0; y < segments; ++y)
                     for (int x = 0; x < sx; ++x) out->push_back({j, x, y * h, std::min((y + 1) * h, d.ny)});
@@ -705,20 +710,18 @@ int deal_tasks(lbm_batch* b, const std::vector<char>& live) {
     double time = 0.0;
     for (const lbm_instance_desc& d : b->hdesc) tallest = std::max(tallest, d.ny);
     for (int hs = 8;; hs += std::max(2, hs / 16 * 2)) {
-        long long rows;
-        int longest;
+        double rows, longest;
         const long long count = walk_tasks(b, live, hs, depth, nullptr, rows, longest);
-        const double t = (double)longest + (count > slots ? (double)rows / (double)slots : 0.0);
+        const double t = longest + (count > slots ? rows / (double)slots : 0.0);
         if ((!b->d_tasks || count <= b->ntasks) && (best == 0 || t < time)) {
             best = hs;
             time = t;
         }
-        if (hs >= tallest) break;
+        if (hs >= 2 * tallest) break;
     }
     if (best == 0) return set_error(LBM_EHIP, "walking tasks overflow");
     std::vector<WalkTask> tasks;
-    long long rows;
-    int longest;
+    double rows, longest;
     walk_tasks(b, live, best, depth, &tasks, rows, longest);
     int rc = LBM_OK;
     if (!b->d_tasks) {

@@ -10,8 +10,9 @@
 // FP64, times what lies outside the grid: strips are 112 columns wide whatever the instance's width, and each
 // task first fills up its D steps in 2 (D - 1) rows.  The host cuts the instances into as many tasks as there
 // are wave slots (deal_tasks).  Measured on MI355X, 56 grids of 64 to 512 nodes a side and all models (us per
-// step, three steps per persistent pass before, 5 steps per walking pass now): FP64 51.9 -> 32.1, FP32 37.8 ->
-// 26.2; 17 of them FP64 23.2 -> 12.2.  Blocks of one wave instead of four measured the same.
+// step, three steps per persistent pass before, 5 steps per walking pass now): FP64 51.9 -> 31.6, FP32 37.8 ->
+// 23.7; 17 of them FP64 23.2 -> 11.4 (with tasks of equal rows, whatever the model: 32.1, 26.2 and
+// 12.2).  Blocks of one wave instead of four measured the same.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -292,10 +292,12 @@ constexpr long long kWideMinStrips = 1024;
 // against strip launches and, in brackets, tile launches, BGK / K):
 // - FP64: 768^2 5.7 / 7.0 against 6.3 / 7.0 (4.9 / 5.4), 1024^2 8.1 / 10.2 against 13.5 / 14.0 (8.4 / 9.9),
 //   2048^2 23.2 / 27.5 against 46.9 / 48.3, 4096^2 81 / 100 against 163 / 169;
-// - FP32: 1024^2 7.7 / 8.2 (5.4 / 6.4), 1470^2 12.8 / 16.5 (1450^2: 11.1 / 12.6), 2048^2 18.4 / 23.5 against
+// - FP32: 1024^2 7.7 / 8.2 (5.4 / 6.4), 1470^2 12.8 / 16.5 (1450^2: 11.1 / 12.6), 1700^2 14.9 /
+//   18.5 (14.0 / 15.7), 2048^2 18.4 / 23.5 against
 //   26.2 / 27.6, 4096^2 55 / 73 against 88 / 86, 3001 x 2047 23.7 / 30.8 against 45.8 / 46.1;
-// - FP16: 1024^2 7.2 / 9.3 (5.0 / 5.9), 1470^2 12.2 / 16.1 (1450^2: 9.8 / 11.6), 2048^2 17.8 / 23.2 against 27.0 / 28.8, 4096^2 50 / 68 against 77 / 80.
-// The line is drawn at the rows of a strip per slot (1024^2: 10 in FP64, 5 in FP32 and FP16; 1470^2: 10.0,
+// - FP16: 1024^2 7.2 / 9.3 (5.0 / 5.9), 1470^2 12.2 / 16.1 (1450^2: 9.8 / 11.6), 1700^2 13.6 / 17.6
+//   (12.5 / 14.5), 2048^2 17.8 / 23.2 against 27.0 / 28.8, 4096^2 50 / 68 against 77 / 80.
+// The line is drawn at the rows of a strip per slot (1024^2: 10 in FP64, 5 in FP32 and FP16; 1700^2: 13.3,
 // 2048^2: 19) and where at most a quarter of the strips' columns lie outside the grid.  A segment's first
 // 2 (D - 1) iterations fill up the D steps, so lower segments take fewer: FP64 1152^2 (14 rows) 9.7 / 11.7
 // with six, 11.8 / 12.5 with four; 2048^2 (40 rows) 23.2 / 27.5 with six, 22.2 / 28.9 with eight; 4096^2
@@ -310,7 +312,7 @@ WalkPick walk_pick(int nx, int ny, int prec, int cus) {
     if (cus <= 0 || nx < 64 * V || ny < 2 * kWalkHalo) return {0, 0};
     const long long sx = walk_strips(nx, W, V), slots = 4LL * cus * (prec == LBM_F64 ? 1 : 2);
     const double per_slot = (double)sx * ny / (double)slots;
-    if (per_slot < (prec == LBM_F64 ? 9.5 : 13.0) || 3 * sx * W > 4LL * nx) return {0, 0};
+    if (per_slot < (prec == LBM_F64 ? 9.5 : 14.5) || 3 * sx * W > 4LL * nx) return {0, 0};
     const long long segments = std::max(1LL, slots / sx);
     const int hs = (int)((ny + segments - 1) / segments + 1) / 2 * 2;
     switch (prec) {
@@ -325,14 +327,14 @@ WalkPick walk_pick(int nx, int ny, int prec, int cus) {
 // measured at each size): 3.6 us per launch, and per step the larger of 0.55 us, the latency of a patch's
 // step, and its work, by the nodes of the rows that are still valid, times the patches per CU.  A patch of
 // 44 in FP64 fills a CU's LDS, and one patch at a time hides no latency (768^2: 6.0 us per step, 32: 4.9).
-// patch = 0 where strips stay: grids of more than 3 2^20 nodes (FP32 4096^2: strips 5.5 us per million nodes,
-// tiles 5.3 / 6.0 at 1450^2) and grids of fewer than 16 nodes a side that need more than one patch per CU.
+// patch = 0 where strips stay: grids of more than 2^22 nodes (FP32 4096^2: strips 5.5 us per million nodes,
+// tiles 4.8 / 5.4 at 1700^2) and grids of fewer than 16 nodes a side that need more than one patch per CU.
 struct TilePick {
     int patch, steps;
 };
 
 TilePick tile_pick(int nx, int ny, int prec, int cus) {
-    if (cus <= 0 || (long long)nx * ny > 3LL << 20) return {0, 0};
+    if (cus <= 0 || (long long)nx * ny > 1LL << 22) return {0, 0};
     const double work = prec == LBM_F64 ? 0.30 : (prec == LBM_F32_SHIFTED ? 0.20 : 0.19);
     TilePick pick{0, 0};
     double best = 0.0;

@@ -20,7 +20,7 @@ def state(sim, buf):
 
 @pytest.mark.parametrize("prec,nx,ny,kind", [("f64", 37, 50, "tile"), ("f32", 300, 200, "tile"), ("f16", 512, 500, "tile"),
                                              ("f64", 700, 640, "tile"), ("f64", 1100, 1000, "walk"),
-                                             ("f32", 1801, 1702, "walk"), ("f16", 1901, 1753, "walk")])
+                                             ("f32", 2131, 1901, "walk"), ("f16", 2131, 1901, "walk")])
 def test_chain(gpu, prec, nx, ny, kind):
     fields = [torch.tensor(a, device=gpu) for a in inputs.vortex_fields(nx, ny, 0.2)]
     s = Sim(*fields, prec=prec, device=gpu, ref_velocity=(0.1, 0.0))

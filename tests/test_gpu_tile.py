@@ -105,7 +105,7 @@ def test_tile_settings(gpu):
     assert s.tile("K") in ((0, 0), first)
     s.close()
     # walking launches, too many nodes, too low for more than a patch per CU
-    for prec, nx, ny in (("f64", 1030, 1030), ("f32", 1800, 1800), ("f64", 100, 40000), ("f32", 30000, 15)):
+    for prec, nx, ny in (("f64", 1030, 1030), ("f32", 2048, 2048), ("f64", 100, 50000), ("f32", 30000, 15)):
         t = Sim(np.ones((ny, nx)), np.zeros((ny, nx)), np.zeros((ny, nx)), prec=prec, device=gpu)
         assert t.tile("BGK") == (0, 0), (prec, nx, ny)
         t.close()

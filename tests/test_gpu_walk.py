@@ -15,8 +15,8 @@ pytestmark = pytest.mark.gpu
 
 MODELS = list(inputs.MODEL_NAMES) + ["STREAM_ONLY"]
 # (precision, nx, ny, most steps per launch, steps)
-CASES = [("f64", 1009, 997, 6, 29), ("f64", 2465, 2410, 8, 29), ("f32", 1801, 1702, 6, 13),
-         ("f32", 1905, 1801, 6, 29), ("f32", 2689, 2300, 8, 29), ("f16", 1901, 1753, 6, 19)]
+CASES = [("f64", 1009, 997, 6, 29), ("f64", 1231, 1201, 6, 29), ("f64", 2465, 2410, 8, 29), ("f32", 2129, 1850, 6, 13),
+         ("f32", 2131, 1901, 6, 29), ("f32", 2689, 2300, 8, 29), ("f16", 2131, 1901, 6, 19)]
 
 
 def rough(nx, ny, seed, device):
@@ -61,14 +61,14 @@ def test_walk_bit_identical(gpu, prec, nx, ny, depth, steps):
 @pytest.mark.parametrize("prec,depth", [("f64", 6), ("f32", 6), ("f16", 6)])
 @pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12])
 def test_walk_step_counts(gpu, prec, depth, n):
-    nx, ny = {"f64": (1026, 990), "f32": (1906, 1600), "f16": (1906, 1602)}[prec]
+    nx, ny = {"f64": (1026, 990), "f32": (2130, 1900), "f16": (2130, 1902)}[prec]
     print(f"walk {prec} {nx}x{ny} steps {n}", flush=True)
     walk, same, (ta, tb) = pair(gpu, prec, "RR", nx, ny, inputs.rates(1e-2, "SRT"), n)
     assert walk[0] == depth
     assert same and ta == tb == (n, -1)
 
 
-@pytest.mark.parametrize("prec,nx,ny", [("f64", 1009, 1000), ("f64", 1026, 1000), ("f32", 1905, 1600), ("f16", 1905, 1600)])
+@pytest.mark.parametrize("prec,nx,ny", [("f64", 1009, 1000), ("f64", 1230, 1201), ("f32", 2129, 1900), ("f16", 2129, 1900)])
 def test_walk_blowup_step(gpu, prec, nx, ny):
     # zero rates: populations only stream.  f_3 = f_1 = -0.6 planted d nodes right and left of a node
     # meet there d steps later and make its density negative; nowhere before
@@ -88,7 +88,7 @@ def test_walk_blowup_step(gpu, prec, nx, ny):
 
 
 def test_walk_settings(gpu):
-    one, zero = np.ones((1100, 1100)), np.zeros((1100, 1100))
+    one, zero = np.ones((1200, 1200)), np.zeros((1200, 1200))
     s = Sim(one, zero, zero, prec="f64", device=gpu)
     depth, rows = s.walk("K")
     assert depth == 6 and rows % 2 == 0
@@ -99,15 +99,15 @@ def test_walk_settings(gpu):
     assert s.walk("K")[0] in (0, 4, 6, 8)
     s.close()
     # too few strips, too narrow, too low
-    for prec, nx, ny in (("f64", 960, 960), ("f32", 1600, 1600), ("f16", 1600, 1600), ("f64", 120, 40000),
+    for prec, nx, ny in (("f64", 960, 960), ("f32", 1700, 1700), ("f16", 1700, 1700), ("f64", 120, 40000),
                          ("f64", 130, 40000), ("f64", 40000, 15)):
         t = Sim(np.ones((ny, nx)), np.zeros((ny, nx)), np.zeros((ny, nx)), prec=prec, device=gpu)
         assert t.walk("BGK") == (0, 0), (prec, nx, ny)
         t.close()
 
 
-@pytest.mark.parametrize("prec,nx,ny,n", [("f64", 1100, 1000, 12), ("f64", 1009, 997, 4), ("f32", 1801, 1702, 6),
-                                          ("f32", 1801, 1702, 40), ("f16", 1901, 1753, 8), ("f16", 1901, 1753, 16)])
+@pytest.mark.parametrize("prec,nx,ny,n", [("f64", 1230, 1200, 12), ("f64", 1009, 997, 4), ("f32", 2131, 1901, 6),
+                                          ("f32", 2131, 1901, 40), ("f16", 2131, 1901, 8), ("f16", 2131, 1901, 16)])
 def test_walk_captured_run(gpu, prec, nx, ny, n):
     # an even number of strip launches: the captured run ends in the copy it starts from and can be
     # replayed to go on, with eager work between the replays
