@@ -417,7 +417,10 @@ def batched_sweep(steps: int, plain_f64_mlups: float, n_inst: int = 512):
     b = Batch(insts, fields, prec="f64", device="cuda:0")
     tuned = b.autotune(3)
     fused_rows = b.fusion()  # 0: one step per pass won the autotuning
-    per_pass = b.fusion_depth() if fused_rows else 1
+    kind, walk_steps = b.passes()  # 1: walking passes, of at most walk_steps steps, won
+    per_pass = walk_steps if kind == 1 else (b.fusion_depth() if fused_rows else 1)
+    if kind == 1:
+        fused_rows = 0
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
     e0.record()
@@ -891,11 +894,11 @@ def reverse_profile_summary(out_root: str, prec: str, n: int = 4096):
             "|---|---|---|---|---|---|---|---|---|---|---|"]
     blob = {"prec": prec, "n": n, "algorithmic_bytes": alg, "kernels": {}}
     for r in stats:
-        m = re.search(r"k_adjoint_strip([12])<(\d+), (\d+)>", r["Name"])
+        m = re.search(r"k_adjoint_strip([12])<(\d+), (\d+)(?:, \d+)?>", r["Name"])
         if not m:
             continue
         depth, model = m.group(1), int(m.group(2))
-        key = f"k_adjoint_strip{depth}<{model}, {m.group(3)}>"
+        key = m.group(0)
         label = f"k_adjoint_strip{depth}<{MODEL_ORDER[model] if model < 8 else model}, {prec}>"
         avg = float(r["AverageNs"]) * 1e-3
         f_kib, _ = _per_dispatch(fetch, key)

@@ -64,8 +64,8 @@ int lbm_batch_create(lbm_batch** out, const lbm_instance_desc* desc, int n, int 
                      const double* rho, const double* ux, const double* uy, void* pop_buf,
                      size_t pop_bytes, void* hip_stream);
 
-/* Advance every live instance by nsteps >= 0 steps in one cooperative persistent launch (with
- * two steps per pass on, lbm_batch_set_fusion: the first 4 * (nsteps / 4) steps in a launch of
+/* Advance every live instance by nsteps >= 0 steps, by the kind of pass that lbm_batch_set_pass chose, in
+ * persistent passes (kind 0) in one cooperative persistent launch (with two steps per pass on, lbm_batch_set_fusion: the first 4 * (nsteps / 4) steps in a launch of
  * the two-step kernel, the rest in one of the single-step kernel; with three steps per pass,
  * lbm_batch_set_fusion_depth: the first 3 * (nsteps / 3) steps in a launch of the three-step
  * kernel, the rest one step per pass).
@@ -107,7 +107,7 @@ int lbm_batch_set_active(lbm_batch* b, const int* active);
 /* Re-deal the live instances (neither blown up nor retired) over the XCDs, largest first, so that
  * every XCD keeps a similar number of nodes to advance as instances drop out; instances that are
  * no longer live leave the per-XCD work lists.  Results are unchanged: an instance's arithmetic is
- * the same on every XCD.  Synchronises the stream. */
+ * the same on every XCD.  Resident passes (lbm_batch_set_pass) keep no lists.  Synchronises the stream. */
 int lbm_batch_rebalance(lbm_batch* b);
 
 /* Launch shape of the persistent kernel: nodes per thread per tile (1, 2 or 4) and resident
@@ -140,7 +140,8 @@ int lbm_batch_set_fusion_depth(lbm_batch* b, int steps);
 /* Steps per fused pass (host pointer, may be NULL). */
 int lbm_batch_get_fusion_depth(lbm_batch* b, int* steps);
 
-/* Passes by ordinary launches in place of the persistent ones (which are the default):
+/* Passes by ordinary launches in place of the persistent ones; a new batch takes resident passes if its
+ * instances are small enough for them, else persistent ones:
  *   kind 0  persistent launches, as lbm_batch_set_launch, _set_fusion and _set_fusion_depth say (each of
  *           these returns to them);
  *   kind 1  walking passes: 7, 5 and 3 steps per pass (5 and 3 in FP16), one wave walking down each strip of

@@ -55,6 +55,7 @@ def transport_accuracy(models_presets, Ls, mach: float = 0.5, nu: float = 1e-4, 
         fields = inputs.vortex_fields(L, L, mach, beta=beta, radius_frac=radius_frac)
         steps = int(round(M * L / u0))
         b = Batch(insts, [fields] * len(insts), prec=prec, device=dev)
+        b.autotune(3)
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         e0.record()
         b.run(steps)

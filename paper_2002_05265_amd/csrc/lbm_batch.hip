@@ -670,30 +670,29 @@ bool walk_takes(const lbm_instance_desc& d) {
 // Time of a row of a walking task by model, BGK = 1 (a grid of 1400^2 in FP64, 10.9 to 13.5 us per step).
 constexpr double kWalkRow[8] = {1.0, 1.065, 1.077, 1.137, 1.166, 1.24, 1.05, 1.12};
 
-// The tasks of the live instances, in order of the model, cut at about hs rows of BGK (an even number, spread
+// The tasks of the live instances, in the order given (by model), cut at about hs rows of BGK (an even number, spread
 // evenly over the segments) or as many fewer of a heavier model as last as long; with `out` null only
 // counted.  `rows` receives the rows of all of them with the 2 (D - 1) that fill up a task's steps, `longest` the
 // most of one, both in the time of BGK's.
-long long walk_tasks(const lbm_batch* b, const std::vector<char>& live, int height, int depth, std::vector<WalkTask>* out,
+long long walk_tasks(const lbm_batch* b, const std::vector<int>& live, int height, int depth, std::vector<WalkTask>* out,
                      double& rows, double& longest) {
     long long count = 0;
     rows = 0.0;
     longest = 0.0;
-    for (int model = 0; model < 8; ++model)
-        for (int j = 0; j < b->n; ++j) {
-            const lbm_instance_desc& d = b->hdesc[j];
-            if (!live[j] || d.model != model) continue;
-            const int sx = walk_strips(d.nx, walk_width<kF64>(), walk_cols<kF64>());
-            const int hs = std::max(2, (int)((double)height / kWalkRow[model]));
-            const int pieces = (d.ny + hs - 1) / hs, h = ((d.ny + pieces - 1) / pieces + 1) / 2 * 2;
-            const int segments = (d.ny + h - 1) / h;
-            count += (long long)sx * segments;
-            rows += kWalkRow[model] * (double)((long long)sx * (d.ny + 2LL * (depth - 1) * segments));
-            longest = std::max(longest, kWalkRow[model] * (std::min(h, d.ny) + 2 * (depth - 1)));
-            if (out)
-                for (int y = 0; y < segments; ++y)
-                    for (int x = 0; x < sx; ++x) out->push_back({j, x, y * h, std::min((y + 1) * h, d.ny)});
-        }
+    for (int j : live) {
+        const lbm_instance_desc& d = b->hdesc[j];
+        const double row = kWalkRow[d.model];
+        const int sx = walk_strips(d.nx, walk_width<kF64>(), walk_cols<kF64>());
+        const int hs = std::max(2, (int)((double)height / row));
+        const int pieces = (d.ny + hs - 1) / hs, h = ((d.ny + pieces - 1) / pieces + 1) / 2 * 2;
+        const int segments = (d.ny + h - 1) / h;
+        count += (long long)sx * segments;
+        rows += row * (double)((long long)sx * (d.ny + 2LL * (depth - 1) * segments));
+        longest = std::max(longest, row * (std::min(h, d.ny) + 2 * (depth - 1)));
+        if (out)
+            for (int y = 0; y < segments; ++y)
+                for (int x = 0; x < sx; ++x) out->push_back({j, x, y * h, std::min((y + 1) * h, d.ny)});
+    }
     return count;
 }
 
@@ -701,9 +700,13 @@ long long walk_tasks(const lbm_batch* b, const std::vector<char>& live, int heig
 // the height with the shortest pass, which lasts as long as its longest task, and where there are more
 // tasks than slots up to as long as all of them over the slots on top.  The table keeps its size (d_tasks null: it is allocated for these tasks), so that a captured pass
 // stays valid when the instances are dealt anew.  Synchronous.
-int deal_tasks(lbm_batch* b, const std::vector<char>& live) {
+int deal_tasks(lbm_batch* b, const std::vector<char>& is_live) {
     for (const lbm_instance_desc& d : b->hdesc)
         if (!walk_takes(d)) return LBM_OK;
+    std::vector<int> live;
+    for (int j = 0; j < b->n; ++j)
+        if (is_live[j]) live.push_back(j);
+    std::stable_sort(live.begin(), live.end(), [&](int i, int j) { return b->hdesc[i].model < b->hdesc[j].model; });
     const long long slots = 4LL * b->cus * (b->prec == LBM_F64 ? 1 : 2);
     const int depth = b->prec == LBM_F16_SHIFTED ? 5 : 7;
     int best = 0, tallest = 0;
@@ -1080,6 +1083,7 @@ int lbm_batch_create(lbm_batch** out, const lbm_instance_desc* desc, int n, int 
     b->copy_elems = o;
     for (int j = 0; j < n; ++j) b->most_cells = std::max(b->most_cells, desc[j].nx * desc[j].ny);
     b->walk_depth = prec == LBM_F16_SHIFTED ? 5 : 7;
+    b->pass = resident_takes(b) ? 2 : 0;
 
     int rc = LBM_OK;
     int dev = 0, clock_khz = 0;
@@ -1345,6 +1349,8 @@ int lbm_batch_set_active(lbm_batch* b, const int* active) {
 
 int lbm_batch_rebalance(lbm_batch* b) {
     if (!b) return set_error(LBM_ESTATE, "batch is NULL");
+    // resident passes have no lists (those of the other kinds may hold instances that are no longer live)
+    if (b->pass == 2) return check_hip(hipStreamSynchronize(b->stream), "synchronise");
     std::vector<char> live;
     const int rc = live_set(b, live);
     return rc != LBM_OK ? rc : deal_tables(b, live);
