@@ -111,7 +111,13 @@ int lbm_init_shifted(lbm_ctx** out, int nx, int ny, int prec, int eq_order, doub
  *          three (forced to 1).
  * CM, CHM and K require eq_order == 4 (LBM_EUNSUPPORTED otherwise).
  * Every step also checks the state it reads for a node with !(rho > 0) (this catches NaN);
- * the first such step is reported by lbm_status.  Asynchronous. */
+ * the first such step is reported by lbm_status.  Asynchronous.
+ * Can be captured into a graph, as can the calls that read or replace the state.  A captured call works on the
+ * copy that held the state when it was recorded: replay it when the state is in that copy again.  A call
+ * leaves the state in the copy it found it in, captured or not, if the strip launches that
+ * lbm_get_fusion and lbm_get_fusion_depth describe would take an even number for nsteps steps, and in the
+ * other copy if an odd one, whatever launches it takes (a context none of whose calls has been captured
+ * is free of this rule). */
 int lbm_step(lbm_ctx* ctx, int model, const double* omega, int nsteps);
 
 /* Macroscopic fields of the current state f(., n) and their totals.

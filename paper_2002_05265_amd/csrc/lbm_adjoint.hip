@@ -573,6 +573,7 @@ size_t lbm_adjoint_bytes(lbm_ctx* ctx) {
 int lbm_save_state(lbm_ctx* ctx, void* dst) {
     if (!ctx) return set_error(LBM_ESTATE, "context is NULL");
     if (!dst) return set_error(LBM_EINVAL, "dst is NULL");
+    note_capture(ctx);
     return check_hip(hipMemcpyAsync(dst, ctx->copy(ctx->cur), lbm_state_bytes(ctx), hipMemcpyDeviceToDevice,
                                     ctx->stream),
                      "save state");
@@ -582,6 +583,7 @@ int lbm_load_state(lbm_ctx* ctx, const void* src, long long step) {
     if (!ctx) return set_error(LBM_ESTATE, "context is NULL");
     if (!src) return set_error(LBM_EINVAL, "src is NULL");
     if (step < 0 || step >= INT_MAX) return set_error(LBM_EINVAL, "step %lld out of range", step);
+    note_capture(ctx);
     int rc = check_hip(hipMemcpyAsync(ctx->copy(ctx->cur), src, lbm_state_bytes(ctx), hipMemcpyDeviceToDevice,
                                       ctx->stream),
                        "load state");
@@ -643,6 +645,7 @@ int lbm_adjoint_step(lbm_ctx* ctx, int model, const double* omega, const void* s
                      const void* lam_next, void* lam, double* domega) {
     if (!ctx) return set_error(LBM_ESTATE, "context is NULL");
     if (!lam_next || !lam || !domega) return set_error(LBM_EINVAL, "NULL pointer");
+    if (!state) note_capture(ctx);
     const void* st = state ? state : ctx->copy(ctx->cur);
     void* lams[2] = {const_cast<void*>(lam_next), lam};
     return lbm_adjoint_many(ctx, model, omega, &st, 1, lams, domega);

@@ -958,6 +958,16 @@ namespace lbm {
 
 int reset_blowup(lbm_ctx* ctx) { return reset_flag(ctx); }
 
+void note_capture(lbm_ctx* ctx) {
+    if (ctx->copy_recorded || !ctx->stream) return;  // the default stream cannot be captured
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        cap = hipStreamCaptureStatusActive;  // not known: the stricter rule
+    }
+    ctx->copy_recorded = cap != hipStreamCaptureStatusNone;
+}
+
 int reduce_partials(lbm_ctx* ctx) {
     hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kFinalizeThreads), 0, ctx->stream, ctx->d_part, ctx->nblocks,
                        ctx->d_tot);
@@ -1100,19 +1110,13 @@ int lbm_step(lbm_ctx* ctx, int model, const double* omega, int nsteps) {
     rc = validate_omega(omega);
     if (rc != LBM_OK) return rc;
     if (ctx->step + nsteps >= INT_MAX) return set_error(LBM_EINVAL, "step counter would overflow");
+    note_capture(ctx);
     const int depth = ctx->walk_depth[lbm_ctx::slot(model)], tile = ctx->tile_steps[lbm_ctx::slot(model)];
     if ((!depth && !tile) || nsteps < 2) {
         step_strips(ctx, model, omega, nsteps);
         return check_hip(hipGetLastError(), "step kernel launch");
     }
-    // A captured run leaves the state in the copy that the strip launches would leave it in: one with an
-    // even number of them can be replayed to go on from its own result
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (ctx->stream) {
-        rc = check_hip(hipStreamIsCapturing(ctx->stream, &cap), "hipStreamIsCapturing");
-        if (rc != LBM_OK) return rc;
-    }
-    int parity = cap == hipStreamCaptureStatusNone ? -1 : strip_launches(ctx, model, nsteps) & 1;
+    int parity = ctx->copy_recorded ? strip_launches(ctx, model, nsteps) & 1 : -1;
     auto launch = [&](int d) {
         if (d < (depth ? 4 : 2)) return step_strips(ctx, model, omega, d);
         if (depth)
@@ -1297,6 +1301,7 @@ int lbm_step_raw_chain(lbm_ctx* ctx, int model, const double* omega, const void*
 
 int lbm_moments(lbm_ctx* ctx, double* rho, double* ux, double* uy, double* totals) {
     if (!ctx) return set_error(LBM_ESTATE, "context is NULL");
+    note_capture(ctx);
     const int nb = launch_moments(ctx, rho, ux, uy, ctx->d_part);
     int rc = check_hip(hipGetLastError(), "moments kernel launch");
     if (rc != LBM_OK || !totals) return rc;
@@ -1323,6 +1328,7 @@ int lbm_moments_noalloc(lbm_ctx* ctx, double* rho, double* ux, double* uy, doubl
     if (ctx->nblocks > kNoAllocMaxBlocks)
         return set_error(LBM_EINVAL, "grid %d x %d needs %d reduction blocks; lbm_moments_noalloc holds %d",
                          ctx->nx, ctx->ny, ctx->nblocks, kNoAllocMaxBlocks);
+    note_capture(ctx);
     double* part = ctx->d_static;
     double* tot = ctx->d_static + 5 * (size_t)kNoAllocMaxBlocks;
     const int nb = launch_moments(ctx, rho, ux, uy, part);
@@ -1351,6 +1357,7 @@ int lbm_status(lbm_ctx* ctx, long long* step, long long* blowup_step) {
 int lbm_get_state(lbm_ctx* ctx, double* f) {
     if (!ctx) return set_error(LBM_ESTATE, "context is NULL");
     if (!f) return set_error(LBM_EINVAL, "f is NULL");
+    note_capture(ctx);
     LBM_DISPATCH_PREC(ctx->prec, launch_get_p, ctx, f);
     return check_hip(hipGetLastError(), "get_state kernel launch");
 }
@@ -1359,6 +1366,7 @@ int lbm_set_state(lbm_ctx* ctx, const double* f, long long step) {
     if (!ctx) return set_error(LBM_ESTATE, "context is NULL");
     if (!f) return set_error(LBM_EINVAL, "f is NULL");
     if (step < 0 || step >= INT_MAX) return set_error(LBM_EINVAL, "step %lld out of range", step);
+    note_capture(ctx);
     LBM_DISPATCH_PREC(ctx->prec, launch_set_p, ctx, f);
     int rc = check_hip(hipGetLastError(), "set_state kernel launch");
     if (rc != LBM_OK) return rc;

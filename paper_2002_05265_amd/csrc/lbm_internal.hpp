@@ -325,6 +325,9 @@ int validate_model(int model, int eq_order);
 struct lbm_ctx;
 namespace lbm {
 int reset_blowup(lbm_ctx* ctx);     // blow-up record := none (kernel on the context's stream)
+// Called by every entry point that reads or writes the copy that holds the state: notes that a capture of the
+// context's stream is recording which copy that is (lbm_ctx::copy_recorded).
+void note_capture(lbm_ctx* ctx);
 int reduce_partials(lbm_ctx* ctx);  // d_tot[0..4] := sum over blocks of d_part (fixed order)
 // One launch of the walking kernel: `depth` steps src -> dst of the whole grid on segments of hs rows
 // (lbm_walk.hpp; depth 4, 6 or, in FP64 and FP32, 8 and, in FP16, 5).
@@ -366,6 +369,10 @@ struct lbm_ctx {
     double* d_static = nullptr;   // this device's address of the library's static reduction scratch
     double* d_wslots = nullptr;   // adjoint: per-block pending rate-gradient sums, 5 per block
     bool wslots_live = false;     // d_wslots holds pending sums
+    // A captured graph names the copy that held the state when it was recorded, and is replayed after eager runs of
+    // the same context.  From the first capture on lbm_step therefore leaves the state, eager or captured, in
+    // the copy that its strip launches would leave it in, whatever launches it takes.
+    bool copy_recorded = false;
     int adj_depth = 1;            // reverse steps per launch in lbm_adjoint_many (1 or 2)
 
     int rows[9] = {LBM_DEFAULT_ROWS, LBM_DEFAULT_ROWS, LBM_DEFAULT_ROWS, LBM_DEFAULT_ROWS,
