@@ -111,7 +111,8 @@ int lbm_batch_set_active(lbm_batch* b, const int* active);
 int lbm_batch_rebalance(lbm_batch* b);
 
 /* Launch shape of the persistent kernel: nodes per thread per tile (1, 2 or 4) and resident
- * workgroups per CU (1 .. the probed residency limit; 0 = that limit).  Takes effect at the next
+ * workgroups per CU (1 .. the probed residency limit; 0 = that limit, but at most 3 for the FP64
+ * one-step kernel and 4 for the FP32 three-step kernel, which run faster so).  Takes effect at the next
  * lbm_batch_run. */
 int lbm_batch_set_launch(lbm_batch* b, int nodes_per_thread, int groups_per_cu);
 

@@ -496,7 +496,7 @@ struct lbm_batch {
     int cus = 0, occ[5] = {0, 0, 0, 0, 0};     // CUs, occupancy limit per shape (runtime query)
     int res_fit[5] = {0, 0, 0, 0, 0};          // groups per CU the kernel's own resources allow
     int resident[5] = {0, 0, 0, 0, 0};         // groups per CU confirmed co-resident (0 = not probed)
-    int npt = 1, gpc = 0;              // launch shape (gpc 0 = occupancy limit)
+    int npt = 1, gpc = 0;              // launch shape (gpc 0 = default_groups)
     // fused passes over strips of hs rows (64: on the 512-instance FP64 sweep with three steps per
     // pass on 48-column strips 77-78 GLUPS against 75 with 32 rows, 69 with 16, 76-77 with 80-128)
     int fuse = 0, hs = 64;
@@ -824,10 +824,21 @@ int groups_limit(lbm_batch* b, int k) {
     return b->res_fit[k] > 0 ? std::min(b->res_fit[k], b->occ[k]) : b->occ[k];
 }
 
-int grid_size(lbm_batch* b, int k) {
+// Groups per CU of a launch of shape k when none were asked for: the limit, but no more than 3 in the FP64
+// one-step and 4 in the FP32 three-step kernel, whose registers allow 5.  More groups than that lose more at the
+// XCD's barrier and in its L2 than they hide.  Measured on MI355X (16 FP64 steps, one node per thread, 3 / 4 / 5
+// groups per CU): 16 of 128^2 344 / 398 / 485 us, 40 of 64^2 236 / 321 / 355, one 512^2 768 / 880 / 1018, 640 of
+// 60^2 1199 / 1333 / 1516; 24 FP32 steps, three per pass on strips of 16 rows, 4 / 5 groups: 16 of 128^2 248 / 265, one
+// 512^2 474 / 542, 640 of 60^2 661 / 646.
+int default_groups(lbm_batch* b, int k) {
     const int lim = groups_limit(b, k);
-    const int per = (b->gpc <= 0 || b->gpc > lim) ? lim : b->gpc;
-    return b->cus * per;
+    if (k < 3 && b->prec == LBM_F64) return std::min(lim, 3);
+    if (k == 4 && b->prec == LBM_F32_SHIFTED) return std::min(lim, 4);
+    return lim;
+}
+
+int grid_size(lbm_batch* b, int k) {
+    return b->cus * (b->gpc <= 0 ? default_groups(b, k) : std::min(b->gpc, groups_limit(b, k)));
 }
 
 // Reset the barrier counter, then one cooperative launch of the persistent kernel of shape k on
@@ -1458,7 +1469,7 @@ int lbm_batch_autotune(lbm_batch* b, int trials, int* nodes_per_thread, int* gro
         rc = check_hip(hipMemcpy(flags0.data(), b->d_blowup, sizeof(int) * flags0.size(), hipMemcpyDeviceToHost),
                        "copy blow-up steps");
     // candidates: one step per pass (1, 2, 4 nodes per thread), then two and (FP64, FP32) three
-    // steps per pass; each at the residency limit and at half of it; times per step
+    // steps per pass; each at its default number of groups and at half the residency limit; times per step
     const int nshapes = batch3_kernel_p(b->prec) ? 5 : 4;
     for (int k = 0; k < nshapes && rc == LBM_OK; ++k)
         for (int half = 0; half < 2 && rc == LBM_OK; ++half) {
@@ -1528,7 +1539,7 @@ int lbm_batch_autotune(lbm_batch* b, int trials, int* nodes_per_thread, int* gro
                        "restore blow-up steps");
     if (rc != LBM_OK) return rc;
     if (nodes_per_thread) *nodes_per_thread = best_npt;
-    if (groups_per_cu) *groups_per_cu = best_gpc == 0 ? b->resident[shape_of(b, best_fuse)] : best_gpc;
+    if (groups_per_cu) *groups_per_cu = best_gpc == 0 ? default_groups(b, shape_of(b, best_fuse)) : best_gpc;
     if (us_per_step) *us_per_step = 1e3 * (double)best / trials;
     return LBM_OK;
 }
