@@ -302,6 +302,11 @@ constexpr long long kWideMinStrips = 1024;
 // 2 (D - 1) iterations fill up the D steps, so lower segments take fewer: FP64 1152^2 (14 rows) 9.7 / 11.7
 // with six, 11.8 / 12.5 with four; 2048^2 (40 rows) 23.2 / 27.5 with six, 22.2 / 28.9 with eight; 4096^2
 // (152 rows) 89 / 103 with six; FP32 2600^2 (32 rows) 28.2 / 33.6 with six, 26.5 / 34.0 with eight.
+// On low and wide grids few segments fit beside each other, and slots stay empty or a second round is nearly so: in
+// FP32 and FP16, whose strip launches are bound by the ALU too, walking launches are left out where a slot walks
+// more than 1.85 times the rows per slot (K, us per step against strip launches: FP32 350000 x 40, 1.77 times, 76
+// against 80; FP16 200000 x 20, 1.72, 22.5 against 23.5; FP16 150000 x 40, 1.91, 40 against 36; FP32 125000 x 32, 2.64,
+// 33 against 26; in FP64 125000 x 16, 2.98, still 23 against 24).
 struct WalkPick {
     int rows, depth;
 };
@@ -315,11 +320,10 @@ WalkPick walk_pick(int nx, int ny, int prec, int cus) {
     if (per_slot < (prec == LBM_F64 ? 9.5 : 14.5) || 3 * sx * W > 4LL * nx) return {0, 0};
     const long long segments = std::max(1LL, slots / sx);
     const int hs = (int)((ny + segments - 1) / segments + 1) / 2 * 2;
-    switch (prec) {
-        case LBM_F64: return {hs, hs < 48 ? 6 : 8};
-        case LBM_F32_SHIFTED: return {hs, hs < 28 ? 6 : 8};
-        default: return {hs, 6};
-    }
+    const int depth = prec == LBM_F16_SHIFTED || hs < (prec == LBM_F64 ? 48 : 28) ? 6 : 8;
+    const long long rounds = (sx * ((ny + hs - 1) / hs) + slots - 1) / slots;
+    if (prec != LBM_F64 && (double)(rounds * (hs + 2 * (depth - 1))) > 1.85 * per_slot) return {0, 0};
+    return {hs, depth};
 }
 
 // Tile launches (lbm_tile_kernel.hpp) of a new context: the patch and the steps per launch with the least
@@ -329,6 +333,10 @@ WalkPick walk_pick(int nx, int ny, int prec, int cus) {
 // 44 in FP64 fills a CU's LDS, and one patch at a time hides no latency (768^2: 6.0 us per step, 32: 4.9).
 // patch = 0 where strips stay: grids of more than 2^22 nodes (FP32 4096^2: strips 5.5 us per million nodes,
 // tiles 4.8 / 5.4 at 1700^2) and grids of fewer than 16 nodes a side that need more than one patch per CU.
+// They also stay in FP32 and FP16 on grids of at most 32 nodes a side whose patches come to more than 1.5 times the
+// grid's nodes and to more than 8 per CU (K, us per step against strip launches: FP16 150000 x 20, 1.83 times and 21
+// per CU, 20.2 against 19.6, FP32 21.1 against 20.4, FP32 166666 x 24, 1.52 and 24, 28.9 against 28.1; FP32 31250 x 16,
+// 1.68 and 7, 4.6 against 4.7; 83333 x 48, 1.52 and 24, 30.5 against 31.2).
 struct TilePick {
     int patch, steps;
 };
@@ -352,6 +360,11 @@ TilePick tile_pick(int nx, int ny, int prec, int cus) {
                 pick = {pw, t};
             }
         }
+    if (pick.patch && prec != LBM_F64 && std::min(nx, ny) <= 32) {
+        const int tw = pick.patch - 2 * (pick.steps - 1);
+        const long long tiles = (long long)((nx + tw - 1) / tw) * ((ny + tw - 1) / tw);
+        if (tiles > 8LL * cus && (double)tiles * pick.patch * pick.patch > 1.5 * (double)nx * ny) return {0, 0};
+    }
     return pick;
 }
 
