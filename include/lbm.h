@@ -227,7 +227,8 @@ int lbm_get_walk(lbm_ctx* ctx, int model, int* steps, int* rows);
  * 2^22 nodes that the walking launches do not take (on grids lower or narrower than 16 nodes while one
  * patch per CU is enough, and in FP32 and FP16 lower or narrower than 33 while the patches number at most 8 per CU
  * or come to at most 1.5 times the grid); lbm_step then splits two steps and more into as few launches as there can be, of
- * nearly equal numbers of steps.  lbm_set_fusion and lbm_set_fusion_depth turn them off for the model,
+ * nearly equal numbers of steps (a run of two, or in FP32 three, that one strip launch takes in even rounds of
+ * workgroups goes to that launch).  lbm_set_fusion and lbm_set_fusion_depth turn them off for the model,
  * lbm_autotune keeps them where they are the fastest.  Bit-identical to single steps.  *steps = *patch = 0
  * when off; host pointers, each may be NULL. */
 int lbm_get_tile(lbm_ctx* ctx, int model, int* steps, int* patch);

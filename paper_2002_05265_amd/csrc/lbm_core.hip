@@ -914,6 +914,24 @@ int strip_launches(const lbm_ctx* ctx, int model, int n) {
     return (n + most - 1) / most;
 }
 
+// Whether a run of n steps on a tile context goes to the strips all the same: two steps, or three in FP32, on a
+// context that runs three per launch, where one launch takes them all and its strips fill the last round of one per
+// CU to 15/16, in as many rounds as steps at most.  One tile launch has little to save then, and recomputes more.  Measured on
+// MI355X (us per call, K, tile against strips): two steps FP64 512^2 (512 strips) 10.8 against 9.1, 2048 x 128 (512)
+// 11.9 against 9.0, 520 x 512 (576) 10.5 against 13.5, FP32 512^2 7.8 against 7.3, 768 x 340 (516) 8.1 against 8.2;
+// 768 x 512 (768)
+// 8.3 against 9.5; three steps FP32 512^2 9.5 against 9.2, 768 x 512 12.9 against 11.1, 520 x 512 9.5 against 10.6, FP64
+// 512^2 13.0 against 13.6; four steps 15.5 against 27.5 and 11.5 against 19.0.
+bool short_run(const lbm_ctx* ctx, int model, int n) {
+    const int k = lbm_ctx::slot(model);
+    if (n > (ctx->prec == LBM_F32_SHIFTED ? 3 : 2) || ctx->fuse_depth[k] != 3 || !(strip_pieces(ctx, model) >> n & 1))
+        return false;
+    const int hs = n == 2 && ctx->tail_ring[k] > 0 ? ctx->tail_strip[k] : ctx->fuse_strip[k];
+    const long long strips = (long long)((ctx->nx + 63) / 64) * ((ctx->ny + hs - 1) / hs);
+    const long long rounds = (strips + ctx->cus - 1) / ctx->cus;
+    return rounds <= n && 16 * (rounds * ctx->cus - strips) <= ctx->cus;
+}
+
 // `nsteps` steps of the whole grid in one tile launch src -> dst from step `step`.
 void launch_tile(lbm_ctx* ctx, int model, const double* w, int nsteps, const void* src, void* dst, int step,
                  const TileKeep* keep = nullptr) {
@@ -1086,6 +1104,7 @@ int lbm_init_shifted(lbm_ctx** out, int nx, int ny, int prec, int eq_order, doub
             ctx->fuse_ring[k] = t.ring;
             ctx->fuse_strip[k] = t.strip;
         }
+    ctx->cus = std::max(cus, 1);
     const WalkPick walk = walk_pick(nx, ny, prec, cus);
     ctx->walk_rows = walk.rows;
     const TilePick tile = tile_pick(nx, ny, prec, cus);
@@ -1125,7 +1144,7 @@ int lbm_step(lbm_ctx* ctx, int model, const double* omega, int nsteps) {
     if (ctx->step + nsteps >= INT_MAX) return set_error(LBM_EINVAL, "step counter would overflow");
     note_capture(ctx);
     const int depth = ctx->walk_depth[lbm_ctx::slot(model)], tile = ctx->tile_steps[lbm_ctx::slot(model)];
-    if ((!depth && !tile) || nsteps < 2) {
+    if ((!depth && !tile) || nsteps < 2 || (tile && short_run(ctx, model, nsteps))) {
         step_strips(ctx, model, omega, nsteps);
         return check_hip(hipGetLastError(), "step kernel launch");
     }

@@ -351,6 +351,7 @@ void launch_tile_f16(lbm_ctx* ctx, int model, const double* w, int nsteps, const
 
 struct lbm_ctx {
     int nx = 0, ny = 0, prec = 0, eq_order = 4;
+    int cus = 1;                  // CUs of the device
     lbm::Ref<double> ref{};                // storage reference: h_i = f_i - f^eq_N(rho_s, U)_i
     lbm::Pop9 fref{};                      // the reference populations
     char* buf = nullptr;          // caller-owned population buffer (two copies)

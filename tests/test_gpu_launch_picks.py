@@ -1,5 +1,6 @@
 """Where walking and tile launches lose against strip launches a new context does not take them: low and wide grids
-in FP32 and FP16 (their waves or patches fill the device badly).  States are bit-identical to single steps whichever launches run; the picks are compared with
+in FP32 and FP16 (their waves or patches fill the device badly), and runs of two or three steps that one strip launch
+takes in even rounds.  States are bit-identical to single steps whichever launches run; the picks are compared with
 the strips' time (set_fusion_depth turns the others off), at most 12% slower where the launches left out were
 20-38% slower and runs differ by 2%."""
 import pytest
@@ -32,7 +33,8 @@ def us(s, model, n):
 
 
 @pytest.mark.parametrize("prec,nx,ny,n", [("f32", 125000, 32, 12), ("f16", 125000, 32, 12), ("f16", 160000, 24, 12),
-                                          ("f16", 160000, 20, 12)])
+                                          ("f16", 160000, 20, 12), ("f32", 2048, 128, 2), ("f32", 2048, 128, 3),
+                                          ("f64", 2048, 128, 2), ("f32", 768, 512, 3)])
 def test_no_slower_than_strips(gpu, prec, nx, ny, n):
     s, t = sim(gpu, prec, nx, ny, "K"), sim(gpu, prec, nx, ny, "K")
     t.set_fusion("K", 0)
