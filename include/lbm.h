@@ -161,7 +161,9 @@ int lbm_set_state(lbm_ctx* ctx, const double* f, long long step);
  *   rows  nodes per thread along y: 1, 2 or 4
  *   xcd   0 = hardware block order, 1 = blocks renumbered so that each of the eight XCDs
  *         owns one contiguous band of tiles
- * Results do not depend on the shape (every node is computed by the same arithmetic). */
+ * Turns walking and tile launches (lbm_get_walk, lbm_get_tile) off for the model, so that the shape takes every
+ * step that the model's fused launches (lbm_get_fusion) do not.  Results do not depend on the shape (every node is
+ * computed by the same arithmetic). */
 int lbm_set_launch(lbm_ctx* ctx, int model, int rows, int xcd);
 
 /* Two steps per pass over memory (temporal blocking) for one model (model code, or
@@ -216,8 +218,8 @@ int lbm_get_fusion_depth(lbm_ctx* ctx, int model, int* steps);
  * on grids so low that its waves walk more than 1.85 times their share of the rows);
  * lbm_step then splits its steps into such launches of at most *steps steps and, for what they
  * do not fill, the launches that lbm_get_fusion and lbm_get_fusion_depth describe.
- * lbm_set_fusion and lbm_set_fusion_depth turn them off for the model, lbm_autotune keeps them where
- * they are the fastest.  Bit-identical to single steps.  *steps = *rows = 0 when off; host pointers,
+ * lbm_set_launch, lbm_set_fusion and lbm_set_fusion_depth turn them off for the model, lbm_autotune keeps them
+ * where they are the fastest.  Bit-identical to single steps.  *steps = *rows = 0 when off; host pointers,
  * each may be NULL. */
 int lbm_get_walk(lbm_ctx* ctx, int model, int* steps, int* rows);
 
@@ -228,8 +230,8 @@ int lbm_get_walk(lbm_ctx* ctx, int model, int* steps, int* rows);
  * patch per CU is enough, and in FP32 and FP16 lower or narrower than 33 while the patches number at most 8 per CU
  * or come to at most 1.5 times the grid); lbm_step then splits two steps and more into as few launches as there can be, of
  * nearly equal numbers of steps (a run of two, or in FP32 three, that one strip launch takes in even rounds of
- * workgroups goes to that launch).  lbm_set_fusion and lbm_set_fusion_depth turn them off for the model,
- * lbm_autotune keeps them where they are the fastest.  Bit-identical to single steps.  *steps = *patch = 0
+ * workgroups goes to that launch).  lbm_set_launch, lbm_set_fusion and lbm_set_fusion_depth turn them off for
+ * the model, lbm_autotune keeps them where they are the fastest.  Bit-identical to single steps.  *steps = *patch = 0
  * when off; host pointers, each may be NULL. */
 int lbm_get_tile(lbm_ctx* ctx, int model, int* steps, int* patch);
 

@@ -1414,6 +1414,8 @@ int lbm_set_launch(lbm_ctx* ctx, int model, int rows, int xcd) {
     if (xcd != 0 && xcd != 1) return set_error(LBM_EINVAL, "xcd %d not in {0,1}", xcd);
     ctx->rows[lbm_ctx::slot(model)] = rows;
     ctx->xcd[lbm_ctx::slot(model)] = xcd;
+    ctx->walk_depth[lbm_ctx::slot(model)] = 0;
+    ctx->tile_steps[lbm_ctx::slot(model)] = 0;
     return LBM_OK;
 }
 
