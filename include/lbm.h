@@ -240,8 +240,10 @@ int lbm_get_tile(lbm_ctx* ctx, int model, int* steps, int* patch);
  * {(8, 8), (8, 16), (8, 40), (8, 64), (16, 16), (4, 16), (4, 20), (4, 64)} and, except for FP16,
  * the three-step shapes {(4, 8), (4, 16), (4, 32), (4, 64), (8, 8), (8, 16), (8, 24), (8, 32),
  * (8, 64), (8, 80), (8, 96), (8, 128)} and, where a new context may take them, the walking and tile
- * launches (lbm_get_walk, lbm_get_tile) are timed with HIP events over `trials` (>= 1) launches that recompute from the same input copy, so the state, the
- * step counter and the blow-up record are unchanged.  The fastest single-step shape is kept (it
+ * launches (lbm_get_walk, lbm_get_tile) are timed with HIP events over `trials` (>= 1) launches.  The state, the step
+ * counter and the blow-up record are unchanged: launches on a state of up to 256 MiB, which may stay in the
+ * last-level cache, each read what the one before wrote, as in a run, and the state is kept in device memory
+ * allocated for the call and put back; on larger ones, or without that memory, all recompute from the same copy.  The fastest single-step shape is kept (it
  * also takes the last steps that do not fill a fused launch) and returned through rows_out /
  * xcd_out; the fastest fused shape per step is kept (lbm_get_fusion, lbm_get_fusion_depth) when it
  * beats it, and fusion is switched off otherwise; walking or tile launches are

@@ -973,6 +973,9 @@ void step_strips(lbm_ctx* ctx, int model, const double* omega, int nsteps) {
     }
 }
 
+// States of at most this many bytes may stay in the last-level cache (256 MB) from one launch to the next.
+constexpr size_t kCachedState = (size_t)256 << 20;
+
 __global__ void k_fill_int(int* __restrict__ p, int n, int v) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -1505,11 +1508,35 @@ int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* 
     hipEvent_t e0 = nullptr, e1 = nullptr;
     rc = check_hip(hipEventCreate(&e0), "hipEventCreate");
     if (rc == LBM_OK) rc = check_hip(hipEventCreate(&e1), "hipEventCreate");
-    // times `trials` launches of `launch` after one untimed one; milliseconds
+    // On a state that may stay in the last-level cache every launch reads what the launch before it wrote, as in a
+    // run, and the state is kept aside and put back: launches that all read one copy find it there and never wait
+    // for the writes, which favours the shapes that move the most bytes (FP16 2048^2 BGK: two steps per launch were
+    // picked at 16.4 us per step and then ran at 23.7, walking launches run at 16.8; FP32 1024^2 BGK 5.9 and 7.8
+    // against tile launches at 6.1).  Larger states, and those that there is no memory left to keep, are reread.
+    void* aside = nullptr;
+    const size_t state_bytes = (size_t)9 * (size_t)ctx->plane * ctx->esize;
+    if (rc == LBM_OK && state_bytes <= kCachedState && hipMalloc(&aside, state_bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        aside = nullptr;
+    }
+    if (rc == LBM_OK && aside)
+        rc = check_hip(hipMemcpyAsync(aside, ctx->copy(ctx->cur), state_bytes, hipMemcpyDeviceToDevice, ctx->stream),
+                       "keep state");
+    auto put_back = [&] {
+        return check_hip(hipMemcpyAsync(ctx->copy(ctx->cur), aside, state_bytes, hipMemcpyDeviceToDevice, ctx->stream),
+                         "put state back");
+    };
+    // times `trials` launches of `launch`, which reads the copy it is given, after one untimed one; milliseconds
     auto timed = [&](auto&& launch) -> float {
-        launch();
+        int from = ctx->cur;
+        if (rc == LBM_OK && aside) rc = put_back();
+        auto next = [&] {
+            launch(from);
+            if (aside) from ^= 1;
+        };
+        if (rc == LBM_OK) next();
         if (rc == LBM_OK) rc = check_hip(hipEventRecord(e0, ctx->stream), "hipEventRecord");
-        for (int t = 0; t < trials && rc == LBM_OK; ++t) launch();
+        for (int t = 0; t < trials && rc == LBM_OK; ++t) next();
         if (rc == LBM_OK) rc = check_hip(hipGetLastError(), "autotune launch");
         if (rc == LBM_OK) rc = check_hip(hipEventRecord(e1, ctx->stream), "hipEventRecord");
         if (rc == LBM_OK) rc = check_hip(hipEventSynchronize(e1), "hipEventSynchronize");
@@ -1517,14 +1544,14 @@ int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* 
         if (rc == LBM_OK) rc = check_hip(hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime");
         return ms;
     };
-    // every launch recomputes from copy `cur` into the other copy: state and counter unchanged
+    // the counter is not advanced, and the state is unchanged or put back
     const int rows_c[3] = {1, 2, 4};
     float best = 0.f;
     int best_rows = ctx->rows[lbm_ctx::slot(model)], best_xcd = ctx->xcd[lbm_ctx::slot(model)];
     for (int ri = 0; ri < 3 && rc == LBM_OK; ++ri)
         for (int xi = 0; xi < 2 && rc == LBM_OK; ++xi) {
             const StepShape sh = step_shape(ctx->nx, ctx->ny, rows_c[ri], xi);
-            const float ms = timed([&] { LBM_DISPATCH_PREC(ctx->prec, launch_step_p, ctx, model, omega, sh, ctx->cur); });
+            const float ms = timed([&](int from) { LBM_DISPATCH_PREC(ctx->prec, launch_step_p, ctx, model, omega, sh, from); });
             if (rc == LBM_OK && (best == 0.f || ms < best)) {
                 best = ms;
                 best_rows = rows_c[ri];
@@ -1539,7 +1566,7 @@ int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* 
     int tail_ring = 0, tail_strip = 0;
     for (int k = 0; k < 8 && rc == LBM_OK; ++k) {
         const int ring = fuse_c[k][0], hs = fuse_c[k][1];
-        const float ms = 0.5f * timed([&] { LBM_DISPATCH_PREC(ctx->prec, launch_step2_p, ctx, model, omega, ring, hs, ctx->cur); });
+        const float ms = 0.5f * timed([&](int from) { LBM_DISPATCH_PREC(ctx->prec, launch_step2_p, ctx, model, omega, ring, hs, from); });
         if (rc == LBM_OK && ms < best) {
             best = ms;
             best_ring = ring;
@@ -1556,9 +1583,9 @@ int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* 
                                {8, 64}, {8, 80}, {8, 96}, {8, 128}};
     for (int k = 0; k < 12 && rc == LBM_OK && ctx->prec != LBM_F16_SHIFTED && ctx->nx >= 2 && ctx->ny >= 2; ++k) {
         const int ring = deep_c[k][0], hs = deep_c[k][1];
-        const float ms = timed([&] {
-            LBM_DISPATCH_PREC(ctx->prec, launch_step3_p, ctx, model, omega, ring, hs, ctx->copy(ctx->cur),
-                              ctx->copy(ctx->cur ^ 1), (int)ctx->step);
+        const float ms = timed([&](int from) {
+            LBM_DISPATCH_PREC(ctx->prec, launch_step3_p, ctx, model, omega, ring, hs, ctx->copy(from),
+                              ctx->copy(from ^ 1), (int)ctx->step);
         }) / 3.f;
         if (rc == LBM_OK && ms < best) {
             best = ms;
@@ -1569,9 +1596,11 @@ int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* 
     }
     // walking launches, per step, on the grids where a new context may take them
     int best_walk = 0;
-    for (int depth = 4; depth <= 8 && rc == LBM_OK && ctx->walk_rows > 0; depth += 2) {
-        if (depth == 8 && ctx->prec == LBM_F16_SHIFTED) continue;
-        const float ms = timed([&] { launch_walk(ctx, model, omega, depth, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1), (int)ctx->step); }) / (float)depth;
+    for (int depth = 4; depth <= 8 && rc == LBM_OK && ctx->walk_rows > 0; ++depth) {
+        if (ctx->prec == LBM_F16_SHIFTED ? depth > 6 : depth & 1) continue;  // the depths that exist
+        const float ms = timed([&](int from) {
+            launch_walk(ctx, model, omega, depth, ctx->copy(from), ctx->copy(from ^ 1), (int)ctx->step);
+        }) / (float)depth;
         if (rc == LBM_OK && ms < best) {
             best = ms;
             best_walk = depth;
@@ -1581,7 +1610,9 @@ int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* 
     int best_tile = 0;
     if (rc == LBM_OK && ctx->tile_patch > 0) {
         const int most = ctx->tile_most;
-        const float ms = timed([&] { launch_tile(ctx, model, omega, most, ctx->copy(ctx->cur), ctx->copy(ctx->cur ^ 1), (int)ctx->step); }) / (float)most;
+        const float ms = timed([&](int from) {
+            launch_tile(ctx, model, omega, most, ctx->copy(from), ctx->copy(from ^ 1), (int)ctx->step);
+        }) / (float)most;
         if (rc == LBM_OK && ms < best) {
             best = ms;
             best_tile = most;
@@ -1590,6 +1621,12 @@ int lbm_autotune(lbm_ctx* ctx, int model, const double* omega, int trials, int* 
     }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
+    if (aside) {  // also after an error
+        const int put = put_back();
+        (void)hipStreamSynchronize(ctx->stream);
+        (void)hipFree(aside);
+        if (rc == LBM_OK) rc = put;
+    }
     if (rc == LBM_OK)
         rc = check_hip(hipMemcpyAsync(ctx->d_flag, &flag0, sizeof(int), hipMemcpyHostToDevice, ctx->stream),
                        "hipMemcpyAsync(flag)");
