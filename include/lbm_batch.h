@@ -154,7 +154,7 @@ int lbm_batch_get_fusion_depth(lbm_batch* b, int* steps);
  * LBM_EUNSUPPORTED for other batches.  lbm_batch_autotune picks between them.  Bit-identical to single steps,
  * blow-up steps included; a blown-up instance stops at the end of the walking pass containing its step, and
  * one step after it in resident passes.  Neither kind needs a probe before a stream capture, but the single
- * steps after walking passes do. */
+ * steps after walking passes do.  Choosing kind 1 synchronises the stream if its tasks have to be dealt. */
 int lbm_batch_set_pass(lbm_batch* b, int kind);
 
 /* The kind of pass and, for walking passes, the most steps of one (0 for the others); host pointers, each

@@ -515,8 +515,9 @@ struct lbm_batch {
     // most walk_depth steps, 2 resident (lbm_batch_resident.hpp)
     int pass = 0, walk_depth = 0;
     int most_cells = 0;                // nodes of the largest instance
-    WalkTask* d_tasks = nullptr;       // tasks of the live instances (nullptr: no walking passes), j < 0 past them
+    WalkTask* d_tasks = nullptr;       // tasks of the live instances (nullptr: not dealt yet), j < 0 past them
     int ntasks = 0;                    // entries of d_tasks
+    bool tasks_old = true;             // instances may have dropped out since d_tasks was dealt
     int* d_blowup = nullptr;
     int* d_active = nullptr;           // per instance: nonzero = advanced by lbm_batch_run
     int* d_retired = nullptr;          // per instance: step at which it was retired (INT_MAX)
@@ -667,6 +668,10 @@ bool walk_takes(const lbm_instance_desc& d) {
     return d.ny >= kWalkHalo && (d.nx % 2 == 0 || d.nx >= 64 * walk_cols<kF64>());
 }
 
+bool walk_takes_all(const lbm_batch* b) {
+    return std::all_of(b->hdesc.begin(), b->hdesc.end(), walk_takes);
+}
+
 // Time of a row of a walking task by model, BGK = 1 (a grid of 1400^2 in FP64, 10.9 to 13.5 us per step).
 constexpr double kWalkRow[8] = {1.0, 1.065, 1.077, 1.137, 1.166, 1.24, 1.05, 1.12};
 
@@ -699,10 +704,9 @@ long long walk_tasks(const lbm_batch* b, const std::vector<int>& live, int heigh
 // Cut the live instances into tasks for the device's wave slots (one per SIMD in FP64, two in FP32 and FP16):
 // the height with the shortest pass, which lasts as long as its longest task, and where there are more
 // tasks than slots up to as long as all of them over the slots on top.  The table keeps its size (d_tasks null: it is allocated for these tasks), so that a captured pass
-// stays valid when the instances are dealt anew.  Synchronous.
+// stays valid when the instances are dealt anew.  Dealt when walking passes are chosen, and anew with the persistent
+// passes' lists while they are (20-30 us of a batch's creation and of each rebalance otherwise).  Synchronous.
 int deal_tasks(lbm_batch* b, const std::vector<char>& is_live) {
-    for (const lbm_instance_desc& d : b->hdesc)
-        if (!walk_takes(d)) return LBM_OK;
     std::vector<int> live;
     for (int j = 0; j < b->n; ++j)
         if (is_live[j]) live.push_back(j);
@@ -729,7 +733,7 @@ int deal_tasks(lbm_batch* b, const std::vector<char>& is_live) {
     int rc = LBM_OK;
     if (!b->d_tasks) {
         const long long entries = std::max(slots, (long long)tasks.size());
-        if (entries >= INT_MAX) return LBM_OK;
+        if (entries >= INT_MAX) return set_error(LBM_EUNSUPPORTED, "too many walking tasks");
         rc = check_hip(hipMalloc(&b->d_tasks, sizeof(WalkTask) * (size_t)entries), "hipMalloc(tasks)");
         if (rc == LBM_OK) b->ntasks = (int)entries;
     }
@@ -737,6 +741,7 @@ int deal_tasks(lbm_batch* b, const std::vector<char>& is_live) {
     if (rc == LBM_OK)
         rc = check_hip(hipMemcpy(b->d_tasks, tasks.data(), sizeof(WalkTask) * tasks.size(), hipMemcpyHostToDevice),
                        "copy tasks");
+    b->tasks_old = rc != LBM_OK;
     return rc;
 }
 
@@ -785,7 +790,8 @@ int deal_tables(lbm_batch* b, const std::vector<char>& live) {
                            "copy xtab");
         if (rc != LBM_OK) return rc;
     }
-    return deal_tasks(b, live);
+    b->tasks_old = true;
+    return b->pass == 1 ? deal_tasks(b, live) : LBM_OK;
 }
 
 int shape_of(const lbm_batch* b, bool fused) { return fused ? (b->depth == 3 ? 4 : 3) : npt_index(b->npt); }
@@ -1004,6 +1010,14 @@ int live_set(lbm_batch* b, std::vector<char>& live) {
     live.assign((size_t)b->n, 0);
     for (int j = 0; j < b->n; ++j) live[j] = blow[j] == INT_MAX && ret[j] == INT_MAX;
     return LBM_OK;
+}
+
+// The tasks of the instances that are live now.  Synchronous if they have to be dealt.
+int current_tasks(lbm_batch* b) {
+    if (b->d_tasks && !b->tasks_old) return LBM_OK;
+    std::vector<char> live;
+    const int rc = live_set(b, live);
+    return rc != LBM_OK ? rc : deal_tasks(b, live);
 }
 
 // (Re)allocate strip table k to hold `total` strips.
@@ -1412,8 +1426,12 @@ int lbm_batch_set_fusion_depth(lbm_batch* b, int steps) {
 int lbm_batch_set_pass(lbm_batch* b, int kind) {
     if (!b) return set_error(LBM_ESTATE, "batch is NULL");
     if (kind < 0 || kind > 2) return set_error(LBM_EINVAL, "kind of pass %d not in 0..2", kind);
-    if (kind == 1 && !b->d_tasks)
-        return set_error(LBM_EUNSUPPORTED, "an instance is too low, or narrow and of odd width, for walking passes");
+    if (kind == 1) {
+        if (!walk_takes_all(b))
+            return set_error(LBM_EUNSUPPORTED, "an instance is too low, or narrow and of odd width, for walking passes");
+        const int rc = current_tasks(b);
+        if (rc != LBM_OK) return rc;
+    }
     if (kind == 2 && !resident_takes(b))
         return set_error(LBM_EUNSUPPORTED, "an instance of %d nodes is too large for resident passes", b->most_cells);
     b->pass = kind;
@@ -1468,6 +1486,12 @@ int lbm_batch_autotune(lbm_batch* b, int trials, int* nodes_per_thread, int* gro
     if (rc == LBM_OK)
         rc = check_hip(hipMemcpy(flags0.data(), b->d_blowup, sizeof(int) * flags0.size(), hipMemcpyDeviceToHost),
                        "copy blow-up steps");
+    bool walks = false;  // dealt before any pass is timed: the records must be those of the true step
+    if (rc == LBM_OK && walk_takes_all(b)) {
+        const int dealt = current_tasks(b);
+        walks = dealt == LBM_OK;
+        if (!walks && dealt != LBM_EUNSUPPORTED) rc = dealt;
+    }
     // candidates: one step per pass (1, 2, 4 nodes per thread), then two and (FP64, FP32) three
     // steps per pass; each at its default number of groups and at half the residency limit; times per step
     const int nshapes = batch3_kernel_p(b->prec) ? 5 : 4;
@@ -1519,7 +1543,7 @@ int lbm_batch_autotune(lbm_batch* b, int trials, int* nodes_per_thread, int* gro
             if (depth) best_walk = depth;
         }
     };
-    if (b->d_tasks)
+    if (walks)
         for (int depth : {5, 7})
             if (depth == 5 || b->prec != LBM_F16_SHIFTED)
                 timed(depth, 1, depth, [&](int k) { for (; k > 0; --k) walk_pass(b, depth, 0, 0); });
