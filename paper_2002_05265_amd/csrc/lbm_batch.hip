@@ -911,19 +911,29 @@ int ensure_resident(lbm_batch* b, int k) {
     return set_error(LBM_EHIP, "no persistent grid of this shape stays co-resident");
 }
 
+int capture_status(lbm_batch* b, bool& capturing) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const int rc = check_hip(hipStreamIsCapturing(b->stream, &cap), "hipStreamIsCapturing");
+    capturing = cap != hipStreamCaptureStatusNone;
+    return rc;
+}
+
+// Whether launches of shape k can be made: the residency probe synchronises, so it cannot run inside a
+// stream capture.
+int ready_units(lbm_batch* b, int k, bool capturing) {
+    if (capturing && b->resident[k] == 0)
+        return set_error(LBM_ESTATE, "launch shape not probed yet: run (or autotune) the batch once with the "
+                                     "same settings before capturing it");
+    return ensure_resident(b, k);
+}
+
 // Advance every live instance by `units` steps (k < 3), pairs (k = 3) or triples (k = 4), in
 // launches short enough that the barrier counter G * units stays below 2^31.
 int run_units(lbm_batch* b, int k, int units) {
     if (units <= 0) return LBM_OK;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    int rc = check_hip(hipStreamIsCapturing(b->stream, &cap), "hipStreamIsCapturing");
-    if (rc != LBM_OK) return rc;
-    const bool capturing = cap != hipStreamCaptureStatusNone;
-    // the residency probe synchronises: it cannot run inside a stream capture
-    if (capturing && b->resident[k] == 0)
-        return set_error(LBM_ESTATE, "launch shape not probed yet: run (or autotune) the batch once with the "
-                                     "same settings before capturing it");
-    rc = ensure_resident(b, k);
+    bool capturing = false;
+    int rc = capture_status(b, capturing);
+    if (rc == LBM_OK) rc = ready_units(b, k, capturing);
     if (rc != LBM_OK) return rc;
     const long long G = grid_size(b, k);
     const int chunk = (int)std::min<long long>(units, (1LL << 31) / G);
@@ -979,10 +989,17 @@ int next_walk(int depth, int left) {
 // Advance every live instance by nsteps steps by ordinary launches.  The kernels take the step from the
 // device counter, which a launch of its own advances at the end, so that a captured run can be replayed.
 int run_passes(lbm_batch* b, int nsteps) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    int rc = check_hip(hipStreamIsCapturing(b->stream, &cap), "hipStreamIsCapturing");
+    bool capturing = false;
+    int rc = capture_status(b, capturing);
     if (rc != LBM_OK) return rc;
     int done = 0;
+    if (b->pass == 1) {
+        // the single steps that the passes leave over are made sure of before the first pass advances anything
+        int left = nsteps;
+        for (int d; (d = next_walk(b->walk_depth, left)) > 0;) left -= d;
+        if (left > 0) rc = ready_units(b, npt_index(b->npt), capturing);
+        if (rc != LBM_OK) return rc;
+    }
     if (b->pass == 2) {
         resident_pass(b, nsteps, 1);
         done = nsteps;
@@ -992,7 +1009,7 @@ int run_passes(lbm_batch* b, int nsteps) {
     if (done > 0) hipLaunchKernelGGL(k_step_add, dim3(1), dim3(64), 0, b->stream, b->d_step, done);
     rc = check_hip(hipGetLastError(), "batch pass launch");
     if (rc != LBM_OK) return rc;
-    if (cap == hipStreamCaptureStatusNone) b->step += done;
+    if (!capturing) b->step += done;
     return run_units(b, npt_index(b->npt), nsteps - done);
 }
 
