@@ -26,10 +26,10 @@
 namespace lbm {
 namespace {
 
+// src and dst are the same memory in a run of an even number of steps, so neither is declared restrict.
 template <int MODEL, int PREC, int NT, int NPT, int CAP>
 __device__ __forceinline__ void resident_steps(typename Store<PREC>::S (&lds)[8][CAP], int& stop,
-                                               const typename Store<PREC>::S* __restrict__ src,
-                                               typename Store<PREC>::S* __restrict__ dst,
+                                               const typename Store<PREC>::S* src, typename Store<PREC>::S* dst,
                                                const BDesc<typename Store<PREC>::R>& d, int n, int nsteps,
                                                int* __restrict__ blowup) {
     using S = typename Store<PREC>::S;
