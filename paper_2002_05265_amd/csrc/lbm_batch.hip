@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <climits>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "lbm.h"
@@ -1032,9 +1033,13 @@ int live_set(lbm_batch* b, std::vector<char>& live) {
 // The tasks of the instances that are live now.  Synchronous if they have to be dealt.
 int current_tasks(lbm_batch* b) {
     if (b->d_tasks && !b->tasks_old) return LBM_OK;
-    std::vector<char> live;
-    const int rc = live_set(b, live);
-    return rc != LBM_OK ? rc : deal_tasks(b, live);
+    try {
+        std::vector<char> live;
+        const int rc = live_set(b, live);
+        return rc != LBM_OK ? rc : deal_tasks(b, live);
+    } catch (const std::bad_alloc&) {  // must not leave through the C interface
+        return set_error(LBM_ESTATE, "out of host memory");
+    }
 }
 
 // (Re)allocate strip table k to hold `total` strips.

@@ -17,10 +17,11 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <string>
 #include <type_traits>
-#include <vector>
 
 #include "lbm.h"
 #include "lbm_cell.hpp"
@@ -1279,15 +1280,19 @@ int lbm_step_raw_chain(lbm_ctx* ctx, int model, const double* omega, const void*
     if (!depth && !tile)
         return set_error(LBM_EUNSUPPORTED, "model %d takes neither walking nor tile launches on this context", model);
     void* scratch[2] = {tmp ? tmp[0] : nullptr, tmp ? tmp[1] : nullptr};
-    std::vector<const void*> all{src};
+    const std::unique_ptr<const void*[]> all(new (std::nothrow) const void*[(size_t)count + 3]);
+    if (!all) return set_error(LBM_ESTATE, "out of host memory");
+    const void** end = all.get();
+    *end++ = src;
     for (int k = 0; k < count; ++k)
-        if (dst[k]) all.push_back(dst[k]);
-    if (all.size() <= (size_t)count) {  // some states are not kept
+        if (dst[k]) *end++ = dst[k];
+    if (end - all.get() <= count) {  // some states are not kept
         if (!scratch[0] || !scratch[1]) return set_error(LBM_EINVAL, "states that are not kept need two scratch states");
-        all.insert(all.end(), scratch, scratch + 2);
+        *end++ = scratch[0];
+        *end++ = scratch[1];
     }
-    std::sort(all.begin(), all.end());
-    if (std::adjacent_find(all.begin(), all.end()) != all.end())
+    std::sort(all.get(), end);
+    if (std::adjacent_find(all.get(), end) != end)
         return set_error(LBM_EINVAL, "the states of a chain must be distinct");
     const unsigned pieces = strip_pieces(ctx, model);
     const StepShape sh = ctx->shape_of(model);
