@@ -370,10 +370,15 @@ TilePick tile_pick(int nx, int ny, int prec, int cus) {
 }
 
 // The launches of a run of n <= kPlanMax steps: plan[i] steps in launch i, their number returned.  Walking
-// launches of the depths that exist (4, 6 and 8; 4, 5 and 6 in FP16) up to `depth` (5 in FP16 also for 4), and strip launches of
-// one step and of those of 2 and 3 that `pieces` (bit d: d steps) has, at the least total of kCost, the time of a
-// launch of d steps at 4096^2 (in 50 us in FP64, in 10 us in FP16; FP32 lies between FP64 and FP16); with
-// parity 0 or 1 among the splits into an even or odd number of launches only.
+// launches of the depths that exist (4, 6 and 8; 4, 5 and 6 in FP16) up to `depth` (5 in FP16 also for 4), and strip
+// launches of one step and of those of 2 and 3 that `pieces` (bit d: d steps) has, at the least total of kCost; with
+// parity 0 or 1 among the splits into an even or odd number of launches only.  Launches of 1, 2, 3, 4, 6 and 8 steps take
+// (K, us) FP64 419, 447, 507, 503, 602, 765 at 4096^2 and 39, 47, 52, 51, 70, - at 1200^2; FP32 203, 238, 254, 317, 437, 573
+// and, at 3001 x 2047, 98, 117, 135, 130, 180, 246; FP16 109, 159, -, 305, 432, - (5: 366).  kCost gives two launches of
+// nearly equal length and none of two or three steps where their sums come close, since on the smaller
+// grids those are the better ones: tables of the times at 4096^2 gain up to 5% there (FP64 7 steps 989 -> 936) and lose up to
+// 18% below (FP32 5 steps as 3 + 2 instead of 4 + 1 at 3001 x 2047 220 -> 251, 4096^2 469 -> 481 BGK, 516 -> 492 K; FP16 8 steps
+// as 6 + 2 instead of 4 + 4 at 1900^2 116 -> 137; FP64 11 steps at 1024^2 124 -> 136).
 constexpr int kPlanMax = 20;
 
 int plan_walk(int prec, int depth, int n, unsigned pieces, int parity, signed char (&plan)[kPlanMax]) {
