@@ -673,7 +673,10 @@ bool walk_takes_all(const lbm_batch* b) {
     return std::all_of(b->hdesc.begin(), b->hdesc.end(), walk_takes);
 }
 
-// Time of a row of a walking task by model, BGK = 1 (a grid of 1400^2 in FP64, 10.9 to 13.5 us per step).
+// Time of a row of a walking task by model, BGK = 1, as walking launches of one grid have it in FP64 (4096^2: 73 to 92 us
+// per step).  In FP32 and FP16 the models lie further apart (2048^2: CM 1.22, K 1.33), but a table of their own cuts
+// some batches better and others worse (us per step: FP32 32 of 400^2 27.0 -> 25.4, 24 of 300^2 14.8 -> 15.1, 56 of 64 to 512
+// a side 14.6 -> 15.1; FP16 26.0 -> 24.3, 13.6 -> 14.3, 13.5 -> 14.3): the cut follows from how the heights round.
 constexpr double kWalkRow[8] = {1.0, 1.065, 1.077, 1.137, 1.166, 1.24, 1.05, 1.12};
 
 // The tasks of the live instances, in the order given (by model), cut at about hs rows of BGK (an even number, spread
