@@ -58,11 +58,11 @@ struct AdjShape {
 };
 
 // Strips of kAdjRing rows run their rows side by side (k_adjoint_pass2) while all of their workgroups fit the
-// device's 256 CUs at once, two per CU in FP32 and FP16 and one in FP64, by their registers.  Measured (two
+// device at once, two per CU in FP32 and FP16 and one in FP64, by their registers.  Measured on 256 CUs (two
 // steps per launch, us per step, CM) against four waves per strip: 256 strips or fewer (256^2) FP32 3.2 against
 // 4.6, FP64 4.3 against 5.7; 288 (384^2) FP32 4.9 against 5.5, FP64 8.5 against 7.5; 512 (512^2) FP32 5.5 against
 // 6.2, FP64 9.5 against 10.0; 800 (640^2) FP32 8.6 against 8.1, FP64 18.2 against 17.2.
-constexpr unsigned kLowStrips = 512, kLowStrips64 = 256;
+constexpr unsigned low_strips_per_cu(int prec) { return prec == LBM_F64 ? 1u : 2u; }
 
 AdjShape adjoint_shape(const lbm_ctx* ctx) {
     AdjShape a;
@@ -72,7 +72,7 @@ AdjShape adjoint_shape(const lbm_ctx* ctx) {
     const long long h = (target + kAdjRing / 2) / kAdjRing * kAdjRing;
     a.hs = (int)(h < kAdjRing ? kAdjRing : (h > LBM_ADJ_MAX_ROWS ? LBM_ADJ_MAX_ROWS : h));
     a.nb = a.sx * (unsigned)((ctx->ny + a.hs - 1) / a.hs);
-    a.low = a.hs == kAdjRing && a.nb <= (ctx->prec == LBM_F64 ? kLowStrips64 : kLowStrips);
+    a.low = a.hs == kAdjRing && a.nb <= low_strips_per_cu(ctx->prec) * (unsigned)ctx->cus;
     return a;
 }
 
