@@ -17,9 +17,9 @@
 // ALU: 304 instructions per node in FP32 for CM, 266 in FP64 (441 and 412 with
 // the whole equilibrium carried back).
 //
-// Coefficient adjoints cb = (cpp, cpm, c11, c21, c12, c22, om) map to the rates by omega_adjoint:
-// d/domega_nu = -cpp/2 + cpm/2 - c11 + om, d/domega_b = -cpp/2 - cpm/2, d/domega_21 = -c21,
-// d/domega_12 = -c12, d/domega_22 = -c22.
+// Coefficient adjoints cb = (kpp, cpm, k11, k21, k12, k22, om), where c21, c12 and c22 = 1 + k count with their k, map to
+// the rates by omega_adjoint: d/domega_nu = -kpp/2 + cpm/2 - k11 + om, d/domega_b = -kpp/2 - cpm/2, d/domega_21 =
+// -k21, d/domega_12 = -k12, d/domega_22 = -k22.
 #pragma once
 
 #include "lbm_cell.hpp"
@@ -103,7 +103,7 @@ __device__ __forceinline__ void eq_adjoint(const Macro<R>& m, const Ref<R>& r, i
     mb.duy += dbb;
 }
 
-// Reverse of the whole collision of one cell.  cb: adjoints of (cpp, cpm, c11, c21, c12, c22, om) (those
+// Reverse of the whole collision of one cell.  cb: adjoints of (kpp, cpm, k11, k21, k12, k22, om) (those
 // the model does not have are zero).
 template <int MODEL, typename R>
 __device__ __forceinline__ void collide_adjoint(const R (&h)[9], const Macro<R>& m, const Ref<R>& ref,

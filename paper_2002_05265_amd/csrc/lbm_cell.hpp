@@ -64,11 +64,11 @@ __host__ __device__ constexpr double rest_weight(int i) {
     return i == 0 ? 4.0 / 9.0 : (i < 5 ? 1.0 / 9.0 : 1.0 / 36.0);
 }
 
-// Relaxation coefficients in the form used by the kernels: (1 - omega) factors, with the
-// second-order diagonal pair written as d20* = cpp d20 + cpm d02, d02* = cpm d20 + cpp d02, and the
-// factors k = c - 1 of the changes d* - d.
+// Relaxation coefficients in the form used by the kernels: factors k = -omega of the changes d* - d, with the
+// second-order diagonal pair written as d20* - d20 = kpp d20 + cpm d02, d02* - d02 = cpm d20 + kpp d02, and the
+// factors c = 1 - omega of the values themselves where a model needs those.
 template <typename R> struct Coef {
-    R cpp, cpm, c11, c21, c12, c22, om;  // om = omega_nu (BGK)
+    R cpm, c21, c12, c22, om;  // om = omega_nu (BGK)
     R kpp, k11, k21, k12, k22;
 };
 
@@ -77,9 +77,7 @@ __host__ __device__ inline Coef<R> make_coef(const double w[5]) {
     const double a = 0.5 * (1.0 - w[1]);  // trace
     const double b = 0.5 * (1.0 - w[0]);  // deviator
     Coef<R> c;
-    c.cpp = R(a + b);
     c.cpm = R(a - b);
-    c.c11 = R(1.0 - w[0]);
     c.c21 = R(1.0 - w[2]);
     c.c12 = R(1.0 - w[3]);
     c.c22 = R(1.0 - w[4]);
