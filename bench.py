@@ -128,6 +128,26 @@ def launch_steps(sim, model: str) -> int:
     return 3 if sim.fusion_depth(model) == 3 and ring in (4, 8) else 2
 
 
+def step_kernel_name(sim, model: str, prec: str) -> str:
+    """The kernel of launch_steps' launches: k_walk<steps>, k_tile, or a strip or single-step kernel."""
+    if hasattr(sim, "walk") and sim.walk(model)[0]:
+        return f"k_walk{sim.walk(model)[0]}"
+    if hasattr(sim, "tile") and sim.tile(model)[0]:
+        return "k_tile"
+    return {3: "k_step3n" if prec == "f64" else "k_step3", 2: "k_step2", 1: "k_step"}[launch_steps(sim, model)]
+
+
+def batch_launches(batch, tuned) -> dict:
+    """What a tuned batch runs: its kind of pass, and the settings that this kind has (None: it has not)."""
+    kind, walk_steps = batch.passes()
+    rows = batch.fusion()
+    if kind == 0:
+        return {"pass": "persistent", "nodes_per_thread": tuned[0], "groups_per_cu": tuned[1],
+                "steps_per_pass": batch.fusion_depth() if rows else 1, "strip_rows": rows}
+    return {"pass": "walking" if kind == 1 else "resident", "nodes_per_thread": None, "groups_per_cu": None,
+            "steps_per_pass": walk_steps if kind == 1 else None, "strip_rows": None}
+
+
 def profile_path(prec: str, kind: str) -> str:
     return os.path.join(PROFILE_DIR, f"step_kernels_{prec}_dsl4096_{kind}.md")
 
@@ -416,11 +436,7 @@ def batched_sweep(steps: int, plain_f64_mlups: float, n_inst: int = 512):
     fields = [inputs.sweep_fields(d) for d in insts]
     b = Batch(insts, fields, prec="f64", device="cuda:0")
     tuned = b.autotune(3)
-    fused_rows = b.fusion()  # 0: one step per pass won the autotuning
-    kind, walk_steps = b.passes()  # 1: walking passes, of at most walk_steps steps, won
-    per_pass = walk_steps if kind == 1 else (b.fusion_depth() if fused_rows else 1)
-    if kind == 1:
-        fused_rows = 0
+    launches = batch_launches(b, tuned)
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
     e0.record()
@@ -456,8 +472,7 @@ def batched_sweep(steps: int, plain_f64_mlups: float, n_inst: int = 512):
             "vs_plain_same_instances": round(mlups / (plain_updates / plain_sec / 1e6), 3),
             "blown_up": int(sum(1 for bl in blow if bl >= 0)),
             "blowup_steps_first10": blow[:10],
-            "autotuned": {"nodes_per_thread": tuned[0], "groups_per_cu": tuned[1],
-                          "steps_per_pass": per_pass, "strip_rows": fused_rows},
+            "autotuned": launches,
             "rebalance_every": 500, "precision": "f64"}
 
 
@@ -1098,7 +1113,7 @@ def main():
     dominant = max(models, key=lambda m: per_model[m]["launch_us"])  # the slowest kernel
     spl = per_model[dominant]["steps_per_launch"]
     dom_launch_us = per_model[dominant]["launch_us"]
-    kname = {3: "k_step3n" if args.prec == "f64" else "k_step3", 2: "k_step2", 1: "k_step"}.get(spl, f"k_walk{spl}")
+    kname = step_kernel_name(sims[dominant], dominant, args.prec)
     for m in models:
         rec = counter_record(m, args.prec) if n == 4096 else None
         lu = per_model[m]["launch_us"]
