@@ -1094,11 +1094,11 @@ def main():
 
     cells = n * n
     bpc = bytes_per_cell(args.prec)
-    per_model = {}
+    per_model, knames = {}, {}
     for m in models:
         ms = ev[m][0].elapsed_time(ev[m][1])
         ring, strip = sims[m].fusion(m)
-        spl = launch_steps(sims[m], m)
+        spl, knames[m] = launch_steps(sims[m], m), step_kernel_name(sims[m], m, args.prec)
         mlups = cells * args.steps / (ms * 1e-3) / 1e6
         gbs = mlups * 1e6 * bpc / spl / 1e9
         per_model[m] = {"mlups": round(mlups, 1), "us_per_step": round(ms * 1e3 / args.steps, 2),
@@ -1107,13 +1107,13 @@ def main():
                         "launch_us": round(launch_us[m], 2)}
     status = {m: s.status() for m, s in sims.items()}
     repeats = repeats_from(rw, cells, args.steps)
-    # last: its restoring lbm_set_fusion drops the contexts' two-step tail shape
+    # last: its restoring lbm_set_fusion drops the contexts' walking launches and two-step tail shape
     single = single_step_rates(sims, models, omega, cells, bpc, max(10, args.steps // 10))
     value = cells * args.steps * len(models) / wall / 1e6
     dominant = max(models, key=lambda m: per_model[m]["launch_us"])  # the slowest kernel
     spl = per_model[dominant]["steps_per_launch"]
     dom_launch_us = per_model[dominant]["launch_us"]
-    kname = step_kernel_name(sims[dominant], dominant, args.prec)
+    kname = knames[dominant]
     for m in models:
         rec = counter_record(m, args.prec) if n == 4096 else None
         lu = per_model[m]["launch_us"]
