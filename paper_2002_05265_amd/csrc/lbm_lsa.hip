@@ -50,13 +50,16 @@ __device__ __forceinline__ double inv_sqrt(double a) {
     const double e = fma(-(a * y), y, 1.0);
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
-// Principal square root (of a shift, which steers the convergence only: squares of values below 1e-145
-// may underflow to zero).
+// Principal square root.  a is first scaled by the power of four that brings it to order one, so that its squared
+// modulus neither overflows nor underflows.
 __device__ __forceinline__ cplx csqrt(cplx a) {
+    const double m = fmax(fabs(a.re), fabs(a.im));
+    if (!(m > 0.0)) return {0.0, 0.0};
+    const int e = __builtin_amdgcn_frexp_exp(m) & ~1;
+    a = {__builtin_amdgcn_ldexp(a.re, -e), __builtin_amdgcn_ldexp(a.im, -e)};
     const double n = cabs2(a);
-    if (!(n > 1e-290)) return {0.0, 0.0};
     const double h = 0.5 * (n * inv_sqrt(n) + fabs(a.re));
-    const double i = inv_sqrt(h), t = h * i, o = 0.5 * a.im * i;
+    const double i = inv_sqrt(h), t = __builtin_amdgcn_ldexp(h * i, e / 2), o = __builtin_amdgcn_ldexp(0.5 * a.im * i, e / 2);
     if (a.re >= 0.0) return {t, o};
     return {fabs(o), a.im >= 0.0 ? t : -t};
 }
