@@ -9,7 +9,8 @@
 // meet at an XCD-wide barrier each step or three; here a step touches no memory and costs two barriers of
 // the workgroup, eight LDS words each way and the collision per node, so that the vector ALU is the bound
 // once two instances share a CU.  512 threads of two nodes hold 1024 nodes, so two FP64 instances (64 KB
-// each) fit a CU and one computes while the other waits; larger instances take 1024 threads.
+// each) fit a CU and one computes while the other waits; larger instances take 1024 threads (FP64 ones of 2049 to
+// 2496 nodes three nodes each, at the 128 registers that 1024 threads leave with 56 bytes per lane in scratch).
 // Measured on MI355X, 640 instances of all models, 64 steps (us per step, three steps per persistent pass before,
 // resident now): 32^2 FP64 15.5 -> 3.8, FP32 18.0 -> 2.7; 40^2 FP64 18.2 -> 7.4, FP32 21.4 -> 5.6.
 //

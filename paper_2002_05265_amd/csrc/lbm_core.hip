@@ -289,15 +289,16 @@ constexpr long long kWideMinStrips = 1024;
 // Walking launches (lbm_walk.hpp) of a new context: the segment height that gives at most one wave per
 // slot of the device (two waves per SIMD in FP32 and FP16, one in FP64, where a wave takes more than half
 // of the SIMD's registers), so that all of them walk at once, and the most steps per launch that pays
-// for it; rows = 0 where the tile or strip launches stay faster.  Measured on MI355X (us per step, walking
-// against strip launches and, in brackets, tile launches, BGK / K):
-// - FP64: 768^2 5.7 / 7.0 against 6.3 / 7.0 (4.9 / 5.4), 1024^2 8.1 / 10.2 against 13.5 / 14.0 (8.4 / 9.9),
-//   2048^2 23.2 / 27.5 against 46.9 / 48.3, 4096^2 81 / 100 against 163 / 169;
-// - FP32: 1024^2 7.7 / 8.2 (5.4 / 6.4), 1470^2 12.8 / 16.5 (1450^2: 11.1 / 12.6), 1700^2 14.9 /
-//   18.5 (14.0 / 15.7), 2048^2 18.4 / 23.5 against
-//   26.2 / 27.6, 4096^2 55 / 73 against 88 / 86, 3001 x 2047 23.7 / 30.8 against 45.8 / 46.1;
-// - FP16: 1024^2 7.2 / 9.3 (5.0 / 5.9), 1470^2 12.2 / 16.1 (1450^2: 9.8 / 11.6), 1700^2 13.6 / 17.6
-//   (12.5 / 14.5), 2048^2 17.8 / 23.2 against 27.0 / 28.8, 4096^2 50 / 68 against 77 / 80.
+// for it; rows = 0 where the tile or strip launches stay faster.  Measured on MI355X (us per step, BGK / K, walking
+// against strip launches and, in brackets, tile launches):
+// - FP64: 768^2 5.6 / 6.8 against 7.7 / 7.9 (4.8 / 5.4), 1024^2 8.9 / 10.2 against 12.9 / 13.5 (10.0 / 10.4),
+//   2048^2 24 / 28 against 43 / 44 (47 / 48), 4096^2 75 / 93 against 162 / 168 (172 / 173);
+// - FP32: 1024^2 8.3 / 10.1 against 7.7 / 8.1 (6.2 / 6.6), 1450^2 11.6 / 13.8 against 15.5 / 15.9 (10.9 / 11.4), 1700^2
+//   14.2 / 17.5 against 20.2 / 20.8 (13.7 / 14.6), 1800^2 15.4 / 19.2 against 22.8 / 23.6 (16.3 / 16.9), 2048^2 17.9 / 22.9
+//   against 24.8 / 25.8 (26.7 / 27.2), 4096^2 53 / 72 against 82 / 85 (101 / 101), 3001 x 2047 23 / 31 against 45 / 45;
+// - FP16: 1024^2 7.9 / 10.2 against 9.0 / 9.0 (5.4 / 6.0), 1450^2 10.9 / 13.8 against 22.0 / 21.9 (9.5 / 10.5), 1700^2 13.2 /
+//   17.4 against 20.6 / 20.8 (12.0 / 13.2), 1800^2 14.4 / 19.1 against 22.9 / 23.3 (13.5 / 14.6), 2048^2 17.1 / 22.6 against
+//   26.5 / 27.3 (17.0 / 19.1), 4096^2 53 / 72 against 75 / 79 (66 / 75).
 // The line is drawn at the rows of a strip per slot (1024^2: 10 in FP64, 5 in FP32 and FP16; 1700^2: 13.3,
 // 2048^2: 19) and where at most a quarter of the strips' columns lie outside the grid.  A segment's first
 // 2 (D - 1) iterations fill up the D steps, so lower segments take fewer: FP64 1152^2 (14 rows) 9.7 / 11.7
@@ -332,8 +333,8 @@ WalkPick walk_pick(int nx, int ny, int prec, int cus) {
 // measured at each size): 3.6 us per launch, and per step the larger of 0.55 us, the latency of a patch's
 // step, and its work, by the nodes of the rows that are still valid, times the patches per CU.  A patch of
 // 44 in FP64 fills a CU's LDS, and one patch at a time hides no latency (768^2: 6.0 us per step, 32: 4.9).
-// patch = 0 where strips stay: grids of more than 2^22 nodes (FP32 4096^2: strips 5.5 us per million nodes,
-// tiles 4.8 / 5.4 at 1700^2) and grids of fewer than 16 nodes a side that need more than one patch per CU.
+// patch = 0 where strips stay: grids of more than 2^22 nodes (FP32 4096^2: strips 82 / 85 us per step, tiles 101)
+// and grids of fewer than 16 nodes a side that need more than one patch per CU.
 // They also stay in FP32 and FP16 on grids of at most 32 nodes a side whose patches come to more than 1.5 times the
 // grid's nodes and to more than 8 per CU (K, us per step against strip launches: FP16 150000 x 20, 1.83 times and 21
 // per CU, 20.2 against 19.6, FP32 21.1 against 20.4, FP32 166666 x 24, 1.52 and 24, 28.9 against 28.1; FP32 31250 x 16,

@@ -197,6 +197,8 @@ __device__ __forceinline__ Macro<R> macro_of(const R (&h)[9], const Ref<R>& ref,
         // unshifted storage: the reference is zero.  1 / rho by two Newton steps on the hardware
         // reciprocal: each is one fused correction, so the result is within an ulp (and all but a few
         // quotients correctly rounded) in five instructions against the eleven of a division
+        // (NaN where rho is 0, infinite or subnormal: a state with rho <= 0 is a blow-up in any case, and one
+        // with an infinite rho turns NaN in the collision by either)
         m.drho = (h[0] + m.s.s13) + (m.s.s24 + m.s.m22);
         m.rho = m.drho;
         rho_d = m.rho;

@@ -10,14 +10,14 @@
 // What bounds it: on a small grid a step launched alone costs 2.6-3 us, nearly all of it launch and memory
 // latency, and moves next to no bytes; a step of the patch costs two barriers, eight LDS words each way and
 // the collision, 0.45-0.75 us.  So the halo is recomputed rather than exchanged, as deep as the workgroups
-// still run at the same time (one per CU).  Measured on MI355X (us per step, BGK / K, strip launches before,
-// tile launches now):
-//   64^2    FP64 2.95 / 2.93 -> 0.82 / 0.92   FP32 2.61 / 2.63 -> 0.79 / 0.86   FP16 3.4 / 3.2 -> 0.84 / 0.90
-//   256^2   FP64 4.19 / 4.24 -> 1.33 / 1.48   FP32 3.58 / 3.68 -> 1.06 / 1.23   FP16 3.8 / 3.9 -> 1.13 / 1.29
-//   512^2   FP64 4.4  / 4.7  -> 2.82 / 3.15   FP32 2.74 / 3.03 -> 2.10 / 2.38   FP16 4.6 / 4.6 -> 1.95 / 2.28
-//   768^2   FP64 6.3  / 7.0  -> 4.94 / 5.37   FP32 5.3  / 5.6  -> 3.63 / 4.21   FP16 6.1 / 6.3 -> 3.32 / 4.08
-//   1024^2  FP64 8.7  / 10.9 -> 8.44 / 9.93   FP32 7.7  / 8.2  -> 5.43 / 6.38   FP16 7.2 / 9.3 -> 4.96 / 5.87
-// (FP64 from 512^2 and FP16 at 768^2 and 1024^2: walking launches before).  Two LDS buffers, for one barrier
+// still run at the same time (one per CU).  Measured on MI355X (us per step, BGK / K, strip launches -> tile launches
+// in runs of 240 steps, 48 at 1024^2):
+//   64^2    FP64 3.6  / 3.8  -> 0.79 / 0.86   FP32 3.3 / 3.7 -> 0.82 / 0.95   FP16 3.5 / 3.8 -> 0.89 / 1.03
+//   256^2   FP64 4.6  / 4.7  -> 1.33 / 1.47   FP32 4.1 / 4.2 -> 1.10 / 1.26   FP16 4.2 / 4.4 -> 1.12 / 1.31
+//   512^2   FP64 4.3  / 4.5  -> 2.82 / 3.14   FP32 2.7 / 3.0 -> 2.10 / 2.36   FP16 4.5 / 4.7 -> 1.92 / 2.21
+//   768^2   FP64 7.7  / 7.9  -> 4.76 / 5.38   FP32 5.3 / 5.6 -> 3.62 / 4.17   FP16 5.9 / 6.1 -> 3.25 / 3.90
+//   1024^2  FP64 12.9 / 13.5 -> 10.0 / 10.4   FP32 7.7 / 8.1 -> 6.20 / 6.60   FP16 9.0 / 9.0 -> 5.4  / 6.1
+// (FP64 1024^2 takes walking launches: 8.9 / 10.2).  Two LDS buffers, for one barrier
 // per step, gained nothing at any size (64^2 FP64 0.92 against 0.82) and halve the workgroups per CU; a patch
 // of 48 (768 threads, three nodes each) was never faster than 44.
 #pragma once

@@ -8,12 +8,12 @@
 // for another, so the number of steps is limited by registers alone: nine values per column and step,
 // 18 VGPRs in FP32 and 36 in FP64 for the two columns of a lane.  In FP32 and FP16 eight (six) steps leave
 // two waves per SIMD, which issue vector instructions all the time: that is the bound (K: 139 per node and
-// step, 73 us per step at 4096^2 where full issue would take 70).  In FP64 one wave per SIMD holds
-// eight steps (some values in accumulation registers) and issues about 65% of the time; one column per
-// lane and two waves took 83 / 105 us per step (BGK / K, 4096^2) against 77 / 96, as a quarter of its
-// lanes is halo against an eighth.  Four columns per lane in FP32 ran 3-12% slower (one wave per SIMD).
-// Measured at 4096^2, us per step, against the strip launches: FP32 BGK 55 (88), K 73 (86); FP64
-// BGK 81 (163), K 100 (169); FP16 BGK 50 (77), K 68 (80); the pure pull moves 4.7-4.9 TB/s in each.
+// step, 72 us per step at 4096^2 where full issue would take 70).  In FP64 one wave per SIMD holds
+// eight steps (some values in accumulation registers) and issues about 75% of the time; one column per
+// lane and two waves took 8-9% longer (4096^2), as a quarter of its lanes is halo against an eighth.  Four columns
+// per lane in FP32 ran 3-12% slower (one wave per SIMD).  Measured at 4096^2, us per step (BGK / K), against the strip
+// launches: FP32 53 / 72 (82 / 85), FP64 75 / 93 (162 / 168), FP16 53 / 72 (75 / 79); the pure pull moves 4.7-4.9 TB/s
+// in each.
 #pragma once
 
 #include <hip/hip_runtime.h>
