@@ -215,7 +215,7 @@ int lbm_get_fusion_depth(lbm_ctx* ctx, int model, int* steps);
  * strip of 112 columns and *rows rows with the steps kept in registers, so that each population is
  * read and written once per launch.  A new context takes them for every model where the grid has
  * enough strips to fill the device (from about 1024 x 1024 in FP64 and 1800 x 1800 in FP32 and FP16; in these not
- * on grids so low that its waves walk more than 1.85 times their share of the rows);
+ * for the heavier models on grids of at most 64 rows whose strips fill the device badly);
  * lbm_step then splits its steps into such launches of at most *steps steps and, for what they
  * do not fill, the launches that lbm_get_fusion and lbm_get_fusion_depth describe.
  * lbm_set_launch, lbm_set_fusion and lbm_set_fusion_depth turn them off for the model, lbm_autotune keeps them
@@ -227,8 +227,8 @@ int lbm_get_walk(lbm_ctx* ctx, int model, int* steps, int* rows);
  * by up to *steps steps in LDS, the valid part shrinking by one node on each side per step, and stores the
  * rest, *patch - 2 (*steps - 1) nodes a side.  A new context takes them for every model on grids of at most
  * 2^22 nodes that the walking launches do not take (on grids lower or narrower than 16 nodes while one
- * patch per CU is enough, and in FP32 and FP16 lower or narrower than 33 while the patches number at most 8 per CU
- * or come to at most 1.5 times the grid); lbm_step then splits two steps and more into as few launches as there can be, of
+ * patch per CU is enough; in FP32 and FP16 not CM, CHM and K on more than 2.5 million nodes in at most 24 rows);
+ * lbm_step then splits two steps and more into as few launches as there can be, of
  * nearly equal numbers of steps (a run of two, or in FP32 three, that one strip launch takes in even rounds of
  * workgroups goes to that launch).  lbm_set_launch, lbm_set_fusion and lbm_set_fusion_depth turn them off for
  * the model, lbm_autotune keeps them where they are the fastest.  Bit-identical to single steps.  *steps = *patch = 0

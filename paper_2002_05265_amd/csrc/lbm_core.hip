@@ -304,11 +304,6 @@ constexpr long long kWideMinStrips = 1024;
 // 2 (D - 1) iterations fill up the D steps, so lower segments take fewer: FP64 1152^2 (14 rows) 9.7 / 11.7
 // with six, 11.8 / 12.5 with four; 2048^2 (40 rows) 23.2 / 27.5 with six, 22.2 / 28.9 with eight; 4096^2
 // (152 rows) 89 / 103 with six; FP32 2600^2 (32 rows) 28.2 / 33.6 with six, 26.5 / 34.0 with eight.
-// On low and wide grids few segments fit beside each other, and slots stay empty or a second round is nearly so: in
-// FP32 and FP16, whose strip launches are bound by the ALU too, walking launches are left out where a slot walks
-// more than 1.85 times the rows per slot (K, us per step against strip launches: FP32 350000 x 40, 1.77 times, 76
-// against 80; FP16 200000 x 20, 1.72, 22.5 against 23.5; FP16 150000 x 40, 1.91, 40 against 36; FP32 125000 x 32, 2.64,
-// 33 against 26; in FP64 125000 x 16, 2.98, still 23 against 24).
 struct WalkPick {
     int rows, depth;
 };
@@ -323,9 +318,28 @@ WalkPick walk_pick(int nx, int ny, int prec, int cus) {
     const long long segments = std::max(1LL, slots / sx);
     const int hs = (int)((ny + segments - 1) / segments + 1) / 2 * 2;
     const int depth = prec == LBM_F16_SHIFTED || hs < (prec == LBM_F64 ? 48 : 28) ? 6 : 8;
-    const long long rounds = (sx * ((ny + hs - 1) / hs) + slots - 1) / slots;
-    if (prec != LBM_F64 && (double)(rounds * (hs + 2 * (depth - 1))) > 1.85 * per_slot) return {0, 0};
     return {hs, depth};
+}
+
+// Time of a row of a walking wave by model (the pull alone last), BGK = 1, in FP32 and FP16 (2048^2).
+constexpr double kWalkRow[9] = {1.0, 1.07, 1.08, 1.22, 1.23, 1.335, 1.05, 1.12, 1.0};
+
+// Whether walking launches of w pay for a model against strip launches.  On low and wide grids few segments fit beside
+// each other, so that slots stay empty or a second round is nearly so; in FP32 and FP16, whose strip launches are not
+// bound by the model's arithmetic there, the heavier models then lose.  The time of a walk is its rows, with the
+// 2 (D - 1) that fill it up, times the rounds (half a round where a last one is at most half full: its waves share
+// their SIMDs with no other), at 0.54 (FP16 0.585) us per step for BGK; that of the strips is 6.4 us per million nodes,
+// and more from 2^23 nodes on.  Measured (us per step, walk against strips): FP32 125000 x 32 BGK 24 / 25.5, K 33.0 / 26.3,
+// 150000 x 40 K 40.1 / 36.8, 250000 x 16 K 27.8 / 26.9, 300000 x 20 K 33.2 / 36.5, 83333 x 48 K 26.2 / 31.3, 140625 x 64 K
+// 61 / 78; FP16 125000 x 32 BGK 24 / 27, K 32.7 / 27.6, 150000 x 40 K 39.8 / 36.2.
+bool walk_pays(const WalkPick& w, int slot, int nx, int ny, int prec, int cus) {
+    if (prec == LBM_F64 || ny > 64 || (long long)nx * ny >= 1LL << 23) return true;
+    const long long slots = 8LL * cus;
+    const long long tasks = (long long)walk_strips(nx, walk_width<kF32>(), walk_cols<kF32>()) * ((ny + w.rows - 1) / w.rows);
+    const long long full = tasks / slots, last = tasks % slots;
+    const double rounds = (double)full + (last == 0 ? 0.0 : (full > 0 && 2 * last <= slots ? 0.5 : 1.0));
+    const double row = (prec == LBM_F16_SHIFTED ? 0.585 : 0.54) * kWalkRow[slot];
+    return row * rounds * (double)(w.rows + 2 * (w.depth - 1)) <= 6.4e-6 * (double)nx * (double)ny;
 }
 
 // Tile launches (lbm_tile_kernel.hpp) of a new context: the patch and the steps per launch with the least
@@ -335,10 +349,6 @@ WalkPick walk_pick(int nx, int ny, int prec, int cus) {
 // 44 in FP64 fills a CU's LDS, and one patch at a time hides no latency (768^2: 6.0 us per step, 32: 4.9).
 // patch = 0 where strips stay: grids of more than 2^22 nodes (FP32 4096^2: strips 82 / 85 us per step, tiles 101)
 // and grids of fewer than 16 nodes a side that need more than one patch per CU.
-// They also stay in FP32 and FP16 on grids of at most 32 nodes a side whose patches come to more than 1.5 times the
-// grid's nodes and to more than 8 per CU (K, us per step against strip launches: FP16 150000 x 20, 1.83 times and 21
-// per CU, 20.2 against 19.6, FP32 21.1 against 20.4, FP32 166666 x 24, 1.52 and 24, 28.9 against 28.1; FP32 31250 x 16,
-// 1.68 and 7, 4.6 against 4.7; 83333 x 48, 1.52 and 24, 30.5 against 31.2).
 struct TilePick {
     int patch, steps;
 };
@@ -362,12 +372,15 @@ TilePick tile_pick(int nx, int ny, int prec, int cus) {
                 pick = {pw, t};
             }
         }
-    if (pick.patch && prec != LBM_F64 && std::min(nx, ny) <= 32) {
-        const int tw = pick.patch - 2 * (pick.steps - 1);
-        const long long tiles = (long long)((nx + tw - 1) / tw) * ((ny + tw - 1) / tw);
-        if (tiles > 8LL * cus && (double)tiles * pick.patch * pick.patch > 1.5 * (double)nx * ny) return {0, 0};
-    }
     return pick;
+}
+
+// Whether tile launches pay for a model: not for the heaviest (CM, CHM, K) in FP32 and FP16 on large grids of at most 24
+// rows, where a patch is mostly halo and the strips are long (K, us per step against strip launches: FP16 150000 x 20
+// 20.2 / 19.6, 187500 x 16 19.9 / 19.8, FP32 150000 x 20 21.1 / 20.4, 166666 x 24 28.9 / 28.1; FP16 125000 x 16 13.9 / 15.0; BGK,
+// FP16 150000 x 20 16.2 / 19.0; 16 x 200000, in FP32, 22 / 70).
+bool tile_pays(int slot, int nx, int ny, int prec) {
+    return prec == LBM_F64 || kWalkRow[slot] < 1.2 || ny > 24 || (long long)nx * ny <= 2'500'000;
 }
 
 // The launches of a run of n <= kPlanMax steps: plan[i] steps in launch i, their number returned.  Walking
@@ -921,16 +934,20 @@ int strip_launches(const lbm_ctx* ctx, int model, int n) {
     return (n + most - 1) / most;
 }
 
-// Whether a run of n steps on a tile context goes to the strips all the same: two steps, or three in FP32, on a
-// context that runs three per launch, where one launch takes them all and its strips fill the last round of one per
-// CU to 15/16, in as many rounds as steps at most.  One tile launch has little to save then, and recomputes more.  Measured on
-// MI355X (us per call, K, tile against strips): two steps FP64 512^2 (512 strips) 10.8 against 9.1, 2048 x 128 (512)
-// 11.9 against 9.0, 520 x 512 (576) 10.5 against 13.5, FP32 512^2 7.8 against 7.3, 768 x 340 (516) 8.1 against 8.2;
-// 768 x 512 (768)
-// 8.3 against 9.5; three steps FP32 512^2 9.5 against 9.2, 768 x 512 12.9 against 11.1, 520 x 512 9.5 against 10.6, FP64
-// 512^2 13.0 against 13.6; four steps 15.5 against 27.5 and 11.5 against 19.0.
+// Whether a run of n steps on a tile context goes to the strips all the same:
+// - two steps, or three in FP32, on a context that runs three per launch, where one launch takes them all and its strips
+//   fill the last round of one per CU to 15/16, in as many rounds as steps at most: one tile launch has little to save
+//   then, and recomputes more (us per call, K, tile against strips: two steps FP64 512^2 (512 strips) 10.8 against 9.1,
+//   2048 x 128 (512) 11.9 against 9.0, 520 x 512 (576) 10.5 against 13.5, FP32 512^2 7.8 against 7.3, 768 x 340 (516) 8.1
+//   against 8.2, 768 x 512 (768) 8.3 against 9.5; three steps FP32 512^2 9.5 against 9.2, 768 x 512 12.9 against 11.1,
+//   520 x 512 9.5 against 10.6, FP64 512^2 13.0 against 13.6; four steps 15.5 against 27.5 and 11.5 against 19.0);
+// - runs that tile launches would take two steps at a time, in FP32 on more than 2.5 million nodes in 25 to 64 rows
+//   (120000 x 32 BGK, two steps 69 against 65, four 137 against 120; 80000 x 48 K 71.5 against 68 and 141 against 132;
+//   but 200000 x 16 BGK 43 against 57 and 85 against 104).
 bool short_run(const lbm_ctx* ctx, int model, int n) {
-    const int k = lbm_ctx::slot(model);
+    const int k = lbm_ctx::slot(model), launches = (n + ctx->tile_steps[k] - 1) / ctx->tile_steps[k];
+    const bool low = ctx->ny > 24 && ctx->ny <= 64 && (long long)ctx->nx * ctx->ny > 2'500'000;
+    if (ctx->prec == LBM_F32_SHIFTED && low && n <= 2 * launches && (strip_pieces(ctx, model) & 4u)) return true;
     if (n > (ctx->prec == LBM_F32_SHIFTED ? 3 : 2) || ctx->fuse_depth[k] != 3 || !(strip_pieces(ctx, model) >> n & 1))
         return false;
     const int hs = n == 2 && ctx->tail_ring[k] > 0 ? ctx->tail_strip[k] : ctx->fuse_strip[k];
@@ -1121,8 +1138,8 @@ int lbm_init_shifted(lbm_ctx** out, int nx, int ny, int prec, int eq_order, doub
     ctx->tile_patch = tile.patch;
     ctx->tile_most = tile.steps;
     for (int k = 0; k < 9; ++k) {
-        ctx->walk_depth[k] = walk.depth;
-        ctx->tile_steps[k] = walk.depth ? 0 : tile.steps;
+        ctx->walk_depth[k] = walk.depth && walk_pays(walk, k, nx, ny, prec, cus) ? walk.depth : 0;
+        ctx->tile_steps[k] = !ctx->walk_depth[k] && tile_pays(k, nx, ny, prec) ? tile.steps : 0;
     }
     int rc = check_hip(hipGetDevice(&ctx->device), "hipGetDevice");
     if (rc == LBM_OK) rc = scratch_address(ctx->device, &ctx->d_static);

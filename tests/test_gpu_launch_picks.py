@@ -48,3 +48,12 @@ def test_no_slower_than_strips(gpu, prec, nx, ny, n):
     print(f"picks {prec} {nx}x{ny} {n} steps: {now:.1f} us, strips {strips:.1f}", flush=True)
     assert now < 1.12 * strips
     s.close()
+
+
+@pytest.mark.parametrize("prec,nx,ny,model", [("f32", 16, 200000, "K"), ("f16", 32, 120000, "K"), ("f32", 60000, 16, "K"),
+                                              ("f16", 60000, 16, "BGK"), ("f32", 83333, 48, "K"), ("f32", 125000, 32, "BGK"),
+                                              ("f16", 160000, 20, "BGK"), ("f64", 120000, 32, "K")])
+def test_taken_where_they_gain(gpu, prec, nx, ny, model):
+    s = sim(gpu, prec, nx, ny, model)
+    assert s.walk(model)[0] + s.tile(model)[0] > 0
+    s.close()
